@@ -209,6 +209,19 @@ int ed_tables_find_rep(const ed_tables_t *t, int64_t n, const uint64_t *states, 
 int ed_build_basis(const ed_lattice_t *lat, const ed_group_t *grp, const ed_irrep_t *irrep,
                    int32_t n_up, const ed_tuning_t *tuning, void *stream, ed_basis_t **out);
 void ed_free_basis(ed_basis_t *b);
+/*
+ * Stored terms.  The target of an off-diagonal term and the element that maps
+ * it to its representative depend on the basis alone.  ed_build_basis(_fermions)
+ * therefore searches every term once and keeps 4 bytes per term, where that is
+ * at most 1/16 of the device's memory and half of what is free (hash-slot
+ * index; row index and coefficient class must fit the 32 bits); H.v, Lanczos
+ * and adjoint then read it instead of searching, with the same results bit for
+ * bit.  ed_basis_terms_bytes: device memory it takes (0: none).
+ * ed_basis_release_terms gives that memory back; later calls search again.
+ * Synchronises the device.
+ */
+int64_t ed_basis_terms_bytes(const ed_basis_t *b);
+int ed_basis_release_terms(ed_basis_t *b);
 int64_t ed_basis_dim(const ed_basis_t *b);
 int ed_basis_is_complex(const ed_basis_t *b);
 int ed_basis_info(const ed_basis_t *b, ed_basis_info_t *info);

@@ -101,6 +101,8 @@ PROTOTYPES = {
     "ed_tables_find_rep": (ctypes.c_int, [P, I64, P, P, P, P]),
     "ed_build_basis": (ctypes.c_int, [P, P, P, I32, P, P, P]),
     "ed_free_basis": (None, [P]),
+    "ed_basis_terms_bytes": (I64, [P]),
+    "ed_basis_release_terms": (ctypes.c_int, [P]),
     "ed_basis_dim": (I64, [P]),
     "ed_basis_is_complex": (ctypes.c_int, [P]),
     "ed_basis_info": (ctypes.c_int, [P, P]),
@@ -277,6 +279,14 @@ def ed_build_basis_fermions(arrays: ModelArrays, n_particles, tuning=None, strea
 
 def ed_free_basis(h):
     lib().ed_free_basis(h)
+
+
+def ed_basis_terms_bytes(h):
+    return lib().ed_basis_terms_bytes(h)
+
+
+def ed_basis_release_terms(h):
+    return check(lib().ed_basis_release_terms(h))
 
 
 def ed_basis_dim(h):

@@ -141,7 +141,7 @@ static constexpr double kTwoStageMinCandidates = 3.0;
 
 static int build_basis_common(const ed_lattice_t *lat, const ed_group_t *grp, const ed_irrep_t *irrep, int32_t n_up,
                               const ed_tuning_t *tuning, uint32_t lds_reserve, void *stream, ed_basis_t **out,
-                              bool fermion = false)
+                              bool fermion = false, bool own_terms = true)
 {
     auto t0 = std::chrono::steady_clock::now();
     if (!out) return set_error(ED_ERR_ARG, "null output handle");
@@ -238,6 +238,7 @@ static int build_basis_common(const ed_lattice_t *lat, const ed_group_t *grp, co
                                  (b->tuning.search_mode == 0 && b->mean_candidates >= kTwoStageMinCandidates));
     dm.staged = b->staged;
     rc = ed::launch_basis_build(b, stream);
+    if (!rc && own_terms) rc = ed::terms_build(b, stream);
     if (rc) {
         ed_free_basis(b);
         return rc;
@@ -264,6 +265,7 @@ void ed_free_basis(ed_basis_t *b)
     if (!b) return;
     (void)hipDeviceSynchronize();
     ed::free_lanczos_workspace(b);
+    ed::terms_free(b);
     for (void *p : b->allocs) (void)hipFree(p);
     delete b;
 }
@@ -531,7 +533,7 @@ int ed_build_multi(const ed_lattice_t *lat, const ed_group_t *grp, int32_t n_sec
     }
     const uint32_t reserve = mb->chi_in_lds ? (uint32_t)((chi_bytes + 15) & ~(size_t)15)
                                             : (mb->chi_signs ? (uint32_t)((ng + 15) & ~15) : 0u);
-    rc = build_basis_common(lat, grp, &trivial, n_up, &tn, reserve, stream, &mb->base);
+    rc = build_basis_common(lat, grp, &trivial, n_up, &tn, reserve, stream, &mb->base, false, false);
     if (rc) {
         delete mb;
         return rc;

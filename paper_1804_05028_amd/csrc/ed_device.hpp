@@ -568,12 +568,39 @@ struct Scalar<true> {
     using T = double2;
 };
 
+// Lanczos state at the start of a step.  Two copies alternate: a step's
+// kernels read one, and its last kernel writes the other for the next step,
+// so that no block reads what another block of its kernel writes.
 struct LzState {
     int j;              // step index
     int done;           // breakdown or finished
     double scale;       // running max(|alpha_k|, beta_k)
-    double alpha_cur, beta_cur, beta_prev;
+    double beta_prev;
 };
+
+// One off-diagonal term, the same in every kernel that sums them (stored
+// terms, hash slots, Limits), so that all give the same bits: kr, ki is the
+// exchange amplitude times the character, v = sqrt(n_j) x_j the scaled
+// amplitude of the target, and 1/sqrt(n_i) is applied to the finished sum.
+template <bool CPLX>
+__device__ __forceinline__ void add_term(double &ar, double &ai, double kr, double ki, double vr, double vi)
+{
+    if (CPLX) {
+        ar = fma(kr, vr, fma(-ki, vi, ar));
+        ai = fma(kr, vi, fma(ki, vr, ai));
+    } else {
+        ar = fma(kr, vr, ar);
+    }
+}
+
+// Re(conj(gy_i) t): a bond's flip term t = chi v in row i against gy_i
+template <bool CPLX>
+__device__ __forceinline__ double adjoint_term(double cr, double ci, double vr, double vi, double g_r, double g_i)
+{
+    if (!CPLX) return g_r * (cr * vr);
+    const double tr = fma(cr, vr, -(ci * vi)), ti = fma(cr, vi, ci * vr);
+    return fma(g_r, tr, g_i * ti);
+}
 
 template <bool CPLX, typename AT>
 __device__ __forceinline__ void chi_of(const Ctx<AT> &c, uint32_t g, double &cr, double &ci)
@@ -650,6 +677,34 @@ inline int lds_limit()
         hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v <= 0)
         v = 65536;
     return v;
+}
+
+// sum over a block of at most 1024 threads, valid in thread 0 (sh: one
+// double per wave)
+__device__ __forceinline__ double block_sum(double v, double *sh)
+{
+    v = wave_sum(v);
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    __syncthreads();
+    if (lane == 0) sh[wave] = v;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < (int)(blockDim.x / kWave); ++w) t += sh[w];
+    return t;
+}
+
+// the sum of n partial sums, by all threads of a block in a fixed order; every
+// thread gets it (sh: one double per wave and one more)
+__device__ __forceinline__ double total_of(const double *partials, int n, double *sh)
+{
+    double a = 0.0;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) a += partials[k];
+    const double t = block_sum(a, sh);
+    double *res = sh + blockDim.x / kWave;
+    if (threadIdx.x == 0) *res = t;
+    __syncthreads();
+    return *res;
 }
 
 int upload_couplings(const ed_basis *bc, const double *J, const double *Jz, hipStream_t st, double *jsum_quarter);

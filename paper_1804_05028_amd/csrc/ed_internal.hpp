@@ -136,6 +136,24 @@ struct ed_basis {
     // (32 bytes real, 64 bytes complex), allocated by the first fused call
     // and freed with the handle
     char *adj_slots = nullptr;
+    // stored terms: the target and coefficient class of every off-diagonal
+    // term (ed_terms.hip), made with the basis where they fit, freed with it
+    // or by ed_basis_release_terms
+    struct {
+        void *words = nullptr;         // groups of 64 lanes x 4 words, slice by slice
+        uint64_t *off = nullptr;       // [n_slices] first group of a slice (nullptr: slice * stride)
+        uint32_t *cnt = nullptr;       // [n_slices] groups of a slice
+        uint32_t stride = 0;
+        double *xs = nullptr;          // [dim + 1] scaled input, its last entry 0
+        double *pair = nullptr;        // [dim + 1] {x, gy} scaled, made by the first fused adjoint
+        double *cls = nullptr;         // [n_cls] coefficients of the current couplings
+        double *cls_chi = nullptr;     // [n_cls] characters
+        std::vector<double> chi_vals;  // distinct characters (re, im)
+        std::vector<int> orbit_bond;   // first bond of every orbit
+        int n_orb = 0, n_cls = 0, ibits = 0;
+        int64_t bytes = 0;
+        bool couplings_ok = false;     // the current couplings are equal, bit for bit, on every orbit
+    } terms;
     // Lanczos workspace, kept between calls and freed with the handle
     struct {
         double *vec[3] = {nullptr, nullptr, nullptr};
@@ -189,6 +207,21 @@ bool backward_fusable(const ed_basis *b);
 int run_lanczos(const ed_basis *b, const double *J, const double *Jz, const void *v0, int n_steps, double *alpha, double *beta,
                 int *n_done, void *psi0, void *stream);
 int check_couplings(const ed_basis *b, const double *J);
+int scan_counts(const uint32_t *counts, uint64_t *offsets, uint64_t n, void *stream);
+// Stored terms (ed_terms.hip)
+int terms_build(ed_basis *b, void *stream);
+void terms_free(ed_basis *b);
+int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream);
+inline bool terms_usable(const ed_basis *b) { return b->terms.words && b->terms.couplings_ok; }
+// a sector whose scaled input fits the LDS of every block: its H.v reads x itself
+inline bool terms_small(const ed_basis *b) { return b->db.dim <= (b->dm.is_complex ? 2048 : 4096); }
+int terms_grid(const ed_basis *b);
+int terms_apply(const ed_basis *b, const void *x, void *y, double jsq, void *stream);
+int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *vprev, double *partials, const void *lz,
+                        double jsq, void *stream);
+int sum_partials_cols(const double *partials, int nrows, int ncols, double *out, void *stream);
+int terms_backward(const ed_basis *b, const void *x, const void *gy, void *gx, double *gJ_host, double *scratch,
+                   size_t scratch_doubles, double jsq, void *stream);
 // Batched sectors (ed_multi.hip)
 int multi_setup(ed_multi *mb, void *stream);
 int multi_apply(const ed_multi *mb, const double *J, const void *x, void *y, void *stream);

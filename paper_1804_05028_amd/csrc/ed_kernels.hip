@@ -131,9 +131,7 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
                 ++kept;
                 double cr, ci;
                 chi_of<CPLX>(c, g, cr, ci);
-                const double amp = jh * rs_i * c.div_sqrt[key >> kNormShift];
-                ar += amp * (cr * vr - ci * vi);
-                if (CPLX) ai += amp * (cr * vi + ci * vr);
+                add_term<CPLX>(ar, ai, jh * cr, jh * ci, vr, vi);
             }
         } else if (INDEX == IDX_HASH) {
             // term counting
@@ -165,13 +163,12 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
                 if (MODE == 1) continue;
                 double cr, ci;
                 chi_of<CPLX>(c, g, cr, ci);
-                const double amp = bd.jhalf * rs_i * c.div_sqrt[ej >> kNormShift];
+                const double sq = c.div_sqrt[ej >> kNormShift];
                 if (CPLX) {
                     const double2 xv = *(const double2 *)&x[j];
-                    ar += amp * (cr * xv.x - ci * xv.y);
-                    ai += amp * (cr * xv.y + ci * xv.x);
+                    add_term<CPLX>(ar, ai, bd.jhalf * cr, bd.jhalf * ci, xv.x * sq, xv.y * sq);
                 } else {
-                    ar += amp * cr * *(const double *)&x[j];
+                    add_term<CPLX>(ar, ai, bd.jhalf * cr, 0.0, *(const double *)&x[j] * sq, 0.0);
                 }
             }
         }
@@ -180,21 +177,21 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
         if (CPLX) {
             const double2 xi = MODE == 2 ? *(const double2 *)&xi_pf : *(const double2 *)&x[i];
             double2 out;
-            out.x = d * xi.x + ar;
-            out.y = d * xi.y + ai;
+            out.x = fma(rs_i, ar, d * xi.x);
+            out.y = fma(rs_i, ai, d * xi.y);
             if (MODE == 2) {
                 const double2 vp = *(const double2 *)&vp_pf;
-                out.x -= beta_prev * vp.x;
-                out.y -= beta_prev * vp.y;
-                acc_part += xi.x * out.x + xi.y * out.y;   // Re(conj(v) w)
+                out.x = fma(-beta_prev, vp.x, out.x);
+                out.y = fma(-beta_prev, vp.y, out.y);
+                acc_part = fma(xi.x, out.x, fma(xi.y, out.y, acc_part));   // Re(conj(v) w)
             }
             *(double2 *)&y[i] = out;
         } else {
             const double xi = MODE == 2 ? *(const double *)&xi_pf : *(const double *)&x[i];
-            double out = d * xi + ar;
+            double out = fma(rs_i, ar, d * xi);
             if (MODE == 2) {
-                out -= beta_prev * *(const double *)&vp_pf;
-                acc_part += xi * out;
+                out = fma(-beta_prev, *(const double *)&vp_pf, out);
+                acc_part = fma(xi, out, acc_part);
             }
             *(double *)&y[i] = out;
         }
@@ -217,24 +214,37 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
     }
 }
 
-// x -> value fields of the slot table (hash index); slot_of gives each
-// representative's slot
-__global__ void k_pack_real(const double *x, const uint32_t *slot_of, char *slots, int64_t D)
+// where the scaled amplitudes sqrt(n_j) x_j of an H.v's input go: the stored
+// terms' dense array, the value fields of the hash slots, or nowhere (the
+// Limits kernels scale what they gather)
+enum { TO_TERMS = 0, TO_SLOTS = 1, TO_NONE = 2 };
+
+template <bool CPLX, int TO>
+__device__ __forceinline__ void put_scaled(char *dst, const uint32_t *slot_of, int64_t j, double sq,
+                                           typename Scalar<CPLX>::T v)
 {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x)
-        *(double *)(slots + (size_t)slot_of[j] * 16 + 8) = x[j];
+    if (TO == TO_NONE) return;
+    const size_t at = TO == TO_SLOTS ? (size_t)slot_of[j] * (CPLX ? 32 : 16) + (CPLX ? 16 : 8) : (size_t)j * sizeof v;
+    if constexpr (CPLX)
+        *(double2 *)(dst + at) = make_double2(v.x * sq, v.y * sq);
+    else
+        *(double *)(dst + at) = v * sq;
 }
 
-__global__ void k_pack_cplx(const double2 *x, const uint32_t *slot_of, char *slots, int64_t D)
+// scaled amplitudes of x; sqrts: the square roots of the divisors of |G|
+template <bool CPLX, int TO>
+__global__ void k_pack(const typename Scalar<CPLX>::T *x, const uint64_t *states, const double *sqrts,
+                       const uint32_t *slot_of, char *dst, int64_t D)
 {
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x)
-        *(double2 *)(slots + (size_t)slot_of[j] * 32 + 16) = x[j];
+        put_scaled<CPLX, TO>(dst, slot_of, j, sqrts[states[j] >> kNormShift], x[j]);
 }
 
 // ---------------------------------------------------------------------------
 // Adjoint slots at the positions of the H.v slots (same keys, same probe
 // sequences): 32 bytes {key, x, gy, -} for a real sector, 64 bytes
-// {key, -, x, gy, -} for a complex one (one 128-byte line either way).
+// {key, -, x, gy, -} for a complex one (one 128-byte line either way), the
+// amplitudes scaled by sqrt(n) as in the H.v slots.
 // ---------------------------------------------------------------------------
 
 template <bool CPLX>
@@ -248,17 +258,19 @@ __global__ void k_adj_slots_keys(const char *slots, char *adj, uint64_t n_slots)
 
 template <bool CPLX>
 __global__ void k_pack_adj(const typename Scalar<CPLX>::T *x, const typename Scalar<CPLX>::T *gy,
-                           const uint32_t *slot_of, char *adj, int64_t D)
+                           const uint64_t *states, const double *sqrts, const uint32_t *slot_of, char *adj, int64_t D)
 {
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x) {
+        const double sq = sqrts[states[j] >> kNormShift];
         if (CPLX) {
             char *p = adj + ((size_t)slot_of[j] << 6);
-            *(double2 *)(p + 16) = *(const double2 *)&x[j];
-            *(double2 *)(p + 32) = *(const double2 *)&gy[j];
+            const double2 a = *(const double2 *)&x[j], g = *(const double2 *)&gy[j];
+            *(double2 *)(p + 16) = make_double2(a.x * sq, a.y * sq);
+            *(double2 *)(p + 32) = make_double2(g.x * sq, g.y * sq);
         } else {
             char *p = adj + ((size_t)slot_of[j] << 5);
-            *(double *)(p + 8) = *(const double *)&x[j];
-            *(double *)(p + 16) = *(const double *)&gy[j];
+            *(double *)(p + 8) = *(const double *)&x[j] * sq;
+            *(double *)(p + 16) = *(const double *)&gy[j] * sq;
         }
     }
 }
@@ -351,7 +363,7 @@ __global__ void __launch_bounds__(1024) k_backward_J(DevModel dm, DevBasis db, c
                 const double2 xv = *(const double2 *)&x[i];
                 g_r = gv.x;
                 g_i = gv.y;
-                gx_r = gv.x * xv.x + gv.y * xv.y;
+                gx_r = fma(gv.x, xv.x, gv.y * xv.y);
             } else {
                 g_r = *(const double *)&gy[i];
                 gx_r = g_r * *(const double *)&x[i];
@@ -375,17 +387,10 @@ __global__ void __launch_bounds__(1024) k_backward_J(DevModel dm, DevBasis db, c
                 if (resolve_adj<CPLX>(db, adj, slot_of_state(r, db.slot_log2), r, key, xj, gj)) {
                     double cr, ci;
                     chi_of<CPLX>(c, g, cr, ci);
-                    const double sq = c.div_sqrt[key >> kNormShift];
                     // the per-bond term exactly as the unfused branch forms it
-                    const double vr = xj.x, vi = CPLX ? xj.y : 0.0;
-                    const double amp = 0.5 * sq * rs_i;
-                    const double tr = amp * (cr * vr - ci * vi), ti = amp * (cr * vi + ci * vr);
-                    contrib += g_r * tr + g_i * ti;
+                    contrib = fma(0.5 * rs_i, adjoint_term<CPLX>(cr, ci, xj.x, xj.y, g_r, g_i), contrib);
                     // and the H gy term exactly as k_apply forms it
-                    const double wr = gj.x, wi = CPLX ? gj.y : 0.0;
-                    const double ampg = bd.jhalf * rs_i * c.div_sqrt[key >> kNormShift];
-                    ar += ampg * (cr * wr - ci * wi);
-                    if (CPLX) ai += ampg * (cr * wi + ci * wr);
+                    add_term<CPLX>(ar, ai, bd.jhalf * cr, bd.jhalf * ci, gj.x, gj.y);
                 }
             } else if (anti) {
                 contrib = -0.5 * gx_r;
@@ -398,34 +403,27 @@ __global__ void __launch_bounds__(1024) k_backward_J(DevModel dm, DevBasis db, c
                 double cr, ci;
                 chi_of<CPLX>(c, g, cr, ci);
                 bool found = false;
-                double sq = 0.0, vr = 0.0, vi = 0.0;
+                double vr = 0.0, vi = 0.0;
                 if (INDEX == IDX_HASH) {
                     const uint64_t sl = slot_of_state(r, db.slot_log2);
                     uint64_t key;
-                    if (resolve_slot<CPLX>(db, load_slot<CPLX>(db.slots, sl), sl, r, key, vr, vi)) {
-                        found = true;
-                        sq = c.div_sqrt[key >> kNormShift];
-                    }
+                    found = resolve_slot<CPLX>(db, load_slot<CPLX>(db.slots, sl), sl, r, key, vr, vi);
                 } else {
                     uint64_t ej = 0;
                     const int64_t j = lookup_limits(c, db, r, mval, ej);
                     if (j >= 0) {
                         found = true;
-                        sq = c.div_sqrt[ej >> kNormShift];
+                        const double sq = c.div_sqrt[ej >> kNormShift];
                         if (CPLX) {
                             const double2 xv = *(const double2 *)&x[j];
-                            vr = xv.x;
-                            vi = xv.y;
+                            vr = xv.x * sq;
+                            vi = xv.y * sq;
                         } else {
-                            vr = *(const double *)&x[j];
+                            vr = *(const double *)&x[j] * sq;
                         }
                     }
                 }
-                if (found) {
-                    const double amp = 0.5 * sq * rs_i;
-                    const double tr = amp * (cr * vr - ci * vi), ti = amp * (cr * vi + ci * vr);
-                    contrib += g_r * tr + g_i * ti;   // Re(conj(gy) t)
-                }
+                if (found) contrib = fma(0.5 * rs_i, adjoint_term<CPLX>(cr, ci, vr, vi, g_r, g_i), contrib);
             }
             const double wsum = wave_sum(contrib);
             if (lane == (b & (kWave - 1))) {
@@ -440,11 +438,11 @@ __global__ void __launch_bounds__(1024) k_backward_J(DevModel dm, DevBasis db, c
             const double d = jsum_quarter - anti_sum;
             if (CPLX) {
                 double2 out;
-                out.x = d * g_r + ar;
-                out.y = d * g_i + ai;
+                out.x = fma(rs_i, ar, d * g_r);
+                out.y = fma(rs_i, ai, d * g_i);
                 *(double2 *)&gx[2 * i] = out;
             } else {
-                gx[i] = d * g_r + ar;
+                gx[i] = fma(rs_i, ar, d * g_r);
             }
         }
     }
@@ -465,13 +463,24 @@ __global__ void __launch_bounds__(1024) k_backward_J(DevModel dm, DevBasis db, c
     }
 }
 
-__global__ void k_sum_partials_cols(const double *partials, int nrows, int ncols, double *out)
+// column sums of the per-block partial sums, one block per column in a fixed
+// order (one thread per column walked the rows in a chain: 54 us for 512
+// blocks, 64 columns)
+__global__ void __launch_bounds__(256) k_sum_partials_cols(const double *partials, int nrows, int ncols, double *out)
 {
-    for (int col = blockIdx.x * blockDim.x + threadIdx.x; col < ncols; col += gridDim.x * blockDim.x) {
-        double t = 0.0;
-        for (int r = 0; r < nrows; ++r) t += partials[(size_t)r * ncols + col];
-        out[col] = t;
-    }
+    __shared__ double sh[256 / kWave];
+    double t = 0.0;
+    for (int r = threadIdx.x; r < nrows; r += blockDim.x) t += partials[(size_t)r * ncols + blockIdx.x];
+    t = block_sum(t, sh);
+    if (threadIdx.x == 0) out[blockIdx.x] = t;
+}
+
+int sum_partials_cols(const double *partials, int nrows, int ncols, double *out, void *stream)
+{
+    hipLaunchKernelGGL(k_sum_partials_cols, dim3(ncols), dim3(256), 0, (hipStream_t)stream, partials, nrows, ncols, out);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "adjoint sums: %s", hipGetErrorString(e));
+    return ED_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -672,6 +681,7 @@ __global__ void k_slots_insert(const uint64_t *states, int64_t D, char *slots, i
             const unsigned long long old = atomicCAS(kp, (unsigned long long)kEmpty, (unsigned long long)key);
             if (old == kEmpty) {
                 slot_of[j] = (uint32_t)sl;
+                kp[1] = (unsigned long long)j;   // the row, until an amplitude takes its place
                 done = true;
                 break;
             }
@@ -692,19 +702,6 @@ __global__ void k_unpack_states(const uint64_t *packed, uint64_t *out, int64_t D
 // ---------------------------------------------------------------------------
 constexpr int kVecThreads = 256;
 
-__device__ double block_sum(double v, double *sh)
-{
-    v = wave_sum(v);
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    __syncthreads();
-    if (lane == 0) sh[wave] = v;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < (int)(blockDim.x / kWave); ++w) t += sh[w];
-    return t;   // valid in thread 0
-}
-
 __global__ void __launch_bounds__(kVecThreads) k_norm2_partial(const double *v, int64_t n, double *partials)
 {
     __shared__ double sh[kVecThreads / kWave];
@@ -715,41 +712,35 @@ __global__ void __launch_bounds__(kVecThreads) k_norm2_partial(const double *v, 
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-// v_out = v_in / sqrt(sum of partials), the sum recomputed in fixed order per block
+// The partial sums of a reduction are added up by every block of the kernel
+// that needs the total, all of its threads in a fixed order (total_of), in
+// place of a kernel of one thread between the two: that thread walked up to
+// 2048 values in a chain, 25 + 67 us of the 410 us step at 3.6e5 rows.
+
+// v_out = v_in / sqrt(sum of partials)
 __global__ void __launch_bounds__(kVecThreads) k_scale_by_norm(const double *vin, double *vout, int64_t n,
                                                                   const double *partials, int np)
 {
-    __shared__ double inv;
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int k = 0; k < np; ++k) t += partials[k];
-        inv = t > 0.0 ? 1.0 / sqrt(t) : 0.0;
-    }
-    __syncthreads();
+    __shared__ double sh[kVecThreads / kWave + 1];
+    const double t = total_of(partials, np, sh);
+    const double inv = t > 0.0 ? 1.0 / sqrt(t) : 0.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         vout[i] = vin[i] * inv;
 }
 
-__global__ void k_lz_alpha(LzState *lz, const double *partials, int np, double *alpha_hist)
+// alpha = sum of <v, w> partials; w -= alpha v; partial |w|^2; psi += s_j v
+// (second pass).  n counts doubles: complex vectors are handled by the same
+// loop since alpha is real.
+__global__ void __launch_bounds__(kVecThreads) k_lz_update(double *w, const double *v, int64_t n, const double *dots,
+                                                              int n_dots, double *partials, const LzState *lz,
+                                                              double *alpha_hist, double *psi, const double *svec)
 {
+    __shared__ double sh[kVecThreads / kWave + 1];
     if (lz->done) return;
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double t = 0.0;
-        for (int k = 0; k < np; ++k) t += partials[k];
-        lz->alpha_cur = t;
-        alpha_hist[lz->j] = t;
-    }
-}
-
-// w -= alpha v ; partial |w|^2 ; psi += s_j v (second pass).  n counts
-// doubles: complex vectors are handled by the same loop since alpha is real.
-__global__ void __launch_bounds__(kVecThreads) k_lz_update(double *w, const double *v, int64_t n, double *partials,
-                                                              const LzState *lz, double *psi, const double *svec)
-{
-    __shared__ double sh[kVecThreads / kWave];
-    if (lz->done) return;
-    const double a = lz->alpha_cur;
-    const double sj = psi ? svec[lz->j] : 0.0;
+    const int j = lz->j;
+    const double a = total_of(dots, n_dots, sh);
+    if (blockIdx.x == 0 && threadIdx.x == 0) alpha_hist[j] = a;
+    const double sj = psi ? svec[j] : 0.0;
     double acc = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double vi = v[i];
@@ -762,34 +753,46 @@ __global__ void __launch_bounds__(kVecThreads) k_lz_update(double *w, const doub
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-__global__ void k_lz_beta(LzState *lz, const double *partials, int np, double *beta_hist, int n_steps, double tol)
+// beta = |w|; v_new = w / beta over the oldest vector, and sqrt(n) v_new to
+// where the next H.v reads it; the state of the next step
+template <bool CPLX, int TO>
+__global__ void __launch_bounds__(kVecThreads)
+    k_lz_next(const typename Scalar<CPLX>::T *w, typename Scalar<CPLX>::T *vnew, int64_t D, const double *partials, int np,
+              const LzState *lz, LzState *lz_next, const double *alpha_hist, double *beta_hist, int n_steps, double tol,
+              const uint64_t *states, const double *sqrts, const uint32_t *slot_of, char *dst)
 {
-    if (lz->done) return;
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double t = 0.0;
-        for (int k = 0; k < np; ++k) t += partials[k];
-        const double b = sqrt(t);
-        beta_hist[lz->j] = b;
-        lz->beta_cur = b;
-        lz->scale = fmax(lz->scale, fmax(fabs(lz->alpha_cur), b));
-        lz->j += 1;
-        if (b <= tol * lz->scale || lz->j >= n_steps) lz->done = 1;
+    __shared__ double sh[kVecThreads / kWave + 1];
+    const LzState cur = *lz;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (cur.done) {
+        if (first) *lz_next = cur;
+        return;
     }
-}
-
-// v_new = w / beta_j, written over the oldest vector
-__global__ void __launch_bounds__(kVecThreads) k_lz_normalize(const double *w, double *vnew, int64_t n, const LzState *lz)
-{
-    if (lz->done) return;
-    const double inv = 1.0 / lz->beta_cur;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        vnew[i] = w[i] * inv;
-}
-
-__global__ void k_lz_shift_beta(LzState *lz)
-{
-    if (lz->done) return;
-    if (threadIdx.x == 0 && blockIdx.x == 0) lz->beta_prev = lz->beta_cur;
+    const double b = sqrt(total_of(partials, np, sh));
+    const double scale = fmax(cur.scale, fmax(fabs(alpha_hist[cur.j]), b));
+    const bool done = b <= tol * scale || cur.j + 1 >= n_steps;
+    if (first) {
+        beta_hist[cur.j] = b;
+        LzState nx;
+        nx.j = cur.j + 1;
+        nx.done = done ? 1 : 0;
+        nx.scale = scale;
+        nx.beta_prev = b;
+        *lz_next = nx;
+    }
+    if (done) return;
+    const double inv = 1.0 / b;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < D; i += (int64_t)gridDim.x * blockDim.x) {
+        typename Scalar<CPLX>::T v = w[i];
+        if constexpr (CPLX) {
+            v.x *= inv;
+            v.y *= inv;
+        } else {
+            v *= inv;
+        }
+        vnew[i] = v;
+        if (TO != TO_NONE) put_scaled<CPLX, TO>(dst, slot_of, i, sqrts[states[i] >> kNormShift], v);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1019,7 +1022,9 @@ int upload_couplings(const ed_basis *bc, const double *J, const double *Jz, hipS
         }
         char *dst = (char *)b->dm.blob + b->dm.off_bonds;
         HIP_TRY(hipMemcpyAsync(dst, bz.data(), (size_t)t.nb * sizeof(BondLds), hipMemcpyHostToDevice, st));
+        const int rc = terms_couplings(b, key.data(), key.data() + t.nb, st);
         HIP_TRY(hipStreamSynchronize(st));
+        if (rc) return rc;
         b->J_cache = key;
         return ED_OK;
     }
@@ -1039,7 +1044,9 @@ int upload_couplings(const ed_basis *bc, const double *J, const double *Jz, hipS
     }
     char *dst = (char *)b->dm.blob + b->dm.off_bonds;
     HIP_TRY(hipMemcpyAsync(dst, bz.data(), (size_t)t.nb * sizeof(BondLds), hipMemcpyHostToDevice, st));
+    const int rc = terms_couplings(b, J, Jz, st);
     HIP_TRY(hipStreamSynchronize(st));
+    if (rc) return rc;
     b->J_cache = key;
     return ED_OK;
 }
@@ -1085,6 +1092,59 @@ static void launch_cfg(const ed_basis *b, Kern kern, size_t lds, int *grid, int 
 
 // ---- basis build ---------------------------------------------------------
 
+// offsets = exclusive prefix sum of counts; synchronises
+int scan_counts(const uint32_t *counts, uint64_t *offsets, uint64_t n_counts, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    std::vector<std::pair<uint64_t *, uint64_t>> levels;
+    uint64_t n = n_counts;
+    const void *in = counts;
+    bool in32 = true;
+    uint64_t *outp = offsets;
+    std::vector<void *> tmp;
+    int rc = ED_OK;
+    while (true) {
+        const uint64_t tiles = (n + kScanTile - 1) / kScanTile;
+        uint64_t *sums = nullptr;
+        if (hipMalloc((void **)&sums, std::max<uint64_t>(tiles, 1) * 8) != hipSuccess) {
+            (void)hipGetLastError();
+            rc = set_error(ED_ERR_OOM, "scan scratch");
+            break;
+        }
+        tmp.push_back(sums);
+        if (in32)
+            hipLaunchKernelGGL(k_scan_tile<uint32_t>, dim3((unsigned)tiles), dim3(kScanThreads), 0, st,
+                               (const uint32_t *)in, outp, n, sums);
+        else
+            hipLaunchKernelGGL(k_scan_tile<uint64_t>, dim3((unsigned)tiles), dim3(kScanThreads), 0, st,
+                               (const uint64_t *)in, outp, n, sums);
+        levels.push_back({outp, n});
+        if (tiles == 1) break;
+        uint64_t *next_out = nullptr;
+        if (hipMalloc((void **)&next_out, tiles * 8) != hipSuccess) {
+            (void)hipGetLastError();
+            rc = set_error(ED_ERR_OOM, "scan scratch");
+            break;
+        }
+        tmp.push_back(next_out);
+        in = sums;
+        in32 = false;
+        outp = next_out;
+        n = tiles;
+    }
+    for (int lv = (int)levels.size() - 2; rc == ED_OK && lv >= 0; --lv) {
+        const uint64_t nn = levels[lv].second;
+        const unsigned g = (unsigned)std::min<uint64_t>((nn + 255) / 256, 65536);
+        hipLaunchKernelGGL(k_scan_add, dim3(g), dim3(256), 0, st, levels[lv].first, nn,
+                           (const uint64_t *)levels[lv + 1].first);
+    }
+    const hipError_t e = hipStreamSynchronize(st);   // the scratch goes
+    for (void *p : tmp) (void)hipFree(p);
+    if (rc == ED_OK && e != hipSuccess) rc = set_error(ED_ERR_HIP, "scan: %s", hipGetErrorString(e));
+    return rc;
+}
+
+
 template <typename AT>
 static int build_impl(ed_basis *b, hipStream_t st)
 {
@@ -1125,46 +1185,7 @@ static int build_impl(ed_basis *b, hipStream_t st)
         return set_error(ED_ERR_HIP, "basis count launch failed");
     }
     {
-        std::vector<std::pair<uint64_t *, uint64_t>> levels;
-        uint64_t n = np;
-        const void *in = counts;
-        bool in32 = true;
-        uint64_t *outp = offsets;
-        std::vector<void *> tmp;
-        int rc = ED_OK;
-        while (true) {
-            const uint64_t tiles = (n + kScanTile - 1) / kScanTile;
-            uint64_t *sums = nullptr;
-            if (hipMalloc((void **)&sums, std::max<uint64_t>(tiles, 1) * 8) != hipSuccess) {
-                rc = set_error(ED_ERR_OOM, "scan scratch");
-                break;
-            }
-            tmp.push_back(sums);
-            if (in32)
-                hipLaunchKernelGGL(k_scan_tile<uint32_t>, dim3((unsigned)tiles), dim3(kScanThreads), 0, st,
-                                   (const uint32_t *)in, outp, n, sums);
-            else
-                hipLaunchKernelGGL(k_scan_tile<uint64_t>, dim3((unsigned)tiles), dim3(kScanThreads), 0, st,
-                                   (const uint64_t *)in, outp, n, sums);
-            levels.push_back({outp, n});
-            if (tiles == 1) break;
-            uint64_t *next_out = nullptr;
-            if (hipMalloc((void **)&next_out, tiles * 8) != hipSuccess) {
-                rc = set_error(ED_ERR_OOM, "scan scratch");
-                break;
-            }
-            tmp.push_back(next_out);
-            in = sums;
-            in32 = false;
-            outp = next_out;
-            n = tiles;
-        }
-        for (int lv = (int)levels.size() - 2; rc == ED_OK && lv >= 0; --lv) {
-            const uint64_t nn = levels[lv].second;
-            const unsigned g = (unsigned)std::min<uint64_t>((nn + 255) / 256, 65536);
-            hipLaunchKernelGGL(k_scan_add, dim3(g), dim3(256), 0, st, levels[lv].first, nn,
-                               (const uint64_t *)levels[lv + 1].first);
-        }
+        int rc = scan_counts(counts, offsets, np, st);
         uint64_t last_off = 0;
         uint32_t last_cnt = 0;
         if (rc == ED_OK) {
@@ -1173,7 +1194,6 @@ static int build_impl(ed_basis *b, hipStream_t st)
                 hipStreamSynchronize(st) != hipSuccess)
                 rc = set_error(ED_ERR_HIP, "basis count readback failed");
         }
-        for (void *p : tmp) (void)hipFree(p);
         if (rc) {
             cleanup();
             return rc;
@@ -1275,15 +1295,35 @@ int launch_basis_build(ed_basis *b, void *stream)
 
 // ---- H.v -----------------------------------------------------------------
 
+// where the scaled input of this basis's H.v goes (the stored terms take the
+// place of both indexes)
+static int input_place(const ed_basis *b)
+{
+    return terms_usable(b) ? TO_TERMS : b->db.index_mode == IDX_HASH ? TO_SLOTS : TO_NONE;
+}
+
+static char *input_dst(const ed_basis *b, int to) { return to == TO_TERMS ? (char *)b->terms.xs : b->db.slots; }
+
+static const double *sqrt_table(const ed_basis *b) { return (const double *)(b->dm.blob + b->dm.off_div); }
+
 static int pack_input(const ed_basis *b, const void *x, hipStream_t st)
 {
-    if (b->db.index_mode != IDX_HASH || b->db.dim == 0) return ED_OK;
+    const int to = input_place(b);
+    if (to == TO_NONE || b->db.dim == 0) return ED_OK;
     const int64_t D = b->db.dim;
-    const unsigned g = (unsigned)std::min<int64_t>((D + 255) / 256, (int64_t)num_cus() * 16);
-    if (b->dm.is_complex)
-        hipLaunchKernelGGL(k_pack_cplx, dim3(g), dim3(256), 0, st, (const double2 *)x, b->db.slot_of, b->db.slots, D);
-    else
-        hipLaunchKernelGGL(k_pack_real, dim3(g), dim3(256), 0, st, (const double *)x, b->db.slot_of, b->db.slots, D);
+    const dim3 g((unsigned)std::min<int64_t>((D + 255) / 256, (int64_t)num_cus() * 16));
+    const double *sq = sqrt_table(b);
+    char *dst = input_dst(b, to);
+#define ED_PACK(C, TO) \
+    hipLaunchKernelGGL((k_pack<C, TO>), g, dim3(256), 0, st, (const Scalar<C>::T *)x, b->db.states, sq, b->db.slot_of, dst, D)
+    if (b->dm.is_complex) {
+        if (to == TO_TERMS) ED_PACK(true, TO_TERMS);
+        else ED_PACK(true, TO_SLOTS);
+    } else {
+        if (to == TO_TERMS) ED_PACK(false, TO_TERMS);
+        else ED_PACK(false, TO_SLOTS);
+    }
+#undef ED_PACK
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "pack launch failed: %s", hipGetErrorString(e));
     return ED_OK;
@@ -1404,8 +1444,10 @@ int launch_apply(const ed_basis *b, const double *J, const double *Jz, const voi
     rc = upload_couplings(b, J, Jz, st, &jsq);
     if (rc) return rc;
     if (b->db.dim == 0) return ED_OK;
+    if (terms_usable(b) && terms_small(b)) return terms_apply(b, x, y, jsq, stream);
     rc = pack_input(b, x, st);
     if (rc) return rc;
+    if (terms_usable(b)) return terms_apply(b, x, y, jsq, stream);
     return apply_dispatch<0>(b, x, y, nullptr, nullptr, nullptr, nullptr, jsq, st);
 }
 
@@ -1436,9 +1478,11 @@ int launch_apply_timed(const ed_basis *b, const double *J, const double *Jz, con
         }
     for (int r = 0; r < reps && rc == ED_OK; ++r) {
         if (hipEventRecord(ev[3 * r], st) != hipSuccess) rc = set_error(ED_ERR_HIP, "event record failed");
-        if (!rc) rc = pack_input(b, x, st);
+        if (!rc && !(terms_usable(b) && terms_small(b))) rc = pack_input(b, x, st);
         if (!rc && hipEventRecord(ev[3 * r + 1], st) != hipSuccess) rc = set_error(ED_ERR_HIP, "event record failed");
-        if (!rc) rc = apply_dispatch<0>(b, x, y, nullptr, nullptr, nullptr, nullptr, jsq, st);
+        if (!rc)
+            rc = terms_usable(b) ? terms_apply(b, x, y, jsq, stream)
+                                 : apply_dispatch<0>(b, x, y, nullptr, nullptr, nullptr, nullptr, jsq, st);
         if (!rc && hipEventRecord(ev[3 * r + 2], st) != hipSuccess) rc = set_error(ED_ERR_HIP, "event record failed");
     }
     if (!rc && hipStreamSynchronize(st) != hipSuccess)
@@ -1521,8 +1565,7 @@ static int backward_impl(const ed_basis *b, const void *x, const void *gy, doubl
     // written, so nothing has to start at zero
     hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, b->dm, b->db, (const T *)x, (const T *)gy, partials,
                        (const char *)b->adj_slots, (double *)gx, jsq);
-    hipLaunchKernelGGL(k_sum_partials_cols, dim3((nb + 256) / 256), dim3(256), 0, st, (const double *)partials, grid,
-                       nb + 1, out);
+    hipLaunchKernelGGL(k_sum_partials_cols, dim3(nb + 1), dim3(256), 0, st, (const double *)partials, grid, nb + 1, out);
     double h[kMaxBondWords * 64 + 1];
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(h, out, (size_t)(nb + 1) * 8, hipMemcpyDeviceToHost, st);
@@ -1589,6 +1632,13 @@ int launch_backward_J(const ed_basis *b, const double *J, const void *x, const v
     }
     const bool c = b->dm.is_complex;
     const int ix = b->db.index_mode, w = b->dm.act_bytes;
+    if (terms_usable(b)) {
+        if (!gx) {
+            rc = pack_input(b, x, st);
+            if (rc) return rc;
+        }
+        return terms_backward(b, x, gy, gx, gJ_host, scratch_dev, kScratchDoubles, jsq, stream);
+    }
     // four sublattices with one to three chunks: search loops fixed at compile time
     const int nsc = (ix == IDX_HASH && b->dm.ns == 4 && b->dm.n_chunks <= 3) ? 32 + b->dm.n_chunks : 0;
     if (gx) {
@@ -1599,10 +1649,10 @@ int launch_backward_J(const ed_basis *b, const double *J, const void *x, const v
         const dim3 pgrid((unsigned)std::min<int64_t>((D + 255) / 256, 1 << 20));
         if (c)
             hipLaunchKernelGGL(k_pack_adj<true>, pgrid, dim3(256), 0, st, (const double2 *)x, (const double2 *)gy,
-                               b->db.slot_of, b->adj_slots, D);
+                               b->db.states, sqrt_table(b), b->db.slot_of, b->adj_slots, D);
         else
             hipLaunchKernelGGL(k_pack_adj<false>, pgrid, dim3(256), 0, st, (const double *)x, (const double *)gy,
-                               b->db.slot_of, b->adj_slots, D);
+                               b->db.states, sqrt_table(b), b->db.slot_of, b->adj_slots, D);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return set_error(ED_ERR_HIP, "adjoint pack failed: %s", hipGetErrorString(e));
 #define ED_FCASE(C, A, K) \
@@ -1657,6 +1707,17 @@ void free_lanczos_workspace(ed_basis *b)
     W.cap_partials = 0;
 }
 
+template <bool CPLX, int TO>
+static void launch_lz_next(const ed_basis *b, int vgrid, const double *w, double *vnew, const double *partials,
+                           const LzState *lz, LzState *lz_next, const double *ahist, double *bhist, int n_steps,
+                           hipStream_t st)
+{
+    using T = typename Scalar<CPLX>::T;
+    hipLaunchKernelGGL((k_lz_next<CPLX, TO>), dim3(vgrid), dim3(kVecThreads), 0, st, (const T *)w, (T *)vnew, b->db.dim,
+                       partials, vgrid, lz, lz_next, ahist, bhist, n_steps, 1e-12, b->db.states, sqrt_table(b),
+                       b->db.slot_of, input_dst(b, TO));
+}
+
 int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const void *v0, int n_steps, double *alpha,
                 double *beta, int *n_done, void *psi0, void *stream)
 {
@@ -1679,7 +1740,8 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         b->grid_blocks = grid;   // fixed launch geometry -> deterministic reductions
     }
     const int vgrid = (int)std::min<int64_t>((nd + kVecThreads - 1) / kVecThreads, (int64_t)num_cus() * 8);
-    const int np_apply = b->grid_blocks;
+    const int to = input_place(b);
+    const int np_apply = to == TO_TERMS ? terms_grid(b) : b->grid_blocks;
     const size_t vb = (size_t)nd * 8;
     auto &W = b->lzw;
     const size_t npart = (size_t)std::max(np_apply, vgrid);
@@ -1689,8 +1751,8 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         free_lanczos_workspace(b);
         bool ok = true;
         for (int k = 0; k < 3; ++k) ok = ok && hipMalloc((void **)&W.vec[k], vb) == hipSuccess;
-        ok = ok && hipMalloc((void **)&W.partials, npart * 8) == hipSuccess;
-        ok = ok && hipMalloc(&W.state, sizeof(LzState)) == hipSuccess;
+        ok = ok && hipMalloc((void **)&W.partials, 2 * npart * 8) == hipSuccess;
+        ok = ok && hipMalloc(&W.state, 2 * sizeof(LzState)) == hipSuccess;
         if (!ok) {
             (void)hipGetLastError();
             free_lanczos_workspace(b);
@@ -1714,13 +1776,14 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     }
     double *A = W.vec[0], *B = W.vec[1], *C = W.vec[2], *partials = W.partials, *ahist = W.ahist, *bhist = W.bhist,
            *svec = W.svec;
-    LzState *lz = (LzState *)W.state;
+    LzState *lz = (LzState *)W.state;             // two states, see LzState
+    double *norms = partials + W.cap_partials;    // |w|^2 partials, beside the <v, w> ones
     std::vector<double> svec_host(n_steps, 0.0);
     const int passes = psi0 ? 2 : 1;
     for (int pass = 0; pass < passes; ++pass) {
         double *psi = pass == 1 ? (double *)psi0 : nullptr;
-        LzState init{};
-        HIP_TRY(hipMemcpyAsync(lz, &init, sizeof init, hipMemcpyHostToDevice, st));
+        const LzState init[2] = {};
+        HIP_TRY(hipMemcpyAsync(lz, init, sizeof init, hipMemcpyHostToDevice, st));
         if (psi) {
             HIP_TRY(hipMemsetAsync(psi, 0, vb, st));
             HIP_TRY(hipMemcpyAsync(svec, svec_host.data(), (size_t)n_steps * 8, hipMemcpyHostToDevice, st));
@@ -1730,24 +1793,32 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         hipLaunchKernelGGL(k_norm2_partial, dim3(vgrid), dim3(kVecThreads), 0, st, (const double *)v0, nd, partials);
         hipLaunchKernelGGL(k_scale_by_norm, dim3(vgrid), dim3(kVecThreads), 0, st, (const double *)v0, B, nd,
                            (const double *)partials, vgrid);
-        // one step: pack v into the slots, w = H v - beta v_prev with <v, w>
-        // partials, alpha, w -= alpha v (and psi += s_j v), beta, v_prev <-
-        // w / beta.  Every quantity that changes between steps lives on the
-        // device (the step index in lz), so the step can be captured once per
-        // buffer assignment and replayed.
-        auto step_kernels = [&](double *vprev_, double *v_, hipStream_t s_) -> int {
-            int r = pack_input(b, v_, s_);
+        rc = pack_input(b, B, st);
+        if (rc) return rc;
+        // one step: w = H v - beta v_prev with <v, w> partials; w -= alpha v
+        // (and psi += s_j v); v_prev <- w / beta, scaled for the next H.v.
+        // Every quantity that changes between steps lives on the device (the
+        // step index in lz), so the step can be captured once per buffer
+        // assignment and replayed.
+        auto step_kernels = [&](int p_, hipStream_t s_) -> int {
+            double *vprev_ = p_ == 0 ? A : B, *v_ = p_ == 0 ? B : A;
+            const LzState *cur = lz + p_;
+            int r = to == TO_TERMS ? terms_lanczos_apply(b, v_, C, vprev_, partials, cur, jsq, s_)
+                                   : apply_dispatch<2>(b, v_, C, vprev_, partials, nullptr, cur, jsq, s_);
             if (r) return r;
-            r = apply_dispatch<2>(b, v_, C, vprev_, partials, nullptr, lz, jsq, s_);
-            if (r) return r;
-            hipLaunchKernelGGL(k_lz_alpha, dim3(1), dim3(64), 0, s_, lz, (const double *)partials, np_apply, ahist);
-            hipLaunchKernelGGL(k_lz_update, dim3(vgrid), dim3(kVecThreads), 0, s_, C, (const double *)v_, nd, partials,
-                               (const LzState *)lz, psi, (const double *)svec);
-            hipLaunchKernelGGL(k_lz_beta, dim3(1), dim3(64), 0, s_, lz, (const double *)partials, vgrid, bhist,
-                               n_steps, 1e-12);
-            hipLaunchKernelGGL(k_lz_normalize, dim3(vgrid), dim3(kVecThreads), 0, s_, (const double *)C, vprev_, nd,
-                               (const LzState *)lz);
-            hipLaunchKernelGGL(k_lz_shift_beta, dim3(1), dim3(64), 0, s_, lz);
+            hipLaunchKernelGGL(k_lz_update, dim3(vgrid), dim3(kVecThreads), 0, s_, C, (const double *)v_, nd,
+                               (const double *)partials, np_apply, norms, cur, ahist, psi, (const double *)svec);
+#define ED_NEXT(CP, TO) launch_lz_next<CP, TO>(b, vgrid, C, vprev_, norms, cur, lz + (p_ ^ 1), ahist, bhist, n_steps, s_)
+            if (cplx) {
+                if (to == TO_TERMS) ED_NEXT(true, TO_TERMS);
+                else if (to == TO_SLOTS) ED_NEXT(true, TO_SLOTS);
+                else ED_NEXT(true, TO_NONE);
+            } else {
+                if (to == TO_TERMS) ED_NEXT(false, TO_TERMS);
+                else if (to == TO_SLOTS) ED_NEXT(false, TO_SLOTS);
+                else ED_NEXT(false, TO_NONE);
+            }
+#undef ED_NEXT
             const hipError_t e = hipGetLastError();
             return e == hipSuccess ? ED_OK : set_error(ED_ERR_HIP, "Lanczos step launch: %s", hipGetErrorString(e));
         };
@@ -1774,7 +1845,7 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
                     release();
                     return set_error(ED_ERR_HIP, "begin capture");
                 }
-                rc = step_kernels(p == 0 ? A : B, p == 0 ? B : A, cap);
+                rc = step_kernels(p, cap);
                 const hipError_t e = hipStreamEndCapture(cap, &graph);
                 if (rc || e != hipSuccess) {
                     if (graph) (void)hipGraphDestroy(graph);
@@ -1798,12 +1869,12 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
                     return set_error(ED_ERR_HIP, "graph launch: %s", hipGetErrorString(e));
                 }
             } else {
-                rc = step_kernels(p == 0 ? A : B, p == 0 ? B : A, st);
+                rc = step_kernels(p, st);
                 if (rc) return rc;
             }
             if ((step & 15) == 15) {
-                LzState hs;
-                if (hipMemcpyAsync(&hs, lz, sizeof hs, hipMemcpyDeviceToHost, st) != hipSuccess ||
+                LzState hs;   // the state that this step wrote
+                if (hipMemcpyAsync(&hs, lz + (p ^ 1), sizeof hs, hipMemcpyDeviceToHost, st) != hipSuccess ||
                     hipStreamSynchronize(st) != hipSuccess) {
                     release();
                     return set_error(ED_ERR_HIP, "Lanczos state readback");
@@ -1819,11 +1890,12 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
             }
             release();
         }
-        LzState hs;
-        HIP_TRY(hipMemcpyAsync(&hs, lz, sizeof hs, hipMemcpyDeviceToHost, st));
+        LzState both[2];
+        HIP_TRY(hipMemcpyAsync(both, lz, sizeof both, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipMemcpyAsync(alpha, ahist, (size_t)n_steps * 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipMemcpyAsync(beta, bhist, (size_t)n_steps * 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
+        const LzState hs = both[0].j > both[1].j ? both[0] : both[1];
         *n_done = hs.j;
         if (pass == 0 && psi0) {
             std::vector<double> ev(hs.j), z(hs.j);

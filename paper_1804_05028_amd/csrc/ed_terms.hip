@@ -1,0 +1,912 @@
+// Stored terms: the targets of a sector's off-diagonal terms, searched once.
+//
+// The representative search and the index lookup of a term depend on the
+// basis alone, not on the couplings or the vector, and a sector's H.v is
+// repeated many times (each Lanczos step, each call of a fit).  Where the
+// table fits, ed_build_basis therefore searches every term once and keeps one
+// 32-bit word per term,
+//   word = class << ibits | row index of the target,
+// where the class names the bond's orbit and the character of the element
+// found (times the Fermi sign, for fermions); the coefficients of the classes
+// (J/2 chi) are rewritten when the couplings change.  Terms without a target
+// in the sector keep their class (their bond counts in the diagonal) and
+// point at row dim, whose amplitude is zero; padding has a class of its own
+// whose coefficients are zero.
+//
+// Rows are taken in slices of 64, one per lane.  A slice holds as many groups
+// of four terms as its longest row needs, a group being 64 lanes x 4 words, so
+// that a wave reads its words as one 1 KB load.  A row's terms are in bond
+// order, as in the searching kernels, and summed by the same operations: both
+// give the same bits.
+#include "ed_device.hpp"
+
+namespace ed {
+
+constexpr int kTermsThreads = 256;
+constexpr int kTermsWaves = kTermsThreads / kWave;
+constexpr int kMaxClasses = 1024;
+
+struct TermsDev {
+    const uint4 *words;
+    const uint64_t *off;
+    const uint32_t *cnt;
+    uint32_t stride;
+    int ibits, n_cls;
+    const double *cls;        // {kr, jz} or {kr, ki, jz, -} of every class
+    const double *cls_chi;    // chi or {re, im} of every class
+};
+
+static TermsDev terms_dev(const ed_basis *b)
+{
+    TermsDev td;
+    td.words = (const uint4 *)b->terms.words;
+    td.off = b->terms.off;
+    td.cnt = b->terms.cnt;
+    td.stride = b->terms.stride;
+    td.ibits = b->terms.ibits;
+    td.n_cls = b->terms.n_cls;
+    td.cls = b->terms.cls;
+    td.cls_chi = b->terms.cls_chi;
+    return td;
+}
+
+__device__ __forceinline__ uint4 load_words(const uint4 *p)
+{
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    // read once per pass: kept out of the way of the amplitudes in L2
+    const u32x4 v = __builtin_nontemporal_load((const u32x4 *)p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// ---------------------------------------------------------------------------
+// building
+// ---------------------------------------------------------------------------
+
+// groups of four terms of every slice
+__global__ void __launch_bounds__(256) k_terms_count(DevModel dm, const uint64_t *states, int64_t D, uint32_t *cnt)
+{
+    __shared__ uint64_t mask[kMaxBondWords * 64];
+    const BondLds *bonds = (const BondLds *)(dm.blob + dm.off_bonds);
+    for (int k = threadIdx.x; k < dm.nb; k += blockDim.x) mask[k] = bonds[k].mask;
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t n_slices = (D + kWave - 1) / kWave;
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t n_waves = (int64_t)gridDim.x * blockDim.x / kWave;
+    for (int64_t sl = wave; sl < n_slices; sl += n_waves) {
+        const int64_t i = sl * kWave + lane;
+        int n = 0;
+        if (i < D) {
+            const uint64_t s = states[i] & kStateMask;
+            for (int k = 0; k < dm.nb; ++k) {
+                const uint64_t t = s & mask[k];
+                n += (t != 0) & (t != mask[k]);
+            }
+        }
+        for (int o = 32; o > 0; o >>= 1) n = max(n, __shfl_xor(n, o, 64));
+        if (lane == 0) cnt[sl] = (uint32_t)(n + 3) / 4;
+    }
+}
+
+// Searches every term.  A wave takes a slice, or, where there are few slices,
+// every parts-th term of one.  As in k_apply, the slot of the next term is
+// requested before the current one is resolved.
+template <typename AT, int NSC, bool FERMI>
+__global__ void __launch_bounds__(1024) k_terms_fill(DevModel dm, DevBasis db, const uint64_t *off, uint32_t stride,
+                                                     uint32_t *cnt, uint32_t *words, const uint16_t *chi_class,
+                                                     const uint16_t *bond_orbit, int n_orb, int ibits, uint32_t pad,
+                                                     int parts)
+{
+    extern __shared__ __align__(16) char lds[];
+    const Ctx<AT> c = stage<AT>(dm, lds);
+    const int nb = dm.nb;
+    const int64_t D = db.dim;
+    const uint64_t smask = (1ull << db.slot_log2) - 1ull;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int sshift = dm.is_complex ? 5 : 4;
+    const int64_t n_units = (D + kWave - 1) / kWave * parts;
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    const int64_t n_waves = (int64_t)gridDim.x * blockDim.x / kWave;
+    for (int64_t unit = wave; unit < n_units; unit += n_waves) {
+        const int64_t slice = unit / parts;
+        const int part = (int)(unit % parts);
+        const int64_t i = slice * kWave + lane;
+        const bool row_ok = i < D;
+        const uint64_t s = row_ok ? db.states[i] & kStateMask : 0ull;
+        BondMask am;
+        am.w0 = bond_word(c, s, 0, nb);
+        am.w1 = nb > 64 ? bond_word(c, s, 1, nb) : 0ull;
+        am.w2 = nb > 128 ? bond_word(c, s, 2, nb) : 0ull;
+        am.w3 = nb > 192 ? bond_word(c, s, 3, nb) : 0ull;
+        const int n_terms = row_ok ? __popcll(am.w0) + __popcll(am.w1) + __popcll(am.w2) + __popcll(am.w3) : 0;
+        int most = n_terms;
+        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+        const int groups = (most + 3) / 4;
+        if (off == nullptr && part == 0 && lane == 0) cnt[slice] = (uint32_t)groups;
+        const uint64_t base = off ? off[slice] : (uint64_t)slice * stride;
+        uint64_t r_nx = 0, sl_nx = 0;
+        uint32_t cl_nx = 0;
+        ulonglong2 q_nx = make_ulonglong2(0ull, 0ull);
+        int done = 0;   // bonds taken off the mask
+        auto request = [&](int t) {
+            int bi = 0;
+            for (; done <= t; ++done) bi = pop_bond(am);
+            const uint64_t sp = s ^ c.bonds[bi].mask;
+            uint32_t g;
+            r_nx = rep_search<AT, NSC>(c, sp, g);
+            uint32_t neg = 0;
+            if constexpr (FERMI)
+                neg = ((uint32_t)__popcll(s & c.between[bi]) & 1u) ^ fermi_parity<AT, NSC>(c, c.g_u[g], sp);
+            cl_nx = (uint32_t)chi_class[neg ? dm.ng + g : g] * n_orb + bond_orbit[bi];
+            sl_nx = slot_of_state(r_nx, db.slot_log2);
+            q_nx = *(const ulonglong2 *)(db.slots + (sl_nx << sshift));
+        };
+        if (part < n_terms) request(part);
+        for (int t = part; t < 4 * groups; t += parts) {
+            const uint64_t r = r_nx, home = sl_nx;
+            const uint32_t cl = cl_nx;
+            uint64_t sl = sl_nx;
+            ulonglong2 q = q_nx;
+            if (t + parts < n_terms) request(t + parts);
+            uint32_t word = pad;
+            if (t < n_terms) {
+                while (q.x != kEmpty && (q.x & kStateMask) != r) {
+                    sl = next_slot(sl, home, smask, sshift == 5 ? 2 : 3);
+                    q = *(const ulonglong2 *)(db.slots + (sl << sshift));
+                }
+                word = cl << ibits | (q.x == kEmpty ? (uint32_t)D : (uint32_t)q.y);
+            }
+            words[((base + (uint64_t)(t >> 2)) * kWave + lane) * 4 + (t & 3)] = word;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// H.v
+// ---------------------------------------------------------------------------
+
+// coefficients of the classes, 1/sqrt of the divisors and, for fermions, the
+// bonds: what an H.v of stored terms keeps in LDS
+template <bool CPLX>
+struct TermsLds {
+    const double *cls, *rsqrt;
+    const BondLds *bonds;
+};
+
+static size_t terms_lds_bytes(const ed_basis *b)
+{
+    return (size_t)b->terms.n_cls * (b->dm.is_complex ? 32 : 16) + (size_t)b->dm.n_div * 8 +
+           (b->fermion ? (size_t)b->dm.nb * sizeof(BondLds) : 0);
+}
+
+template <bool CPLX, bool FERMI>
+__device__ __forceinline__ TermsLds<CPLX> stage_terms(const DevModel &dm, const TermsDev &td, double *lds)
+{
+    const int n = td.n_cls * (CPLX ? 4 : 2);
+    for (int k = threadIdx.x; k < n; k += blockDim.x) lds[k] = td.cls[k];
+    const double *rs = (const double *)(dm.blob + dm.off_div) + dm.n_div;
+    for (int k = threadIdx.x; k < dm.n_div; k += blockDim.x) lds[n + k] = rs[k];
+    TermsLds<CPLX> t;
+    t.cls = lds;
+    t.rsqrt = lds + n;
+    t.bonds = (const BondLds *)(lds + n + dm.n_div);
+    if (FERMI) {
+        const double *src = (const double *)(dm.blob + dm.off_bonds);
+        for (int k = threadIdx.x; k < dm.nb * (int)(sizeof(BondLds) / 8); k += blockDim.x) lds[n + dm.n_div + k] = src[k];
+    }
+    __syncthreads();
+    return t;
+}
+
+// the four terms of a group; anti collects the Ising parts of their bonds
+template <bool CPLX, typename XS>
+__device__ __forceinline__ void add_group(const TermsLds<CPLX> &tl, uint4 w, int ibits, XS xs, double &ar, double &ai,
+                                          double &anti)
+{
+    const uint32_t im = (1u << ibits) - 1u;
+    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+    typename Scalar<CPLX>::T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = xs(ww[k] & im);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t cl = ww[k] >> ibits;
+        if constexpr (CPLX) {
+            const double2 c = *(const double2 *)(tl.cls + 4 * cl);
+            add_term<true>(ar, ai, c.x, c.y, v[k].x, v[k].y);
+            anti += tl.cls[4 * cl + 2];
+        } else {
+            const double2 c = *(const double2 *)(tl.cls + 2 * cl);
+            add_term<false>(ar, ai, c.x, 0.0, v[k], 0.0);
+            anti += c.y;
+        }
+    }
+}
+
+template <bool CPLX, int MODE, bool FERMI, typename XS>
+__device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const TermsDev &td, int nb, int64_t slice, int lane,
+                                            const uint64_t *states, int64_t D, XS xs,
+                                            const typename Scalar<CPLX>::T *x, typename Scalar<CPLX>::T *y,
+                                            const typename Scalar<CPLX>::T *vprev, double beta_prev, double jsq)
+{
+    using T = typename Scalar<CPLX>::T;
+    const int64_t i = slice * kWave + lane;
+    const bool ok = i < D;
+    const int groups = (int)td.cnt[slice];
+    const uint4 *p = td.words + ((td.off ? td.off[slice] : (uint64_t)slice * td.stride) * kWave + lane);
+    const uint64_t e = ok ? states[i] : 0ull;
+    T xi{}, vp{};
+    if (ok) {
+        xi = x[i];
+        if (MODE == 2) vp = vprev[i];
+    }
+    double ar = 0.0, ai = 0.0, anti = 0.0;
+    uint4 w = make_uint4(0, 0, 0, 0), w2 = w;
+    if (groups > 0) w = load_words(p);
+    if (groups > 1) w2 = load_words(p + kWave);
+    for (int g = 0; g < groups; ++g) {
+        uint4 w3 = w2;
+        if (g + 2 < groups) w3 = load_words(p + (size_t)(g + 2) * kWave);
+        add_group<CPLX>(tl, w, td.ibits, xs, ar, ai, anti);
+        w = w2;
+        w2 = w3;
+    }
+    double d;
+    if (FERMI) {
+        const uint64_t s = e & kStateMask;
+        d = 0.0;
+        for (int k = 0; k < nb; ++k) {
+            const uint64_t bm = tl.bonds[k].mask;
+            if ((s & bm) == bm) d += tl.bonds[k].jzhalf;
+        }
+    } else {
+        d = jsq - anti;
+    }
+    double dot = 0.0;
+    if (ok) {
+        const double rs = tl.rsqrt[e >> kNormShift];
+        T out;
+        if constexpr (CPLX) {
+            out.x = fma(rs, ar, d * xi.x);
+            out.y = fma(rs, ai, d * xi.y);
+            if (MODE == 2) {
+                out.x = fma(-beta_prev, vp.x, out.x);
+                out.y = fma(-beta_prev, vp.y, out.y);
+                dot = fma(xi.x, out.x, xi.y * out.y);
+            }
+        } else {
+            out = fma(rs, ar, d * xi);
+            if (MODE == 2) {
+                out = fma(-beta_prev, vp, out);
+                dot = xi * out;
+            }
+        }
+        y[i] = out;
+    }
+    return dot;
+}
+
+// H.v from the stored terms: a coalesced read of the words and a gather of
+// scaled amplitudes.
+// The rows are in ascending order and consecutive rows differ in their last
+// bits, so that the targets of one bond lie close together too: on the 32-site
+// square sector the 64 rows of a slice touch 0.57 lines of 128 bytes per term
+// and load instruction, 0.35 over all their terms, and 8192 consecutive rows
+// 0.21 (36-site triangular: 0.74, 0.51, 0.20), where hashed slots cost 1.04.
+// chunks = 8 gives each XCD (blocks go round the XCDs in turn) one contiguous
+// range of rows, which its L2 then shares.
+template <bool CPLX, int MODE, bool FERMI>
+__global__ void __launch_bounds__(kTermsThreads)
+    k_terms_apply(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int64_t D,
+                  const typename Scalar<CPLX>::T *__restrict__ xs, const typename Scalar<CPLX>::T *__restrict__ x,
+                  typename Scalar<CPLX>::T *__restrict__ y, const typename Scalar<CPLX>::T *__restrict__ vprev,
+                  double *partials, const LzState *lz, double jsq, int chunks)
+{
+    using T = typename Scalar<CPLX>::T;
+    extern __shared__ __align__(16) double lds_d[];
+    if (MODE == 2 && lz->done) return;
+    const double beta_prev = MODE == 2 ? lz->beta_prev : 0.0;
+    const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d);
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t n_slices = (D + kWave - 1) / kWave;
+    const int64_t per = (n_slices + chunks - 1) / chunks;
+    const int64_t first = per * (blockIdx.x % chunks);
+    const int64_t last = min(first + per, n_slices);
+    const int64_t step = (int64_t)(gridDim.x / chunks) * kTermsWaves;
+    auto gather = [&](uint32_t j) { return *(const T *)((const char *)xs + (uint32_t)(j * (uint32_t)sizeof(T))); };
+    double dot = 0.0;
+    for (int64_t sl = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave; sl < last; sl += step)
+        dot += terms_row<CPLX, MODE, FERMI>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, beta_prev, jsq);
+    if (MODE == 2) {
+        __shared__ double sh[kTermsWaves];
+        const double t = block_sum(dot, sh);
+        if (threadIdx.x == 0) partials[blockIdx.x] = t;
+    }
+}
+
+// The same for sectors whose input fits LDS: every block scales all of x into
+// LDS itself, so that one launch does the whole H.v and the gathers stay on
+// the compute unit.  At 822 rows the call is one launch.
+template <bool CPLX, bool FERMI>
+__global__ void __launch_bounds__(kTermsThreads)
+    k_terms_apply_small(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int64_t D,
+                        const typename Scalar<CPLX>::T *__restrict__ x, typename Scalar<CPLX>::T *__restrict__ y, double jsq)
+{
+    using T = typename Scalar<CPLX>::T;
+    extern __shared__ __align__(16) double lds_d[];
+    T *xs = (T *)lds_d;
+    const double *sq = (const double *)(dm.blob + dm.off_div);
+    for (int k = threadIdx.x; k < (int)D; k += blockDim.x) {
+        const double q = sq[states[k] >> kNormShift];
+        T v = x[k];
+        if constexpr (CPLX) {
+            v.x *= q;
+            v.y *= q;
+        } else {
+            v *= q;
+        }
+        xs[k] = v;
+    }
+    if (threadIdx.x == 0) xs[D] = T{};
+    // the class table starts on a 16-byte boundary
+    const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d + (((D + 1) * (CPLX ? 2 : 1) + 1) & ~(int64_t)1));
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t n_slices = (D + kWave - 1) / kWave;
+    auto gather = [&](uint32_t j) { return xs[j]; };
+    for (int64_t sl = (int64_t)blockIdx.x * kTermsWaves + wave; sl < n_slices; sl += (int64_t)gridDim.x * kTermsWaves)
+        terms_row<CPLX, 0, FERMI>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, nullptr, 0.0, jsq);
+}
+
+// blocks of a pass over all slices: a multiple of 8 (see chunks) where there
+// are at least 8 blocks' worth, at most 8 per compute unit
+int terms_grid(const ed_basis *b)
+{
+    const int64_t blocks = ((b->db.dim + kWave - 1) / kWave + kTermsWaves - 1) / kTermsWaves;
+    if (blocks < 8) return (int)std::max<int64_t>(blocks, 1);
+    return (int)std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * 8 & ~7));
+}
+
+static int terms_chunks(const ed_basis *b) { return terms_grid(b) % 8 == 0 ? 8 : 1; }
+
+template <bool CPLX, int MODE, bool FERMI>
+static int launch_terms(const ed_basis *b, const void *x, void *y, const void *vprev, double *partials, const void *lz,
+                        double jsq, hipStream_t st)
+{
+    using T = typename Scalar<CPLX>::T;
+    const size_t lds = terms_lds_bytes(b);
+    if (MODE == 0 && terms_small(b)) {
+        const size_t xb = (((size_t)b->db.dim + 1) * sizeof(T) + 15) & ~(size_t)15;
+        const int64_t slices = (b->db.dim + kWave - 1) / kWave;
+        hipLaunchKernelGGL((k_terms_apply_small<CPLX, FERMI>), dim3((unsigned)((slices + kTermsWaves - 1) / kTermsWaves)),
+                           dim3(kTermsThreads), xb + lds, st, b->dm, terms_dev(b), b->db.states, b->db.dim, (const T *)x,
+                           (T *)y, jsq);
+    } else {
+        hipLaunchKernelGGL((k_terms_apply<CPLX, MODE, FERMI>), dim3(terms_grid(b)), dim3(kTermsThreads), lds, st, b->dm,
+                           terms_dev(b), b->db.states, b->db.dim, (const T *)b->terms.xs, (const T *)x, (T *)y,
+                           (const T *)vprev, partials, (const LzState *)lz, jsq, terms_chunks(b));
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "H.v launch failed: %s", hipGetErrorString(e));
+    return ED_OK;
+}
+
+template <int MODE>
+static int terms_dispatch(const ed_basis *b, const void *x, void *y, const void *vprev, double *partials, const void *lz,
+                          double jsq, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    if (b->fermion)
+        return b->dm.is_complex ? launch_terms<true, MODE, true>(b, x, y, vprev, partials, lz, jsq, st)
+                                : launch_terms<false, MODE, true>(b, x, y, vprev, partials, lz, jsq, st);
+    return b->dm.is_complex ? launch_terms<true, MODE, false>(b, x, y, vprev, partials, lz, jsq, st)
+                            : launch_terms<false, MODE, false>(b, x, y, vprev, partials, lz, jsq, st);
+}
+
+// y = H x; the scaled x is in terms.xs unless the sector is small
+int terms_apply(const ed_basis *b, const void *x, void *y, double jsq, void *stream)
+{
+    return terms_dispatch<0>(b, x, y, nullptr, nullptr, nullptr, jsq, stream);
+}
+
+int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *vprev, double *partials, const void *lz,
+                        double jsq, void *stream)
+{
+    return terms_dispatch<2>(b, v, w, vprev, partials, lz, jsq, stream);
+}
+
+// ---------------------------------------------------------------------------
+// adjoint
+// ---------------------------------------------------------------------------
+
+// {sqrt(n) x, sqrt(n) gy} of every row, zero behind the last
+template <bool CPLX>
+__global__ void k_terms_pair(const typename Scalar<CPLX>::T *x, const typename Scalar<CPLX>::T *gy, const uint64_t *states,
+                             const double *sqrts, double *pair, int64_t D)
+{
+    constexpr int W = CPLX ? 2 : 1;
+    const double *xd = (const double *)x, *gd = (const double *)gy;
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j <= D; j += (int64_t)gridDim.x * blockDim.x) {
+        const double sq = j < D ? sqrts[states[j] >> kNormShift] : 0.0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            pair[(2 * j) * W + k] = j < D ? xd[j * W + k] * sq : 0.0;
+            pair[(2 * j + 1) * W + k] = j < D ? gd[j * W + k] * sq : 0.0;
+        }
+    }
+}
+
+// Per-bond adjoint sums as k_backward_J forms them (same order, same bits),
+// the targets read from the stored terms; FUSED: gx = H gy in the same pass,
+// x_j and gy_j from one read of the pair array.  All lanes visit a bond
+// together; a lane's word is the one at its count of antiparallel bonds so
+// far.  Four bonds are read ahead, so that eight dependent reads of a lane are
+// two latencies.
+template <bool CPLX, bool FUSED>
+__global__ void __launch_bounds__(kTermsThreads)
+    k_terms_backward(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int64_t D,
+                     const double *__restrict__ src, const typename Scalar<CPLX>::T *__restrict__ x,
+                     const typename Scalar<CPLX>::T *__restrict__ gy, double *partials, double *__restrict__ gx, double jsq,
+                     int chunks)
+{
+    constexpr int W = CPLX ? 2 : 1;
+    constexpr int kAhead = 4;
+    extern __shared__ __align__(16) double lds_d[];
+    // characters of the classes, 1/sqrt of the divisors, bonds; the block's
+    // sums take their place at the end
+    double *chi = lds_d, *rsqrt = lds_d + td.n_cls * W;
+    BondLds *bonds = (BondLds *)(rsqrt + dm.n_div);
+    const int nb = dm.nb;
+    for (int k = threadIdx.x; k < td.n_cls * W; k += blockDim.x) chi[k] = td.cls_chi[k];
+    {
+        const double *rs = (const double *)(dm.blob + dm.off_div) + dm.n_div;
+        for (int k = threadIdx.x; k < dm.n_div; k += blockDim.x) rsqrt[k] = rs[k];
+        const double *bs = (const double *)(dm.blob + dm.off_bonds);
+        for (int k = threadIdx.x; k < nb * (int)(sizeof(BondLds) / 8); k += blockDim.x) ((double *)bonds)[k] = bs[k];
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const uint32_t im = (1u << td.ibits) - 1u;
+    const int64_t n_slices = (D + kWave - 1) / kWave;
+    const int64_t per = (n_slices + chunks - 1) / chunks;
+    const int64_t first = per * (blockIdx.x % chunks);
+    const int64_t last = min(first + per, n_slices);
+    const int64_t step = (int64_t)(gridDim.x / chunks) * kTermsWaves;
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0, tot = 0.0;
+    for (int64_t sl = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave; sl < last; sl += step) {
+        const int64_t i = sl * kWave + lane;
+        const bool valid = i < D;
+        const uint32_t *p = (const uint32_t *)(td.words + (td.off ? td.off[sl] : (uint64_t)sl * td.stride) * kWave) + lane * 4;
+        uint64_t s = 0;
+        double rs_i = 0.0, gx_r = 0.0, g_r = 0.0, g_i = 0.0;
+        if (valid) {
+            const uint64_t e = states[i];
+            s = e & kStateMask;
+            rs_i = rsqrt[e >> kNormShift];
+            if (CPLX) {
+                const double2 gv = *(const double2 *)&gy[i];
+                const double2 xv = *(const double2 *)&x[i];
+                g_r = gv.x;
+                g_i = gv.y;
+                gx_r = fma(gv.x, xv.x, gv.y * xv.y);
+            } else {
+                g_r = *(const double *)&gy[i];
+                gx_r = g_r * *(const double *)&x[i];
+            }
+        }
+        tot += wave_sum(gx_r);
+        double anti_sum = 0.0, ar = 0.0, ai = 0.0;
+        int pos = 0;
+        for (int b0 = 0; b0 < nb; b0 += kAhead) {
+            bool anti[kAhead];
+            uint32_t word[kAhead];
+            double v[kAhead][FUSED ? 2 * W : W];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const int b = b0 + k;
+                anti[k] = false;
+                word[k] = 0;
+                if (b < nb) {
+                    const uint64_t bm = bonds[b].mask, t = s & bm;
+                    anti[k] = valid && t != 0 && t != bm;
+                }
+                if (anti[k]) {
+                    word[k] = p[(size_t)(pos >> 2) * (kWave * 4) + (pos & 3)];
+                    ++pos;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                if (anti[k]) {
+                    const double *q = src + (size_t)(word[k] & im) * (FUSED ? 2 * W : W);
+                    if constexpr (FUSED && !CPLX) {
+                        const double2 a = *(const double2 *)q;
+                        v[k][0] = a.x;
+                        v[k][1] = a.y;
+                    } else if constexpr (FUSED) {
+                        const double2 a = *(const double2 *)q, g = *(const double2 *)(q + 2);
+                        v[k][0] = a.x;
+                        v[k][1] = a.y;
+                        v[k][2] = g.x;
+                        v[k][3] = g.y;
+                    } else {
+                        for (int m = 0; m < W; ++m) v[k][m] = q[m];
+                    }
+                } else {
+                    for (int m = 0; m < (FUSED ? 2 * W : W); ++m) v[k][m] = 0.0;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const int b = b0 + k;
+                if (b >= nb || !__ballot(anti[k])) continue;
+                double contrib = 0.0;
+                if (anti[k]) {
+                    const uint32_t cl = word[k] >> td.ibits;
+                    const double cr = chi[cl * W], ci = CPLX ? chi[cl * W + W - 1] : 0.0;
+                    contrib = -0.5 * gx_r;
+                    // a dropped term (row D) adds nothing, also not to a sum that is not finite
+                    if ((word[k] & im) < (uint32_t)D)
+                        contrib = fma(0.5 * rs_i, adjoint_term<CPLX>(cr, ci, v[k][0], CPLX ? v[k][W - 1] : 0.0, g_r, g_i), contrib);
+                    if (FUSED) {
+                        const double jh = bonds[b].jhalf;
+                        anti_sum += bonds[b].jzhalf;
+                        add_term<CPLX>(ar, ai, jh * cr, jh * ci, v[k][FUSED ? W : 0], CPLX ? v[k][FUSED ? 2 * W - 1 : 0] : 0.0);
+                    }
+                }
+                const double wsum = wave_sum(contrib);
+                if (lane == (b & (kWave - 1))) {
+                    const int q = b >> 6;
+                    if (q == 0) a0 += wsum;
+                    else if (q == 1) a1 += wsum;
+                    else if (q == 2) a2 += wsum;
+                    else a3 += wsum;
+                }
+            }
+        }
+        if (FUSED && valid) {
+            const double d = jsq - anti_sum;
+            if (CPLX) {
+                double2 out;
+                out.x = fma(rs_i, ar, d * g_r);
+                out.y = fma(rs_i, ai, d * g_i);
+                *(double2 *)&gx[2 * i] = out;
+            } else {
+                gx[i] = fma(rs_i, ar, d * g_r);
+            }
+        }
+    }
+    __syncthreads();
+    double *red = lds_d;   // [waves][nb + 1]
+    const int w1 = nb + 1;
+    for (int b = lane; b < nb; b += kWave) {
+        const int q = b >> 6;
+        red[wave * w1 + b] = q == 0 ? a0 : q == 1 ? a1 : q == 2 ? a2 : a3;
+    }
+    if (lane == 0) red[wave * w1 + nb] = tot;
+    __syncthreads();
+    for (int b = threadIdx.x; b < w1; b += blockDim.x) {
+        double sum = 0.0;
+        for (int w = 0; w < kTermsWaves; ++w) sum += red[w * w1 + b];
+        partials[(size_t)blockIdx.x * w1 + b] = sum;
+    }
+}
+
+// per-bond sums (and gx = H gy if given).  Without gx the scaled x is in
+// terms.xs.  The partial sums live in scratch if it is given.
+int terms_backward(const ed_basis *bc, const void *x, const void *gy, void *gx, double *gJ_host, double *scratch,
+                   size_t scratch_doubles, double jsq, void *stream)
+{
+    ed_basis *b = const_cast<ed_basis *>(bc);
+    hipStream_t st = (hipStream_t)stream;
+    const int nb = b->t.nb, W = b->dm.is_complex ? 2 : 1;
+    const int64_t D = b->db.dim;
+    // half the blocks of an H.v: each of them leaves a row of partial sums
+    int grid = terms_grid(b);
+    if (grid > 1024) grid = 1024;
+    const int chunks = grid % 8 == 0 ? 8 : 1;
+    const size_t n_part = (size_t)grid * (nb + 1);
+    if (gx && !b->terms.pair) {
+        void *p = nullptr;
+        const size_t bytes = ((size_t)D + 1) * 16 * W;
+        if (hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return set_error(ED_ERR_OOM, "adjoint pairs (%zu bytes)", bytes);
+        }
+        b->terms.pair = (double *)p;
+        b->device_bytes += (int64_t)bytes;
+        b->terms.bytes += (int64_t)bytes;
+    }
+    double *partials = nullptr, *out = nullptr;
+    if (scratch) {
+        if (n_part + (size_t)(nb + 1) > scratch_doubles)
+            return set_error(ED_ERR_UNSUPPORTED, "adjoint partials of %zu doubles exceed the %zu-double scratch array",
+                             n_part + (size_t)(nb + 1), scratch_doubles);
+        partials = scratch;
+    } else if (hipMalloc((void **)&partials, (n_part + nb + 1) * 8) != hipSuccess) {
+        (void)hipGetLastError();
+        return set_error(ED_ERR_OOM, "adjoint partials");
+    }
+    out = partials + n_part;
+    const size_t lds = std::max((size_t)b->terms.n_cls * W * 8 + (size_t)b->dm.n_div * 8 + (size_t)nb * sizeof(BondLds),
+                                (size_t)kTermsWaves * (nb + 1) * 8);
+    const double *sq = (const double *)(b->dm.blob + b->dm.off_div);
+    const dim3 pgrid((unsigned)std::min<int64_t>((D + 256) / 256, (int64_t)num_cus() * 16));
+#define ED_BACK(C, F) \
+    hipLaunchKernelGGL((k_terms_backward<C, F>), dim3(grid), dim3(kTermsThreads), lds, st, b->dm, terms_dev(b), b->db.states, \
+                       D, (const double *)(F ? b->terms.pair : b->terms.xs), (const Scalar<C>::T *)x, \
+                       (const Scalar<C>::T *)gy, partials, (double *)gx, jsq, chunks)
+    if (b->dm.is_complex) {
+        if (gx) {
+            hipLaunchKernelGGL(k_terms_pair<true>, pgrid, dim3(256), 0, st, (const double2 *)x, (const double2 *)gy,
+                               b->db.states, sq, b->terms.pair, D);
+            ED_BACK(true, true);
+        } else {
+            ED_BACK(true, false);
+        }
+    } else {
+        if (gx) {
+            hipLaunchKernelGGL(k_terms_pair<false>, pgrid, dim3(256), 0, st, (const double *)x, (const double *)gy,
+                               b->db.states, sq, b->terms.pair, D);
+            ED_BACK(false, true);
+        } else {
+            ED_BACK(false, false);
+        }
+    }
+#undef ED_BACK
+    int rc = sum_partials_cols(partials, grid, nb + 1, out, stream);
+    double h[kMaxBondWords * 64 + 1];
+    hipError_t e = rc ? hipSuccess : hipMemcpyAsync(h, out, (size_t)(nb + 1) * 8, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (!scratch) (void)hipFree(partials);
+    if (rc) return rc;
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "adjoint failed: %s", hipGetErrorString(e));
+    for (int k = 0; k < nb; ++k) gJ_host[k] = h[k] + 0.25 * h[nb];
+    return ED_OK;
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+
+void terms_free(ed_basis *b)
+{
+    auto &t = b->terms;
+    for (void *p : {t.words, (void *)t.off, (void *)t.cnt, (void *)t.xs, (void *)t.pair, (void *)t.cls, (void *)t.cls_chi})
+        if (p) (void)hipFree(p);
+    t.words = nullptr;
+    t.off = nullptr;
+    t.cnt = nullptr;
+    t.xs = t.pair = t.cls = t.cls_chi = nullptr;
+    b->device_bytes -= t.bytes;
+    t.bytes = 0;
+    t.couplings_ok = false;
+}
+
+// class coefficients of new couplings (ordered on the stream, which the
+// caller synchronises before the host arrays here go: none do, they are
+// copied first)
+int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream)
+{
+    auto &t = b->terms;
+    if (!t.words) return ED_OK;
+    hipStream_t st = (hipStream_t)stream;
+    // one coefficient per orbit: couplings that differ in their last bits
+    // within an orbit (the check allows 1e-12) run the searching kernels,
+    // which read them bond by bond
+    t.couplings_ok = false;
+    for (int k = 0; k < b->t.nb; ++k) {
+        const int f = t.orbit_bond[b->t.bond_orbit[k]];
+        if (J[k] != J[f] || Jz[k] != Jz[f]) return ED_OK;
+    }
+    const int W = b->dm.is_complex ? 4 : 2;
+    std::vector<double> tab((size_t)t.n_cls * W, 0.0);
+    const int n_chi = (int)t.chi_vals.size() / 2;
+    for (int x = 0; x < n_chi; ++x)
+        for (int o = 0; o < t.n_orb; ++o) {
+            double *c = &tab[((size_t)x * t.n_orb + o) * W];
+            const double jh = b->fermion ? -J[t.orbit_bond[o]] : 0.5 * J[t.orbit_bond[o]];
+            c[0] = jh * t.chi_vals[2 * x];
+            if (b->dm.is_complex) c[1] = jh * t.chi_vals[2 * x + 1];
+            c[b->dm.is_complex ? 2 : 1] = b->fermion ? 0.0 : 0.5 * Jz[t.orbit_bond[o]];
+        }
+    HIP_TRY(hipMemcpyAsync(t.cls, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    t.couplings_ok = true;
+    return ED_OK;
+}
+
+template <typename AT, int NSC, bool FERMI>
+static int fill_impl(ed_basis *b, const uint16_t *chi_class, const uint16_t *orbit, uint32_t pad, hipStream_t st)
+{
+    auto kern = k_terms_fill<AT, NSC, FERMI>;
+    const int th = (int)b->dm.lds_total * 2 > lds_limit() ? 1024 : 512;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, th, b->dm.lds_total) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    // few slices: several waves share one, so that a short table is not one
+    // wave's chain of searches
+    const int64_t slices = (b->db.dim + kWave - 1) / kWave, waves = (int64_t)per_cu * num_cus() * (th / kWave);
+    int parts = 1;
+    while (parts < 16 && slices * parts * 2 <= waves) parts *= 2;
+    const int64_t need = (slices * parts + th / kWave - 1) / (th / kWave);
+    const int grid = (int)std::max<int64_t>(std::min<int64_t>((int64_t)per_cu * num_cus(), need), 1);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(th), b->dm.lds_total, st, b->dm, b->db, (const uint64_t *)b->terms.off,
+                       b->terms.stride, b->terms.cnt, (uint32_t *)b->terms.words, chi_class, orbit, b->terms.n_orb,
+                       b->terms.ibits, pad, parts);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "term search launch failed: %s", hipGetErrorString(e));
+    return ED_OK;
+}
+
+// the search instances of the H.v kernels
+template <typename AT, bool FERMI>
+static int fill_ns(ed_basis *b, const uint16_t *cc, const uint16_t *orb, uint32_t pad, hipStream_t st)
+{
+    const int ns = b->dm.ns, nc = b->dm.n_chunks;
+    if constexpr (FERMI) {
+        if (ns == 4 && nc == 3) return fill_impl<AT, 35, true>(b, cc, orb, pad, st);
+        if (ns == 4 && nc == 2) return fill_impl<AT, 34, true>(b, cc, orb, pad, st);
+        return fill_impl<AT, 0, true>(b, cc, orb, pad, st);
+    } else {
+        constexpr int F = kStagedFlag;
+        if (b->staged) {
+            if (ns == 4 && nc == 1) return fill_impl<AT, 33 + F, false>(b, cc, orb, pad, st);
+            if (ns == 4 && nc == 2) return fill_impl<AT, 34 + F, false>(b, cc, orb, pad, st);
+            if (ns == 4 && nc == 3) return fill_impl<AT, 35 + F, false>(b, cc, orb, pad, st);
+            if (ns == 2) return fill_impl<AT, 16 + F, false>(b, cc, orb, pad, st);
+            if (ns == 3) return fill_impl<AT, 24 + F, false>(b, cc, orb, pad, st);
+            if (ns == 4) return fill_impl<AT, 32 + F, false>(b, cc, orb, pad, st);
+        }
+        if (ns == 4 && nc == 1) return fill_impl<AT, 33, false>(b, cc, orb, pad, st);
+        if (ns == 4 && nc == 2) return fill_impl<AT, 34, false>(b, cc, orb, pad, st);
+        if (ns == 4 && nc == 3) return fill_impl<AT, 35, false>(b, cc, orb, pad, st);
+        switch (ns) {
+        case 2: return fill_impl<AT, 16, false>(b, cc, orb, pad, st);
+        case 3: return fill_impl<AT, 24, false>(b, cc, orb, pad, st);
+        case 4: return fill_impl<AT, 32, false>(b, cc, orb, pad, st);
+        case 5: return fill_impl<AT, 40, false>(b, cc, orb, pad, st);
+        case 6: return fill_impl<AT, 48, false>(b, cc, orb, pad, st);
+        case 8: return fill_impl<AT, 64, false>(b, cc, orb, pad, st);
+        case 9: return fill_impl<AT, 72, false>(b, cc, orb, pad, st);
+        case 10: return fill_impl<AT, 80, false>(b, cc, orb, pad, st);
+        default: return fill_impl<AT, 0, false>(b, cc, orb, pad, st);
+        }
+    }
+}
+
+// Builds the table, if the sector can have one: a hash-slot basis with bonds,
+// a word that holds class and row, and a table of at most 1/16 of the device's
+// memory and half of what is free.  Anything else leaves the basis without
+// one, to the searching kernels; only an error of the device is returned.
+int terms_build(ed_basis *b, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    auto &t = b->terms;
+    const int64_t D = b->db.dim;
+    const int nb = b->t.nb, ng = b->t.ng;
+    if (b->db.index_mode != 0 || D < 1 || nb < 1) return ED_OK;
+    // distinct characters (fermions: and their negatives, for the sign)
+    std::vector<uint16_t> cls((size_t)ng * 2);
+    t.chi_vals.clear();
+    for (int sgn = 0; sgn < (b->fermion ? 2 : 1); ++sgn)
+        for (int g = 0; g < ng; ++g) {
+            const double re = sgn ? -b->chi_host[2 * g] : b->chi_host[2 * g];
+            const double im = b->dm.is_complex ? (sgn ? -b->chi_host[2 * g + 1] : b->chi_host[2 * g + 1]) : 0.0;
+            size_t k = 0;
+            while (k < t.chi_vals.size() && !(t.chi_vals[k] == re && t.chi_vals[k + 1] == im)) k += 2;
+            if (k / 2 >= (size_t)kMaxClasses) return ED_OK;
+            if (k == t.chi_vals.size()) {
+                t.chi_vals.push_back(re);
+                t.chi_vals.push_back(im);
+            }
+            cls[(size_t)sgn * ng + g] = (uint16_t)(k / 2);
+        }
+    std::vector<uint16_t> orb(nb);
+    t.orbit_bond.clear();
+    for (int k = 0; k < nb; ++k) {
+        orb[k] = (uint16_t)b->t.bond_orbit[k];
+        if ((size_t)orb[k] >= t.orbit_bond.size()) t.orbit_bond.resize(orb[k] + 1, -1);
+        if (t.orbit_bond[orb[k]] < 0) t.orbit_bond[orb[k]] = k;
+    }
+    t.n_orb = (int)t.orbit_bond.size();
+    t.n_cls = (int)(t.chi_vals.size() / 2) * t.n_orb + 1;   // and the padding
+    if (t.n_cls > kMaxClasses) return ED_OK;
+    int cbits = 1;
+    while ((1 << cbits) < t.n_cls) ++cbits;
+    t.ibits = 32 - cbits;
+    const size_t vec = ((size_t)D + 1) * (b->dm.is_complex ? 16 : 8);
+    if ((uint64_t)D >= (1ull << t.ibits) || vec > 0xFFFFFFFFull) return ED_OK;
+
+    const int64_t slices = (D + kWave - 1) / kWave;
+    auto give_up = [&]() {
+        (void)hipGetLastError();
+        terms_free(b);
+        return ED_OK;
+    };
+    auto take = [&](void **p, size_t bytes) {
+        if (hipMalloc(p, bytes) != hipSuccess) {
+            *p = nullptr;
+            return false;
+        }
+        t.bytes += (int64_t)bytes;
+        b->device_bytes += (int64_t)bytes;
+        return true;
+    };
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return give_up();
+    if (!take((void **)&t.cnt, (size_t)slices * 4)) return give_up();
+    // small sectors take the longest possible slices at a fixed stride; others
+    // are counted first
+    constexpr size_t kGroupBytes = (size_t)kWave * 16;
+    uint64_t groups = (uint64_t)slices * (uint64_t)((nb + 3) / 4);
+    if (groups * kGroupBytes <= (16u << 20)) {
+        t.stride = (uint32_t)((nb + 3) / 4);
+    } else {
+        t.stride = 0;
+        const unsigned g = (unsigned)std::min<int64_t>((slices + 3) / 4, (int64_t)num_cus() * 32);
+        hipLaunchKernelGGL(k_terms_count, dim3(g), dim3(256), 0, st, b->dm, b->db.states, D, t.cnt);
+        HIP_TRY(hipGetLastError());
+        if (!take((void **)&t.off, (size_t)slices * 8)) return give_up();
+        int rc = scan_counts(t.cnt, t.off, (uint64_t)slices, st);
+        if (rc == ED_ERR_OOM) return give_up();
+        if (rc) return rc;
+        uint64_t last_off = 0;
+        uint32_t last_cnt = 0;
+        HIP_TRY(hipMemcpyAsync(&last_off, t.off + slices - 1, 8, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(&last_cnt, t.cnt + slices - 1, 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        groups = last_off + last_cnt;
+    }
+    const size_t bytes = std::max<size_t>(groups, 1) * kGroupBytes;
+    if (bytes + vec > std::min(total_b / 16, free_b / 2)) return give_up();
+    const size_t clsb = (size_t)t.n_cls * (b->dm.is_complex ? 32 : 16);
+    void *d_cls = nullptr;   // chi classes and bond orbits, needed by the search only
+    if (!take(&t.words, bytes) || !take((void **)&t.xs, vec) || !take((void **)&t.cls, clsb) ||
+        !take((void **)&t.cls_chi, clsb / 2) || hipMalloc(&d_cls, (cls.size() + orb.size()) * 2) != hipSuccess)
+        return give_up();
+    std::vector<double> chi((size_t)t.n_cls * (b->dm.is_complex ? 2 : 1), 0.0);
+    for (int k = 0; k + 1 < t.n_cls; ++k) {
+        const double *v = &t.chi_vals[2 * (k / t.n_orb)];
+        if (b->dm.is_complex) {
+            chi[2 * k] = v[0];
+            chi[2 * k + 1] = v[1];
+        } else {
+            chi[k] = v[0];
+        }
+    }
+    cls.insert(cls.end(), orb.begin(), orb.end());
+    hipError_t e = hipMemcpyAsync(d_cls, cls.data(), cls.size() * 2, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(t.cls_chi, chi.data(), chi.size() * 8, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemsetAsync((char *)t.xs + vec - (b->dm.is_complex ? 16 : 8), 0, b->dm.is_complex ? 16 : 8, st);
+    int rc = ED_OK;
+    if (e == hipSuccess) {
+        const uint32_t pad = (uint32_t)(t.n_cls - 1) << t.ibits | (uint32_t)D;
+        const uint16_t *cc = (const uint16_t *)d_cls, *ob = cc + 2 * (size_t)ng;
+        if (b->fermion)
+            rc = b->dm.act_bytes == 2 ? fill_ns<FermiU16, true>(b, cc, ob, pad, st) : fill_ns<uint32_t, true>(b, cc, ob, pad, st);
+        else
+            rc = b->dm.act_bytes == 1   ? fill_ns<uint8_t, false>(b, cc, ob, pad, st)
+                 : b->dm.act_bytes == 2 ? fill_ns<uint16_t, false>(b, cc, ob, pad, st)
+                                        : fill_ns<uint32_t, false>(b, cc, ob, pad, st);
+        const hipError_t es = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = es;
+    }
+    (void)hipFree(d_cls);
+    if (rc) return rc;
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "term search failed: %s", hipGetErrorString(e));
+    b->J_cache.clear();
+    return ED_OK;
+}
+
+}  // namespace ed
+
+extern "C" int64_t ed_basis_terms_bytes(const ed_basis_t *b) { return b && b->terms.words ? b->terms.bytes : 0; }
+
+extern "C" int ed_basis_release_terms(ed_basis_t *b)
+{
+    if (!b) return ed::set_error(ED_ERR_ARG, "null basis");
+    if (!b->terms.words) return ED_OK;
+    if (hipDeviceSynchronize() != hipSuccess) return ed::set_error(ED_ERR_HIP, "device synchronisation");
+    ed::terms_free(b);
+    return ED_OK;
+}

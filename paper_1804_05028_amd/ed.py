@@ -63,6 +63,11 @@ class Basis:
     def info(self):
         return L.ed_basis_info(self.handle)
 
+    def release_terms(self):
+        """Give back the device memory of the stored terms; H.v, Lanczos and
+        adjoint then search each term again, with the same results."""
+        L.ed_basis_release_terms(self.handle)
+
     @property
     def dtype(self):
         return torch.complex128 if self.is_complex else torch.float64

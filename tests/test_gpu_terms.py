@@ -1,0 +1,166 @@
+"""Stored terms (one word per off-diagonal term, searched once per basis)
+against the searching kernels on the same basis: H.v and gx must agree bit for
+bit, since both sum a row's terms in bond order by the same operations.  The
+per-bond sums and the Lanczos coefficients add the rows in another order; their
+bound is a few times sqrt(rows) eps of the sum's terms, far below 1e-12.
+
+The cases take every width of table entry, one and several chunks, one- and
+two-stage search, real and complex sectors, fermions, couplings that differ
+between bond orbits, sectors of less than a slice of 64 rows, of exactly one,
+and on both sides of the 4096 (complex: 2048) rows up to which an H.v keeps its
+input in LDS, the counted (not fixed-stride) layout, and the refusals: the
+Limits index, too many classes, and couplings that differ in their last bit
+within an orbit."""
+import numpy as np
+import pytest
+import torch
+
+from ed_inputs import lattice as lat
+from ed_inputs import vectors as vec
+from ed_inputs import workloads as wl
+from tests.test_gpu_adjoint_fused import CASES as SPIN_CASES
+from tests.test_gpu_fermions import CASES as FERMI_CASES, IDS as FERMI_IDS
+from tests.test_gpu_parity import SMALL
+
+pytestmark = pytest.mark.gpu
+
+
+def _chain(n, sub, k, n_up, **kw):
+    c = lat.chain(n, superlattice_period=sub, **kw)
+    return wl.Workload(f"chain{n}", c, lat.characters(c, k), n_up, np.ones(c.n_bonds))
+
+
+def _trivial_group(n, n_up, sub=1):
+    """No symmetry but the identity: every bond an orbit of its own."""
+    c = lat.chain(n, superlattice_period=sub)
+    c.perm, c.flip = c.perm[:1], c.flip[:1]
+    return wl.Workload("open", c, np.ones(1, complex), n_up, np.linspace(0.5, 1.5, c.n_bonds))
+
+
+def _square24(k):
+    c = lat.square((6, 0), (0, 4), rotations=False, superlattice=wl.SQ_2X2)
+    o = lat.bond_orbits(c)
+    J = np.linspace(0.7, 1.3, o.max() + 1)[o]
+    return wl.Workload("square24", c, lat.characters(c, k), 12, J)
+
+
+EDGES = [
+    ("one_row", lambda: _chain(4, 2, 2, 2), None),
+    ("chain8_1up", lambda: _chain(8, 2, 0, 1), None),
+    ("chain14_k3", lambda: _chain(14, 7, 3, 5), None),
+    ("rows_64", lambda: _trivial_group(64 // 8, 1), None),
+    ("no_symmetry_924", lambda: _trivial_group(12, 6), None),
+    ("no_symmetry_3432", lambda: _trivial_group(14, 7, 2), None),
+    ("no_symmetry_4368", lambda: _trivial_group(16, 5, 2), None),    # above the LDS bound, real
+    ("chain18_k1", lambda: _chain(18, 3, 1, 9), None),               # complex, 2704 rows
+    ("chain16_k1", lambda: _chain(16, 4, 1, 8), None),               # complex, 800 rows
+    ("square24_k0", lambda: _square24(0), None),                     # 1.1e5 rows, counted layout
+    ("square24_k5", lambda: _square24(5), None),
+]
+CASES = EDGES + [c for c in SPIN_CASES if c[0] != "square32_disorder"] + [(n, (lambda w=w: w), None) for n, w in SMALL]
+
+
+def _vectors(b):
+    return [torch.as_tensor(vec.normal_vector(b.dim, seed=s, complex_=b.is_complex)).cuda() for s in (21, 22)]
+
+
+@pytest.mark.parametrize("name,make,tuning", CASES, ids=[c[0] for c in CASES])
+def test_stored_terms_equal_search(name, make, tuning):
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    w = make()
+    b = ed.Basis.from_workload(w, tuning)
+    try:
+        print(f"[terms] {name}: D={b.dim}", flush=True)
+        assert L.ed_basis_terms_bytes(b.handle) > 0 or b.dim == 0
+        o = lat.bond_orbits(w.cluster)
+        J = lat.orbit_mean(np.asarray(w.J, np.float64), o)
+        Jz = J * 0.37
+        x, gy = _vectors(b)
+        steps = max(1, min(12, b.dim // 3))
+
+        def all_of():
+            gx = b.empty()
+            gJ = L.ed_apply_H_backward(b.handle, J, x, gy, gx, True, None)
+            alone = L.ed_apply_H_backward(b.handle, J, x, gy, None, True, None)
+            assert np.array_equal(gJ, alone)
+            r = b.lanczos(J, x, steps, want_psi0=True, Jz=Jz)
+            return b.apply(J, x), b.apply(J, x, Jz=Jz), gx, gJ, r
+
+        a = all_of()
+        # couplings with one value off by a bit within an orbit: searched bond by bond
+        big = int(np.argmax(np.bincount(o)))
+        if np.bincount(o)[big] > 1:
+            J2 = J.copy()
+            k = np.nonzero(o == big)[0][-1]
+            J2[k] = np.nextafter(J2[k], 2.0)
+            y2 = b.apply(J2, x)
+        b.release_terms()
+        assert L.ed_basis_terms_bytes(b.handle) == 0
+        s = all_of()
+        torch.cuda.synchronize()
+        assert torch.equal(a[0], s[0]) and torch.equal(a[1], s[1]) and torch.equal(a[2], s[2])
+        if np.bincount(o)[big] > 1:
+            assert torch.equal(y2, b.apply(J2, x))
+        scale = max(1.0, np.abs(s[3]).max())
+        assert np.abs(a[3] - s[3]).max() <= 1e-12 * scale
+        assert a[4]["n_done"] == s[4]["n_done"]
+        assert np.abs(a[4]["alpha"] - s[4]["alpha"]).max() <= 1e-11
+        assert np.abs(a[4]["beta"] - s[4]["beta"]).max() <= 1e-11
+    finally:
+        b.close()
+
+
+@pytest.mark.parametrize("w,tune", FERMI_CASES, ids=FERMI_IDS)
+def test_stored_terms_equal_search_fermions(w, tune):
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    b = ed.FermionBasis.from_workload(w, tune)
+    try:
+        print(f"[terms] {w.name}: D={b.dim}", flush=True)
+        assert L.ed_basis_terms_bytes(b.handle) > 0 or b.dim == 0
+        if b.dim == 0:
+            return
+        x, _ = _vectors(b)
+        a = b.apply(w.t, x, V=w.V), b.apply(w.t, x)
+        b.release_terms()
+        assert torch.equal(a[0], b.apply(w.t, x, V=w.V)) and torch.equal(a[1], b.apply(w.t, x))
+    finally:
+        b.close()
+
+
+def test_refusals_and_release():
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    w = wl.square_4x4()
+    b = ed.Basis.from_workload(w, {"index_mode": 1})
+    assert L.ed_basis_terms_bytes(b.handle) == 0
+    b.release_terms()
+    b.close()
+    b = ed.Basis.from_workload(w)
+    held, before = L.ed_basis_terms_bytes(b.handle), b.info()["device_bytes"]
+    b.release_terms()
+    assert b.info()["device_bytes"] == before - held
+    b.release_terms()
+    b.close()
+
+
+def test_captured_call_replays():
+    """An H.v captured in a graph replays with new inputs and the eager result."""
+    from paper_1804_05028_amd import ed
+    for w in (wl.square_4x4(), _square24(0)):
+        b = ed.Basis.from_workload(w)
+        x, gy = _vectors(b)
+        buf, y = x.clone(), b.empty()
+        b.apply(w.J, buf, out=y)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            b.apply(w.J, buf, out=y)
+        for v in (gy, x, gy):
+            buf.copy_(v)
+            g.replay()
+            torch.cuda.synchronize()
+            got = y.clone()
+            assert torch.equal(got, b.apply(w.J, v))
+        b.close()
