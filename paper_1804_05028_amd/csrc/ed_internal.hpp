@@ -146,6 +146,8 @@ struct ed_basis {
         uint32_t stride = 0;
         double *xs = nullptr;          // [dim + 1] scaled input, its last entry 0
         double *pair = nullptr;        // [dim + 1] {x, gy} scaled, made by the first fused adjoint
+        unsigned int *next = nullptr;  // slice counters of the 8 row ranges (nullptr: fixed stride)
+        double *dots = nullptr;        // [n_slices] <v, w> of a Lanczos step, with the counters
         double *cls = nullptr;         // [n_cls] coefficients of the current couplings
         double *cls_chi = nullptr;     // [n_cls] characters
         std::vector<double> chi_vals;  // distinct characters (re, im)
@@ -215,7 +217,8 @@ int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream
 inline bool terms_usable(const ed_basis *b) { return b->terms.words && b->terms.couplings_ok; }
 // a sector whose scaled input fits the LDS of every block: its H.v reads x itself
 inline bool terms_small(const ed_basis *b) { return b->db.dim <= (b->dm.is_complex ? 2048 : 4096); }
-int terms_grid(const ed_basis *b);
+int terms_dots(const ed_basis *b);
+constexpr int kTermsNextStride = 32;
 int terms_apply(const ed_basis *b, const void *x, void *y, double jsq, void *stream);
 int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *vprev, double *partials, const void *lz,
                         double jsq, void *stream);

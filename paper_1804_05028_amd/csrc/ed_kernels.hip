@@ -231,11 +231,18 @@ __device__ __forceinline__ void put_scaled(char *dst, const uint32_t *slot_of, i
         *(double *)(dst + at) = v * sq;
 }
 
+// the stored terms' slice counters back to 0, before the H.v that follows
+__device__ __forceinline__ void reset_slices(unsigned int *next)
+{
+    if (next && blockIdx.x == 0 && threadIdx.x < 8) next[kTermsNextStride * threadIdx.x] = 0u;
+}
+
 // scaled amplitudes of x; sqrts: the square roots of the divisors of |G|
 template <bool CPLX, int TO>
 __global__ void k_pack(const typename Scalar<CPLX>::T *x, const uint64_t *states, const double *sqrts,
-                       const uint32_t *slot_of, char *dst, int64_t D)
+                       const uint32_t *slot_of, char *dst, int64_t D, unsigned int *next)
 {
+    if (TO == TO_TERMS) reset_slices(next);
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x)
         put_scaled<CPLX, TO>(dst, slot_of, j, sqrts[states[j] >> kNormShift], x[j]);
 }
@@ -759,9 +766,10 @@ template <bool CPLX, int TO>
 __global__ void __launch_bounds__(kVecThreads)
     k_lz_next(const typename Scalar<CPLX>::T *w, typename Scalar<CPLX>::T *vnew, int64_t D, const double *partials, int np,
               const LzState *lz, LzState *lz_next, const double *alpha_hist, double *beta_hist, int n_steps, double tol,
-              const uint64_t *states, const double *sqrts, const uint32_t *slot_of, char *dst)
+              const uint64_t *states, const double *sqrts, const uint32_t *slot_of, char *dst, unsigned int *next)
 {
     __shared__ double sh[kVecThreads / kWave + 1];
+    if (TO == TO_TERMS) reset_slices(next);
     const LzState cur = *lz;
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     if (cur.done) {
@@ -1315,7 +1323,7 @@ static int pack_input(const ed_basis *b, const void *x, hipStream_t st)
     const double *sq = sqrt_table(b);
     char *dst = input_dst(b, to);
 #define ED_PACK(C, TO) \
-    hipLaunchKernelGGL((k_pack<C, TO>), g, dim3(256), 0, st, (const Scalar<C>::T *)x, b->db.states, sq, b->db.slot_of, dst, D)
+    hipLaunchKernelGGL((k_pack<C, TO>), g, dim3(256), 0, st, (const Scalar<C>::T *)x, b->db.states, sq, b->db.slot_of, dst, D, b->terms.next)
     if (b->dm.is_complex) {
         if (to == TO_TERMS) ED_PACK(true, TO_TERMS);
         else ED_PACK(true, TO_SLOTS);
@@ -1715,7 +1723,7 @@ static void launch_lz_next(const ed_basis *b, int vgrid, const double *w, double
     using T = typename Scalar<CPLX>::T;
     hipLaunchKernelGGL((k_lz_next<CPLX, TO>), dim3(vgrid), dim3(kVecThreads), 0, st, (const T *)w, (T *)vnew, b->db.dim,
                        partials, vgrid, lz, lz_next, ahist, bhist, n_steps, 1e-12, b->db.states, sqrt_table(b),
-                       b->db.slot_of, input_dst(b, TO));
+                       b->db.slot_of, input_dst(b, TO), b->terms.next);
 }
 
 int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const void *v0, int n_steps, double *alpha,
@@ -1741,7 +1749,7 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     }
     const int vgrid = (int)std::min<int64_t>((nd + kVecThreads - 1) / kVecThreads, (int64_t)num_cus() * 8);
     const int to = input_place(b);
-    const int np_apply = to == TO_TERMS ? terms_grid(b) : b->grid_blocks;
+    const int np_apply = to == TO_TERMS ? terms_dots(b) : b->grid_blocks;
     const size_t vb = (size_t)nd * 8;
     auto &W = b->lzw;
     const size_t npart = (size_t)std::max(np_apply, vgrid);

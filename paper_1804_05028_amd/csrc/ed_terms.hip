@@ -25,6 +25,7 @@ namespace ed {
 constexpr int kTermsThreads = 256;
 constexpr int kTermsWaves = kTermsThreads / kWave;
 constexpr int kMaxClasses = 1024;
+constexpr int kNextStride = kTermsNextStride;   // a counter per 128-byte line
 
 struct TermsDev {
     const uint4 *words;
@@ -198,29 +199,87 @@ __device__ __forceinline__ TermsLds<CPLX> stage_terms(const DevModel &dm, const 
     return t;
 }
 
-// the four terms of a group; anti collects the Ising parts of their bonds
-template <bool CPLX, typename XS>
-__device__ __forceinline__ void add_group(const TermsLds<CPLX> &tl, uint4 w, int ibits, XS xs, double &ar, double &ai,
-                                          double &anti)
+// the words of groups first .. first + kUnroll - 1; padding beyond the last
+template <int U>
+__device__ __forceinline__ void load_part(uint4 (&w)[U], const uint4 *p, int first, int groups, uint32_t none)
+{
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        w[u] = first + u < groups ? load_words(p + (size_t)(first + u) * kWave) : make_uint4(none, none, none, none);
+}
+
+// their terms, all gathers requested before the first is used; anti collects
+// the Ising parts of their bonds
+template <bool CPLX, int U, typename XS>
+__device__ __forceinline__ void add_part(const TermsLds<CPLX> &tl, const uint4 (&w)[U], int first, int groups, int ibits, XS xs,
+                                         double &ar, double &ai, double &anti)
 {
     const uint32_t im = (1u << ibits) - 1u;
-    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-    typename Scalar<CPLX>::T v[4];
+    typename Scalar<CPLX>::T v[U * 4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = xs(ww[k] & im);
+    for (int u = 0; u < U; ++u) {
+        if (first + u >= groups) break;   // uniform
+        v[4 * u] = xs(w[u].x & im);
+        v[4 * u + 1] = xs(w[u].y & im);
+        v[4 * u + 2] = xs(w[u].z & im);
+        v[4 * u + 3] = xs(w[u].w & im);
+    }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t cl = ww[k] >> ibits;
-        if constexpr (CPLX) {
-            const double2 c = *(const double2 *)(tl.cls + 4 * cl);
-            add_term<true>(ar, ai, c.x, c.y, v[k].x, v[k].y);
-            anti += tl.cls[4 * cl + 2];
-        } else {
-            const double2 c = *(const double2 *)(tl.cls + 2 * cl);
-            add_term<false>(ar, ai, c.x, 0.0, v[k], 0.0);
-            anti += c.y;
+    for (int u = 0; u < U; ++u) {
+        if (first + u >= groups) break;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t cl = (k == 0 ? w[u].x : k == 1 ? w[u].y : k == 2 ? w[u].z : w[u].w) >> ibits;
+            if constexpr (CPLX) {
+                const double2 c = *(const double2 *)(tl.cls + 4 * cl);
+                add_term<true>(ar, ai, c.x, c.y, v[4 * u + k].x, v[4 * u + k].y);
+                anti += tl.cls[4 * cl + 2];
+            } else {
+                const double2 c = *(const double2 *)(tl.cls + 2 * cl);
+                add_term<false>(ar, ai, c.x, 0.0, v[4 * u + k], 0.0);
+                anti += c.y;
+            }
         }
     }
+}
+
+// y_i from the finished sums; returns Re(conj(x_i) y_i) in MODE 2
+template <bool CPLX, int MODE, bool FERMI>
+__device__ __forceinline__ double finish_row(const TermsLds<CPLX> &tl, int nb, uint64_t e, double ar, double ai, double anti,
+                                             typename Scalar<CPLX>::T xi, typename Scalar<CPLX>::T vp, double beta_prev,
+                                             double jsq, typename Scalar<CPLX>::T *y)
+{
+    double d;
+    if (FERMI) {
+        const uint64_t s = e & kStateMask;
+        d = 0.0;
+        for (int k = 0; k < nb; ++k) {
+            const uint64_t bm = tl.bonds[k].mask;
+            if ((s & bm) == bm) d += tl.bonds[k].jzhalf;
+        }
+    } else {
+        d = jsq - anti;
+    }
+    const double rs = tl.rsqrt[e >> kNormShift];
+    double dot = 0.0;
+    typename Scalar<CPLX>::T out;
+    if constexpr (CPLX) {
+        out.x = fma(rs, ar, d * xi.x);
+        out.y = fma(rs, ai, d * xi.y);
+        if (MODE == 2) {
+            out.x = fma(-beta_prev, vp.x, out.x);
+            out.y = fma(-beta_prev, vp.y, out.y);
+            dot = fma(xi.x, out.x, xi.y * out.y);
+        }
+    } else {
+        out = fma(rs, ar, d * xi);
+        if (MODE == 2) {
+            out = fma(-beta_prev, vp, out);
+            dot = xi * out;
+        }
+    }
+    *y = out;
+    return dot;
 }
 
 template <bool CPLX, int MODE, bool FERMI, typename XS>
@@ -241,66 +300,45 @@ __device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const Term
         if (MODE == 2) vp = vprev[i];
     }
     double ar = 0.0, ai = 0.0, anti = 0.0;
-    uint4 w = make_uint4(0, 0, 0, 0), w2 = w;
-    if (groups > 0) w = load_words(p);
-    if (groups > 1) w2 = load_words(p + kWave);
-    for (int g = 0; g < groups; ++g) {
-        uint4 w3 = w2;
-        if (g + 2 < groups) w3 = load_words(p + (size_t)(g + 2) * kWave);
-        add_group<CPLX>(tl, w, td.ibits, xs, ar, ai, anti);
-        w = w2;
-        w2 = w3;
+    // the words of the next groups are read while these are gathered
+    const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
+    constexpr int U = 4;
+    uint4 w[U], nx[U];
+    load_part<U>(w, p, 0, groups, none);
+    for (int g = 0; g < groups; g += U) {
+        load_part<U>(nx, p, g + U, groups, none);
+        add_part<CPLX, U>(tl, w, g, groups, td.ibits, xs, ar, ai, anti);
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = nx[u];
     }
-    double d;
-    if (FERMI) {
-        const uint64_t s = e & kStateMask;
-        d = 0.0;
-        for (int k = 0; k < nb; ++k) {
-            const uint64_t bm = tl.bonds[k].mask;
-            if ((s & bm) == bm) d += tl.bonds[k].jzhalf;
-        }
-    } else {
-        d = jsq - anti;
-    }
-    double dot = 0.0;
-    if (ok) {
-        const double rs = tl.rsqrt[e >> kNormShift];
-        T out;
-        if constexpr (CPLX) {
-            out.x = fma(rs, ar, d * xi.x);
-            out.y = fma(rs, ai, d * xi.y);
-            if (MODE == 2) {
-                out.x = fma(-beta_prev, vp.x, out.x);
-                out.y = fma(-beta_prev, vp.y, out.y);
-                dot = fma(xi.x, out.x, xi.y * out.y);
-            }
-        } else {
-            out = fma(rs, ar, d * xi);
-            if (MODE == 2) {
-                out = fma(-beta_prev, vp, out);
-                dot = xi * out;
-            }
-        }
-        y[i] = out;
-    }
-    return dot;
+    return ok ? finish_row<CPLX, MODE, FERMI>(tl, nb, e, ar, ai, anti, xi, vp, beta_prev, jsq, y + i) : 0.0;
 }
 
 // H.v from the stored terms: a coalesced read of the words and a gather of
-// scaled amplitudes.
+// scaled amplitudes, bound by the lines of 128 bytes that the gathers miss in
+// L2 (random lines come at 55e9 per second here, from HBM and MALL alike).
 // The rows are in ascending order and consecutive rows differ in their last
 // bits, so that the targets of one bond lie close together too: on the 32-site
-// square sector the 64 rows of a slice touch 0.57 lines of 128 bytes per term
-// and load instruction, 0.35 over all their terms, and 8192 consecutive rows
-// 0.21 (36-site triangular: 0.74, 0.51, 0.20), where hashed slots cost 1.04.
+// square sector the 64 rows of a slice touch 0.57 lines per term and load
+// instruction, 0.35 over all their terms, and 8192 consecutive rows 0.21
+// (36-site triangular: 0.74, 0.51, 0.20), where hashed slots cost 1.04.
 // chunks = 8 gives each XCD (blocks go round the XCDs in turn) one contiguous
 // range of rows, which its L2 then shares.
+//
+// Lines are shared only while they stay in L2, so few rows should be in work
+// at a time, and these should be neighbours.  Where the input exceeds the L2s,
+// one block per compute unit runs (four waves with 16 gathers of each lane in
+// flight) and a wave takes the next slice of its XCD's range from a counter:
+// with a fixed stride the waves drift apart and so do their rows.  32-site
+// square 4.68 ms with eight blocks and a fixed stride, 3.91 with one, 3.05
+// with the counter; 36-site triangular 5.20, 4.47, 3.46 ms.  The 1.4e6 rows of
+// the 28-site square (11 MB) gain nothing: 157, 171, 179 us.
 template <bool CPLX, int MODE, bool FERMI>
 __global__ void __launch_bounds__(kTermsThreads)
     k_terms_apply(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int64_t D,
                   const typename Scalar<CPLX>::T *__restrict__ xs, const typename Scalar<CPLX>::T *__restrict__ x,
                   typename Scalar<CPLX>::T *__restrict__ y, const typename Scalar<CPLX>::T *__restrict__ vprev,
-                  double *partials, const LzState *lz, double jsq, int chunks)
+                  double *partials, const LzState *lz, double jsq, int chunks, unsigned int *next)
 {
     using T = typename Scalar<CPLX>::T;
     extern __shared__ __align__(16) double lds_d[];
@@ -314,6 +352,23 @@ __global__ void __launch_bounds__(kTermsThreads)
     const int64_t last = min(first + per, n_slices);
     const int64_t step = (int64_t)(gridDim.x / chunks) * kTermsWaves;
     auto gather = [&](uint32_t j) { return *(const T *)((const char *)xs + (uint32_t)(j * (uint32_t)sizeof(T))); };
+    if (next) {
+        // the counter's last value is taken by every wave of the range in turn
+        // beyond its end; k_pack and k_lz_next set it back to 0
+        unsigned int *ctr = next + kNextStride * (blockIdx.x % chunks);
+        unsigned int mine = lane == 0 ? atomicAdd(ctr, 1u) : 0u;
+        while (true) {
+            const int64_t sl = first + (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
+            if (sl >= last) return;
+            mine = lane == 0 ? atomicAdd(ctr, 1u) : 0u;   // the one after, asked for early
+            const double t = terms_row<CPLX, MODE, FERMI>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, beta_prev, jsq);
+            // which wave takes a slice varies from run to run: one sum per slice
+            if (MODE == 2) {
+                const double ws = wave_sum(t);
+                if (lane == 0) partials[sl] = ws;
+            }
+        }
+    }
     double dot = 0.0;
     for (int64_t sl = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave; sl < last; sl += step)
         dot += terms_row<CPLX, MODE, FERMI>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, beta_prev, jsq);
@@ -322,6 +377,18 @@ __global__ void __launch_bounds__(kTermsThreads)
         const double t = block_sum(dot, sh);
         if (threadIdx.x == 0) partials[blockIdx.x] = t;
     }
+}
+
+// the slices' <v, w> in kDotBlocks partial sums
+constexpr int kDotBlocks = 64;
+__global__ void __launch_bounds__(kTermsThreads) k_terms_dots(const double *dots, int64_t n, double *partials, const LzState *lz)
+{
+    __shared__ double sh[kTermsWaves];
+    if (lz->done) return;
+    double a = 0.0;
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) a += dots[k];
+    const double t = block_sum(a, sh);
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
 // The same for sectors whose input fits LDS: every block scales all of x into
@@ -358,13 +425,17 @@ __global__ void __launch_bounds__(kTermsThreads)
 }
 
 // blocks of a pass over all slices: a multiple of 8 (see chunks) where there
-// are at least 8 blocks' worth, at most 8 per compute unit
+// are at least 8 blocks' worth; one per compute unit with the slice counter,
+// else at most 8
 int terms_grid(const ed_basis *b)
 {
     const int64_t blocks = ((b->db.dim + kWave - 1) / kWave + kTermsWaves - 1) / kTermsWaves;
     if (blocks < 8) return (int)std::max<int64_t>(blocks, 1);
-    return (int)std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * 8 & ~7));
+    return (int)std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * (b->terms.next ? 1 : 8) & ~7));
 }
+
+// partial sums that a Lanczos H.v leaves
+int terms_dots(const ed_basis *b) { return b->terms.next ? kDotBlocks : terms_grid(b); }
 
 static int terms_chunks(const ed_basis *b) { return terms_grid(b) % 8 == 0 ? 8 : 1; }
 
@@ -383,7 +454,11 @@ static int launch_terms(const ed_basis *b, const void *x, void *y, const void *v
     } else {
         hipLaunchKernelGGL((k_terms_apply<CPLX, MODE, FERMI>), dim3(terms_grid(b)), dim3(kTermsThreads), lds, st, b->dm,
                            terms_dev(b), b->db.states, b->db.dim, (const T *)b->terms.xs, (const T *)x, (T *)y,
-                           (const T *)vprev, partials, (const LzState *)lz, jsq, terms_chunks(b));
+                           (const T *)vprev, b->terms.next ? b->terms.dots : partials, (const LzState *)lz, jsq,
+                           terms_chunks(b), b->terms.next);
+        if (MODE == 2 && b->terms.next)
+            hipLaunchKernelGGL(k_terms_dots, dim3(kDotBlocks), dim3(kTermsThreads), 0, st, (const double *)b->terms.dots,
+                               (b->db.dim + kWave - 1) / kWave, partials, (const LzState *)lz);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "H.v launch failed: %s", hipGetErrorString(e));
@@ -600,10 +675,11 @@ int terms_backward(const ed_basis *bc, const void *x, const void *gy, void *gx, 
     hipStream_t st = (hipStream_t)stream;
     const int nb = b->t.nb, W = b->dm.is_complex ? 2 : 1;
     const int64_t D = b->db.dim;
-    // half the blocks of an H.v: each of them leaves a row of partial sums
-    int grid = terms_grid(b);
-    if (grid > 1024) grid = 1024;
-    const int chunks = grid % 8 == 0 ? 8 : 1;
+    // at most 4 blocks per compute unit, each of which leaves a row of partial
+    // sums, and slices at a fixed stride: the sums are the same on every run
+    int64_t blocks = ((D + kWave - 1) / kWave + kTermsWaves - 1) / kTermsWaves;
+    if (blocks >= 8) blocks = std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * 4 & ~7));
+    const int grid = (int)blocks, chunks = grid % 8 == 0 ? 8 : 1;
     const size_t n_part = (size_t)grid * (nb + 1);
     if (gx && !b->terms.pair) {
         void *p = nullptr;
@@ -671,12 +747,14 @@ int terms_backward(const ed_basis *bc, const void *x, const void *gy, void *gx, 
 void terms_free(ed_basis *b)
 {
     auto &t = b->terms;
-    for (void *p : {t.words, (void *)t.off, (void *)t.cnt, (void *)t.xs, (void *)t.pair, (void *)t.cls, (void *)t.cls_chi})
+    for (void *p : {t.words, (void *)t.off, (void *)t.cnt, (void *)t.xs, (void *)t.pair, (void *)t.cls, (void *)t.cls_chi,
+                    (void *)t.next, (void *)t.dots})
         if (p) (void)hipFree(p);
     t.words = nullptr;
     t.off = nullptr;
     t.cnt = nullptr;
-    t.xs = t.pair = t.cls = t.cls_chi = nullptr;
+    t.xs = t.pair = t.cls = t.cls_chi = t.dots = nullptr;
+    t.next = nullptr;
     b->device_bytes -= t.bytes;
     t.bytes = 0;
     t.couplings_ok = false;
@@ -859,10 +937,13 @@ int terms_build(ed_basis *b, void *stream)
     }
     const size_t bytes = std::max<size_t>(groups, 1) * kGroupBytes;
     if (bytes + vec > std::min(total_b / 16, free_b / 2)) return give_up();
+    // the scaled input exceeds the L2s (8 x 4 MB): slices from a counter
+    const bool counted = vec > (32u << 20);
     const size_t clsb = (size_t)t.n_cls * (b->dm.is_complex ? 32 : 16);
     void *d_cls = nullptr;   // chi classes and bond orbits, needed by the search only
     if (!take(&t.words, bytes) || !take((void **)&t.xs, vec) || !take((void **)&t.cls, clsb) ||
-        !take((void **)&t.cls_chi, clsb / 2) || hipMalloc(&d_cls, (cls.size() + orb.size()) * 2) != hipSuccess)
+        !take((void **)&t.cls_chi, clsb / 2) ||
+        (counted && (!take((void **)&t.next, 8 * kNextStride * 4) || !take((void **)&t.dots, (size_t)slices * 8))) || hipMalloc(&d_cls, (cls.size() + orb.size()) * 2) != hipSuccess)
         return give_up();
     std::vector<double> chi((size_t)t.n_cls * (b->dm.is_complex ? 2 : 1), 0.0);
     for (int k = 0; k + 1 < t.n_cls; ++k) {

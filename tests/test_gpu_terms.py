@@ -60,6 +60,11 @@ EDGES = [
 CASES = EDGES + [c for c in SPIN_CASES if c[0] != "square32_disorder"] + [(n, (lambda w=w: w), None) for n, w in SMALL]
 
 
+def _square32(k, n_up):
+    c = lat.square((4, 4), (-4, 4), rotations=False, superlattice=wl.SQ_2X2)
+    return wl.Workload("square32", c, lat.characters(c, k), n_up, np.ones(c.n_bonds))
+
+
 def _vectors(b):
     return [torch.as_tensor(vec.normal_vector(b.dim, seed=s, complex_=b.is_complex)).cuda() for s in (21, 22)]
 
@@ -125,6 +130,40 @@ def test_stored_terms_equal_search_fermions(w, tune):
         a = b.apply(w.t, x, V=w.V), b.apply(w.t, x)
         b.release_terms()
         assert torch.equal(a[0], b.apply(w.t, x, V=w.V)) and torch.equal(a[1], b.apply(w.t, x))
+    finally:
+        b.close()
+
+
+# inputs on both sides of the 32 MB above which slices come from a counter
+COUNTED = [("square32_n11", 0, 11, False), ("square32_n12", 0, 12, True), ("square32_k1_n10", 1, 10, False),
+           ("square32_k1_n11", 1, 11, True)]
+
+
+@pytest.mark.parametrize("name,k,n_up,counted", COUNTED, ids=[c[0] for c in COUNTED])
+def test_slice_counter(name, k, n_up, counted):
+    """Repeated H.v and Lanczos calls with slices taken from a counter give the
+    same bits each time, and those of the searching kernels."""
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    w = _square32(k, n_up)
+    b = ed.Basis.from_workload(w)
+    try:
+        print(f"[terms] {name}: D={b.dim}", flush=True)
+        assert (b.dim * (16 if b.is_complex else 8) > 32 << 20) == counted
+        x, gy = _vectors(b)
+        y = b.apply(w.J, x)
+        z = b.apply(w.J, gy)
+        assert torch.equal(y, b.apply(w.J, x)) and torch.equal(z, b.apply(w.J, gy))
+        r = b.lanczos(w.J, x, 5)
+        r2 = b.lanczos(w.J, x, 5)
+        assert np.array_equal(r["alpha"], r2["alpha"]) and np.array_equal(r["beta"], r2["beta"])
+        gx = b.empty()
+        L.ed_apply_H_backward(b.handle, w.J, x, gy, gx, True, None)
+        assert torch.equal(gx, z)
+        b.release_terms()
+        assert torch.equal(y, b.apply(w.J, x)) and torch.equal(z, b.apply(w.J, gy))
+        s = b.lanczos(w.J, x, 5)
+        assert np.abs(r["alpha"] - s["alpha"]).max() <= 1e-11 and np.abs(r["beta"] - s["beta"]).max() <= 1e-11
     finally:
         b.close()
 
