@@ -237,8 +237,10 @@ static int build_basis_common(const ed_lattice_t *lat, const ed_group_t *grp, co
     b->staged = two_stage_ok && (b->tuning.search_mode == ED_SEARCH_TWO_STAGE ||
                                  (b->tuning.search_mode == 0 && b->mean_candidates >= kTwoStageMinCandidates));
     dm.staged = b->staged;
+    b->want_terms = own_terms;
     rc = ed::launch_basis_build(b, stream);
-    if (!rc && own_terms) rc = ed::terms_build(b, stream);
+    if (!rc) rc = ed::terms_build(b, stream);
+    ed::free_rep_index(b);
     if (rc) {
         ed_free_basis(b);
         return rc;

@@ -1,6 +1,8 @@
 // Internal declarations shared by the host code and the HIP kernels.
 #pragma once
 
+#include <hip/hip_runtime.h>
+
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -105,6 +107,19 @@ struct DevBasis {
     const uint32_t *slot_of;   // [dim] slot index of every representative
 };
 
+// Rows of the representatives by (top block, middle bits, last R bits): entry
+// prefix * chunks + k / 64, k the pattern's rank among the R-bit patterns of
+// its popcount, holds a bit per kept pattern and the row of the first.  Made
+// by the basis build for the search of the stored terms.  Consecutive rows
+// share entries, so that this costs fewer lines than a hashed slot.
+struct RepIndex {
+    ulonglong2 *entries;
+    uint32_t chunks;
+    int R, mid_bits;
+    const uint16_t *rank;       // [2^R] rank of a pattern
+    const uint16_t *top_rank;   // [2^m] rank of a top block
+};
+
 }  // namespace ed
 
 struct ed_tables {
@@ -136,6 +151,10 @@ struct ed_basis {
     // (32 bytes real, 64 bytes complex), allocated by the first fused call
     // and freed with the handle
     char *adj_slots = nullptr;
+    // index for the search of the stored terms, freed after it
+    ed::RepIndex rep_index{};
+    uint16_t *rep_lists = nullptr;
+    bool want_terms = false;       // the basis may store its terms (not a batched one's)
     // stored terms: the target and coefficient class of every off-diagonal
     // term (ed_terms.hip), made with the basis where they fit, freed with it
     // or by ed_basis_release_terms
@@ -211,7 +230,9 @@ int run_lanczos(const ed_basis *b, const double *J, const double *Jz, const void
 int check_couplings(const ed_basis *b, const double *J);
 int scan_counts(const uint32_t *counts, uint64_t *offsets, uint64_t n, void *stream);
 // Stored terms (ed_terms.hip)
+bool terms_wanted(const ed_basis *b);
 int terms_build(ed_basis *b, void *stream);
+void free_rep_index(ed_basis *b);
 void terms_free(ed_basis *b);
 int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream);
 inline bool terms_usable(const ed_basis *b) { return b->terms.words && b->terms.couplings_ok; }
