@@ -431,6 +431,14 @@ int ed_build_multi(const ed_lattice_t *lat, const ed_group_t *grp, int32_t n_sec
                    int32_t n_up, const ed_tuning_t *tuning, void *stream, ed_multi_t **out);
 void ed_free_multi(ed_multi_t *mb);
 int ed_multi_info(const ed_multi_t *mb, ed_multi_info_t *info);
+/*
+ * Stored terms of the shared rows, as for ed_build_basis (at most 56 sectors;
+ * elements with equal characters in every sector share a class): device memory
+ * they take (0: none), and giving it back.  The searching kernels then give
+ * the same results up to rounding.
+ */
+int64_t ed_multi_terms_bytes(const ed_multi_t *mb);
+int ed_multi_release_terms(ed_multi_t *mb);
 /* dims_host[k] = dimension of sector k (rows with bit k set). */
 int ed_multi_sector_dims(const ed_multi_t *mb, int64_t *dims_host);
 /* Shared representatives, ascending -> host [dim] (synchronises). */

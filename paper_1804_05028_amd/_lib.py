@@ -125,6 +125,8 @@ PROTOTYPES = {
     "ed_build_multi": (ctypes.c_int, [P, P, I32, P, I32, P, P, P]),
     "ed_free_multi": (None, [P]),
     "ed_multi_info": (ctypes.c_int, [P, P]),
+    "ed_multi_terms_bytes": (I64, [P]),
+    "ed_multi_release_terms": (ctypes.c_int, [P]),
     "ed_multi_sector_dims": (ctypes.c_int, [P, P]),
     "ed_multi_copy_states": (ctypes.c_int, [P, P, P]),
     "ed_multi_copy_masks": (ctypes.c_int, [P, P, P]),
@@ -447,6 +449,14 @@ def ed_build_multi(arrays: ModelArrays, chis, n_up, tuning=None, stream=None):
 
 def ed_free_multi(h):
     lib().ed_free_multi(h)
+
+
+def ed_multi_terms_bytes(h):
+    return lib().ed_multi_terms_bytes(h)
+
+
+def ed_multi_release_terms(h):
+    return check(lib().ed_multi_release_terms(h))
 
 
 def ed_multi_info(h):

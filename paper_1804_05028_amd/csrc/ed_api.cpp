@@ -237,10 +237,12 @@ static int build_basis_common(const ed_lattice_t *lat, const ed_group_t *grp, co
     b->staged = two_stage_ok && (b->tuning.search_mode == ED_SEARCH_TWO_STAGE ||
                                  (b->tuning.search_mode == 0 && b->mean_candidates >= kTwoStageMinCandidates));
     dm.staged = b->staged;
-    b->want_terms = own_terms;
+    b->want_terms = true;
     rc = ed::launch_basis_build(b, stream);
-    if (!rc) rc = ed::terms_build(b, stream);
-    ed::free_rep_index(b);
+    if (!rc && own_terms) {   // a batched basis stores its terms in multi_setup
+        rc = ed::terms_build(b, stream);
+        ed::free_rep_index(b);
+    }
     if (rc) {
         ed_free_basis(b);
         return rc;
@@ -268,6 +270,7 @@ void ed_free_basis(ed_basis_t *b)
     (void)hipDeviceSynchronize();
     ed::free_lanczos_workspace(b);
     ed::terms_free(b);
+    ed::free_rep_index(b);
     for (void *p : b->allocs) (void)hipFree(p);
     delete b;
 }
@@ -544,6 +547,7 @@ int ed_build_multi(const ed_lattice_t *lat, const ed_group_t *grp, int32_t n_sec
     for (int k = 0; k < n_sectors; ++k)
         std::copy(irreps[k].chi, irreps[k].chi + 2 * (size_t)ng, mb->chi_host.begin() + (size_t)k * ng * 2);
     rc = ed::multi_setup(mb, stream);
+    ed::free_rep_index(mb->base);
     if (rc) {
         ed_free_multi(mb);
         return rc;
@@ -558,8 +562,19 @@ void ed_free_multi(ed_multi_t *mb)
     if (!mb) return;
     (void)hipDeviceSynchronize();
     ed::multi_free_workspace(mb);
+    ed::multi_free_terms(mb);
     ed_free_basis(mb->base);
     delete mb;
+}
+
+int64_t ed_multi_terms_bytes(const ed_multi_t *mb) { return mb && mb->terms.row_class ? mb->base->terms.bytes : 0; }
+
+int ed_multi_release_terms(ed_multi_t *mb)
+{
+    if (!mb) return set_error(ED_ERR_ARG, "null basis");
+    if (hipDeviceSynchronize() != hipSuccess) return set_error(ED_ERR_HIP, "device synchronisation");
+    ed::multi_free_terms(mb);
+    return ED_OK;
 }
 
 int ed_multi_info(const ed_multi_t *mb, ed_multi_info_t *info)

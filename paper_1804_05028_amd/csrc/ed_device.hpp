@@ -707,6 +707,41 @@ __device__ __forceinline__ double total_of(const double *partials, int n, double
     return *res;
 }
 
+// ---------------------------------------------------------------------------
+// stored terms (ed_terms.hip)
+// ---------------------------------------------------------------------------
+struct TermsDev {
+    const uint4 *words;
+    const uint64_t *off;
+    const uint32_t *cnt;
+    uint32_t stride;
+    int ibits, n_cls;
+    const double *cls;        // {kr, jz} or {kr, ki, jz, -} of every class
+    const double *cls_chi;    // chi or {re, im} of every class
+};
+
+inline TermsDev terms_dev(const ed_basis *b)
+{
+    TermsDev td;
+    td.words = (const uint4 *)b->terms.words;
+    td.off = b->terms.off;
+    td.cnt = b->terms.cnt;
+    td.stride = b->terms.stride;
+    td.ibits = b->terms.ibits;
+    td.n_cls = b->terms.n_cls;
+    td.cls = b->terms.cls;
+    td.cls_chi = b->terms.cls_chi;
+    return td;
+}
+
+__device__ __forceinline__ uint4 load_words(const uint4 *p)
+{
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    // read once per pass: kept out of the way of the amplitudes in L2
+    const u32x4 v = __builtin_nontemporal_load((const u32x4 *)p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 int upload_couplings(const ed_basis *bc, const double *J, const double *Jz, hipStream_t st, double *jsum_quarter);
 
 }  // namespace ed

@@ -202,6 +202,14 @@ struct ed_multi {
     void *sgn_dev = nullptr;       // [ng] bytes (padded to 16): bit k set iff chi_k(g) = -1
     double build_ms = 0.0;
     int grid_blocks = 0;
+    // stored terms of the shared rows (base->terms); made where they fit
+    struct {
+        uint8_t *row_class = nullptr;   // [dim + 1] class of (sector mask, norm); the last: no sector
+        void *row_table = nullptr;      // [n_row_classes] {mask, sqrt(n), 1/sqrt(n)}
+        void *chi = nullptr;            // [n_elem_classes][K] double2
+        unsigned int *next = nullptr;   // slice counters (nullptr: fixed stride)
+        int n_row_classes = 0, n_elem_classes = 0;
+    } terms;
     // Lanczos workspace, kept between calls
     struct {
         void *vec[3] = {nullptr, nullptr, nullptr};
@@ -216,6 +224,7 @@ namespace ed {
 // Kernel launchers (ed_kernels.hip)
 int launch_basis_build(ed_basis *b, void *stream);
 int multi_lanes_per_row(const ed_multi *mb);
+void multi_free_terms(ed_multi *mb);
 int launch_apply(const ed_basis *b, const double *J, const double *Jz, const void *x, void *y, void *stream, int stats_mode,
                  unsigned long long *stats_dev);
 int launch_apply_timed(const ed_basis *b, const double *J, const double *Jz, const void *x, void *y, int reps,
@@ -231,7 +240,7 @@ int check_couplings(const ed_basis *b, const double *J);
 int scan_counts(const uint32_t *counts, uint64_t *offsets, uint64_t n, void *stream);
 // Stored terms (ed_terms.hip)
 bool terms_wanted(const ed_basis *b);
-int terms_build(ed_basis *b, void *stream);
+int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class = nullptr, int n_elem_class = 0);
 void free_rep_index(ed_basis *b);
 void terms_free(ed_basis *b);
 int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream);

@@ -341,6 +341,174 @@ __global__ void __launch_bounds__((multi_block_bound<KB, SPLIT>()))
 }
 
 // ---------------------------------------------------------------------------
+// Batched H.v from stored terms (ed_terms.hip).  A lane holds one sector of a
+// row: LPR lanes per row, so that one load instruction reads a target's K
+// amplitudes as whole lines, and the words of a row are one address for its
+// lanes.  A term's word names the target row, the bond's orbit and the class
+// of its element (elements with equal characters in every sector); a byte per
+// row names the target's sector mask and norm.  Bound by the lines of the
+// targets' amplitudes (8 sectors: one line of 128 bytes per term, 5.8e8 in
+// 11.8 ms on the 36-site triangular cluster; the searching kernel takes 39.9):
+// as in k_terms_apply, slices come from a counter where the vector exceeds the
+// L2s, and few are in work at a time.
+// ---------------------------------------------------------------------------
+struct RowInfo {
+    uint64_t mask;
+    double sq, rsq;
+};
+
+struct MultiTerms {
+    const uint8_t *row_class;
+    const RowInfo *rows;
+    const double2 *chi;       // [n_elem_classes][K]
+    unsigned int *next;
+    int n_rows, n_elems, n_orb;
+};
+
+template <int LPR>
+__global__ void __launch_bounds__(256)
+    k_multi_terms(TermsDev td, MultiTerms mt, int64_t D, int K, const double2 *__restrict__ x, double2 *y, const double2 *vprev,
+                  const MlzSector *__restrict__ sec, double jsq, int chunks)
+{
+    constexpr int kRows = kWave / LPR;   // rows of a wave
+    constexpr int U = 2;                 // groups of four terms in flight
+    extern __shared__ __align__(16) char lds[];
+    double2 *cls = (double2 *)lds;                     // {J/2, Jz/2} of the classes
+    double2 *chi = cls + td.n_cls;                     // [n_elems][K]
+    RowInfo *rows = (RowInfo *)(chi + mt.n_elems * K);
+    for (int k = threadIdx.x; k < td.n_cls; k += blockDim.x) cls[k] = ((const double2 *)td.cls)[k];
+    for (int k = threadIdx.x; k < mt.n_elems * K; k += blockDim.x) chi[k] = mt.chi[k];
+    for (int k = threadIdx.x; k < mt.n_rows; k += blockDim.x) rows[k] = mt.rows[k];
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int k = min(lane % LPR, K - 1);
+    const bool lane_ok = lane % LPR < K;
+    const uint32_t im = (1u << td.ibits) - 1u;
+    const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
+    const int64_t n_units = (D + kRows - 1) / kRows;   // kRows rows each, LPR to a slice
+    const int64_t per = ((n_units + chunks - 1) / chunks + LPR - 1) / LPR * LPR;
+    const int64_t first = per * (blockIdx.x % chunks);
+    const int64_t last = min(first + per, n_units);
+    const int waves = (int)blockDim.x / kWave;
+    const int64_t step = (int64_t)(gridDim.x / chunks) * waves;
+    unsigned int *ctr = mt.next ? mt.next + kTermsNextStride * (blockIdx.x % chunks) : nullptr;
+    unsigned int mine = ctr && lane == 0 ? atomicAdd(ctr, 1u) : 0u;
+    int64_t unit = ctr ? 0 : first + (int64_t)(blockIdx.x / chunks) * waves + wave;
+    while (true) {
+        if (ctr) unit = first + (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
+        if (unit >= last) return;
+        if (ctr && lane == 0) mine = atomicAdd(ctr, 1u);
+        const int64_t sl = unit / LPR;
+        const int rl = (int)(unit % LPR) * kRows + lane / LPR;   // row of the slice
+        const int64_t i = sl * kWave + rl;
+        const bool ok = i < D;
+        const int groups = (int)td.cnt[sl];
+        const uint4 *p = td.words + (td.off ? td.off[sl] : (uint64_t)sl * td.stride) * kWave + rl;
+        const RowInfo ri = rows[ok ? mt.row_class[i] : mt.n_rows - 1];
+        const bool in = lane_ok && ok && (ri.mask >> k & 1ull);
+        const size_t at = (size_t)(ok ? i : 0) * K + k;
+        double2 xi = x[at], vp = make_double2(0.0, 0.0);
+        double bp = 0.0;
+        if (vprev) {
+            vp = vprev[at];
+            bp = sec[k].beta_prev;
+        }
+        double ar = 0.0, ai = 0.0, anti = 0.0;
+        uint4 w[U], nx[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = u < groups ? load_words(p + (size_t)u * kWave) : make_uint4(none, none, none, none);
+        for (int g = 0; g < groups; g += U) {
+            uint32_t ww[4 * U];
+            double2 v[4 * U];
+            uint32_t rc[4 * U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                ww[4 * u] = w[u].x;
+                ww[4 * u + 1] = w[u].y;
+                ww[4 * u + 2] = w[u].z;
+                ww[4 * u + 3] = w[u].w;
+                nx[u] = g + U + u < groups ? load_words(p + (size_t)(g + U + u) * kWave) : make_uint4(none, none, none, none);
+            }
+#pragma unroll
+            for (int q = 0; q < 4 * U; ++q) {
+                const uint32_t j = ww[q] & im;
+                rc[q] = mt.row_class[j];
+                // padding (row D) reads row 0 and is dropped with its class
+                v[q] = x[(size_t)(j < (uint32_t)D ? j : 0u) * K + k];
+            }
+#pragma unroll
+            for (int q = 0; q < 4 * U; ++q) {
+                const uint32_t cl = ww[q] >> td.ibits;
+                const double2 jj = cls[cl];
+                const RowInfo rj = rows[rc[q]];
+                const double2 ch = chi[min(cl / (uint32_t)mt.n_orb, (uint32_t)mt.n_elems - 1u) * K + k];
+                const bool both = rj.mask >> k & 1ull;   // entries outside the sector count as 0 whatever they hold
+                cmac(ar, ai, jj.x * rj.sq, ch, both ? v[q] : make_double2(0.0, 0.0));
+                anti += jj.y;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) w[u] = nx[u];
+        }
+        if (lane_ok && ok) {
+            double2 out = make_double2(0.0, 0.0);
+            if (in) {
+                const double d = jsq - anti;
+                out.x = fma(ri.rsq, ar, d * xi.x);
+                out.y = fma(ri.rsq, ai, d * xi.y);
+                if (vprev) {
+                    out.x = fma(-bp, vp.x, out.x);
+                    out.y = fma(-bp, vp.y, out.y);
+                }
+            }
+            y[at] = out;
+        }
+        if (!ctr) unit += step;
+    }
+}
+
+// the slice counters before a pass (a captured pass may not clear them with a
+// memset node)
+__global__ void k_multi_reset(unsigned int *next)
+{
+    if (threadIdx.x < 8) next[kTermsNextStride * threadIdx.x] = 0u;
+}
+
+// distinct (sector mask, norm) pairs of the rows: an open-addressing set of
+// 1024 keys, full = more than the caller can use
+constexpr int kRowSet = 1024;
+__device__ __forceinline__ uint64_t row_key(uint64_t e, uint64_t mask) { return (mask | (e >> kNormShift) << 56) + 1ull; }
+
+__global__ void k_row_set(const uint64_t *states, const uint64_t *masks, int64_t D, unsigned long long *set, unsigned int *full)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < D; i += (int64_t)gridDim.x * blockDim.x) {
+        const unsigned long long key = row_key(states[i], masks[i]);
+        uint32_t h = (uint32_t)(key * 0x9e3779b97f4a7c15ull >> 54);
+        int n = 0;
+        for (; n < kRowSet; ++n, h = (h + 1) & (kRowSet - 1)) {
+            unsigned long long cur = set[h];
+            if (cur == 0ull) cur = atomicCAS(&set[h], 0ull, key);
+            if (cur == 0ull || cur == key) break;
+        }
+        if (n == kRowSet) *full = 1u;
+    }
+}
+
+__global__ void k_row_classes(const uint64_t *states, const uint64_t *masks, int64_t D, const unsigned long long *set,
+                              const uint8_t *class_of, uint8_t none, uint8_t *out)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= D; i += (int64_t)gridDim.x * blockDim.x) {
+        if (i == D) {
+            out[i] = none;
+            continue;
+        }
+        const unsigned long long key = row_key(states[i], masks[i]);
+        uint32_t h = (uint32_t)(key * 0x9e3779b97f4a7c15ull >> 54);
+        while (set[h] != key) h = (h + 1) & (kRowSet - 1);
+        out[i] = class_of[h];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Batched Lanczos vector kernels.  Thread t of a block handles sector
 // t % K of rows t / K of each group of R = blockDim / K rows, so it always
 // sees one sector; per-(block, sector) sums are formed in a fixed order.
@@ -639,6 +807,162 @@ static int multi_launch(const ed_multi *mb, const void *x, void *y, const void *
     return set_error(ED_ERR_UNSUPPORTED, "batched sectors need 2- or 4-byte action-table entries");
 }
 
+void multi_free_terms(ed_multi *mb)
+{
+    auto &t = mb->terms;
+    for (void *p : {(void *)t.row_class, t.row_table, t.chi, (void *)t.next})
+        if (p) (void)hipFree(p);
+    t.row_class = nullptr;
+    t.row_table = t.chi = nullptr;
+    t.next = nullptr;
+    if (mb->base) terms_free(mb->base);
+}
+
+static int multi_lpr(const ed_multi *mb)
+{
+    int l = 1;
+    while (l < mb->K) l *= 2;
+    return l;
+}
+
+static size_t multi_terms_lds(const ed_multi *mb)
+{
+    return (size_t)mb->base->terms.n_cls * 16 + (size_t)mb->terms.n_elem_classes * mb->K * 16 +
+           (size_t)mb->terms.n_row_classes * sizeof(RowInfo);
+}
+
+// Stored terms of a batched basis, where single ones would be made, with at
+// most 56 sectors, 255 pairs of mask and norm and 32 KB of characters.
+// Anything else leaves the basis to the searching kernel.
+static int multi_terms_build(ed_multi *mb, hipStream_t st)
+{
+    ed_basis *b = mb->base;
+    const int K = mb->K, ng = b->t.ng;
+    const int64_t D = b->db.dim;
+    auto &t = mb->terms;
+    if (K > 56 || !terms_wanted(b)) return ED_OK;
+    // classes of elements with equal characters in every sector
+    std::vector<uint16_t> cls(ng);
+    std::vector<double> chi;
+    int n_vec = 0;
+    for (int g = 0; g < ng; ++g) {
+        std::vector<double> v(2 * (size_t)K);
+        for (int k = 0; k < K; ++k) {
+            v[2 * k] = mb->chi_host[((size_t)k * ng + g) * 2];
+            v[2 * k + 1] = mb->chi_host[((size_t)k * ng + g) * 2 + 1];
+        }
+        int c = 0;
+        while (c < n_vec && !std::equal(v.begin(), v.end(), chi.begin() + (size_t)c * 2 * K)) ++c;
+        if (c == n_vec) {
+            if ((size_t)(n_vec + 1) * K * 16 > 32768) return ED_OK;
+            chi.insert(chi.end(), v.begin(), v.end());
+            ++n_vec;
+        }
+        cls[g] = (uint16_t)c;
+    }
+    auto give_up = [&]() {
+        (void)hipGetLastError();
+        multi_free_terms(mb);
+        return ED_OK;
+    };
+    auto take = [&](void **p, size_t bytes) {
+        if (hipMalloc(p, bytes) != hipSuccess) {
+            *p = nullptr;
+            return false;
+        }
+        b->terms.bytes += (int64_t)bytes;
+        b->device_bytes += (int64_t)bytes;
+        return true;
+    };
+    // pairs of mask and norm
+    struct Scratch {
+        unsigned long long *set = nullptr;
+        ~Scratch() { if (set) (void)hipFree(set); }
+    } sc;   // the set, a flag, then the classes of its places
+    if (hipMalloc((void **)&sc.set, kRowSet * 8 + 16 + kRowSet) != hipSuccess) return give_up();
+    unsigned int *full = (unsigned int *)(sc.set + kRowSet);
+    uint8_t *class_of = (uint8_t *)(full + 4);
+    HIP_TRY(hipMemsetAsync(sc.set, 0, kRowSet * 8 + 16, st));
+    const unsigned rg = (unsigned)std::min<int64_t>((D + 256) / 256, (int64_t)num_cus() * 16);
+    hipLaunchKernelGGL(k_row_set, dim3(rg), dim3(256), 0, st, b->db.states, (const uint64_t *)mb->masks, D, sc.set, full);
+    HIP_TRY(hipGetLastError());
+    std::vector<unsigned long long> set(kRowSet + 1, 0);
+    HIP_TRY(hipMemcpyAsync(set.data(), sc.set, kRowSet * 8 + 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if ((unsigned int)set[kRowSet]) return ED_OK;
+    std::vector<unsigned long long> keys;
+    for (int h = 0; h < kRowSet; ++h)
+        if (set[h]) keys.push_back(set[h]);
+    std::sort(keys.begin(), keys.end());
+    if (keys.size() > 255) return ED_OK;
+    std::vector<uint8_t> places(kRowSet, 0);
+    std::vector<RowInfo> rows;
+    for (int h = 0; h < kRowSet; ++h)
+        if (set[h]) places[h] = (uint8_t)(std::lower_bound(keys.begin(), keys.end(), set[h]) - keys.begin());
+    for (unsigned long long key : keys) {
+        const uint32_t d = b->divs[(key - 1) >> 56];
+        rows.push_back({(key - 1) & ((1ull << 56) - 1ull), std::sqrt((double)d), 1.0 / std::sqrt((double)d)});
+    }
+    rows.push_back({0ull, 0.0, 0.0});   // no row
+    t.n_row_classes = (int)rows.size();
+    t.n_elem_classes = n_vec;
+    int rc = terms_build(b, st, cls.data(), n_vec);
+    if (rc || !b->terms.words) return rc;
+    const bool counted = (size_t)D * K * 16 > (32u << 20);
+    if (!take((void **)&t.row_class, (size_t)D + 1) || !take(&t.row_table, rows.size() * sizeof(RowInfo)) ||
+        !take(&t.chi, chi.size() * 8) || (counted && !take((void **)&t.next, 8 * kTermsNextStride * 4)))
+        return give_up();
+    HIP_TRY(hipMemcpyAsync(t.row_table, rows.data(), rows.size() * sizeof(RowInfo), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(t.chi, chi.data(), chi.size() * 8, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(class_of, places.data(), kRowSet, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_row_classes, dim3(rg), dim3(256), 0, st, b->db.states, (const uint64_t *)mb->masks, D,
+                       (const unsigned long long *)sc.set, (const uint8_t *)class_of, (uint8_t)(rows.size() - 1), t.row_class);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(st));
+    return ED_OK;
+}
+
+template <int LPR>
+static void launch_multi_terms(const ed_multi *mb, const void *x, void *y, const void *vprev, const void *sec, double jsq,
+                               hipStream_t st)
+{
+    const ed_basis *b = mb->base;
+    const auto &t = mb->terms;
+    const int64_t units = (b->db.dim * LPR + kWave - 1) / kWave, blocks = (units + 3) / 4;
+    int64_t grid = blocks;
+    // with the counter: 4 blocks per compute unit (36-site triangular, 8
+    // sectors: 22.4 ms with 1, 13.8 with 2, 11.8 with 4 and 8); 2 for up to two
+    // sectors, whose lines several rows share (30-site square: 1.28 against
+    // 1.52 ms with 4)
+    const int per_cu = !t.next ? 8 : mb->K <= 2 ? 2 : 4;
+    if (blocks >= 8) grid = std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * per_cu & ~7));
+    const MultiTerms mt{t.row_class, (const RowInfo *)t.row_table, (const double2 *)t.chi, t.next,
+                        t.n_row_classes, t.n_elem_classes, b->terms.n_orb};
+    if (t.next) hipLaunchKernelGGL(k_multi_reset, dim3(1), dim3(64), 0, st, t.next);
+    hipLaunchKernelGGL(k_multi_terms<LPR>, dim3((unsigned)grid), dim3(256), multi_terms_lds(mb), st, terms_dev(b), mt,
+                       b->db.dim, mb->K, (const double2 *)x, (double2 *)y, (const double2 *)vprev, (const MlzSector *)sec, jsq,
+                       grid % 8 == 0 ? 8 : 1);
+}
+
+// the batched H.v (or Lanczos w = H v - beta vprev), by whichever kernel the
+// basis has
+static int multi_hv(const ed_multi *mb, const void *x, void *y, const void *vprev, const void *sec, double jsq, hipStream_t st)
+{
+    if (!mb->terms.row_class || !terms_usable(mb->base)) return multi_launch<0>(mb, x, y, vprev, sec, nullptr, jsq, st);
+    switch (multi_lpr(mb)) {
+    case 1: launch_multi_terms<1>(mb, x, y, vprev, sec, jsq, st); break;
+    case 2: launch_multi_terms<2>(mb, x, y, vprev, sec, jsq, st); break;
+    case 4: launch_multi_terms<4>(mb, x, y, vprev, sec, jsq, st); break;
+    case 8: launch_multi_terms<8>(mb, x, y, vprev, sec, jsq, st); break;
+    case 16: launch_multi_terms<16>(mb, x, y, vprev, sec, jsq, st); break;
+    case 32: launch_multi_terms<32>(mb, x, y, vprev, sec, jsq, st); break;
+    default: launch_multi_terms<64>(mb, x, y, vprev, sec, jsq, st); break;
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "batched H.v launch failed: %s", hipGetErrorString(e));
+    return ED_OK;
+}
+
 template <typename AT>
 static void launch_masks(const ed_multi *mb, const uint64_t *triv, uint64_t all, unsigned long long *counts,
                          hipStream_t st)
@@ -718,7 +1042,7 @@ int multi_setup(ed_multi *mb, void *stream)
     HIP_TRY(hipMemcpyAsync(cnt.data(), d_cnt, (size_t)K * 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     mb->dims.assign(cnt.begin(), cnt.end());
-    return ED_OK;
+    return multi_terms_build(mb, st);
 }
 
 int multi_apply(const ed_multi *mb, const double *J, const void *x, void *y, void *stream)
@@ -731,7 +1055,7 @@ int multi_apply(const ed_multi *mb, const double *J, const void *x, void *y, voi
     rc = upload_couplings(b, J, nullptr, st, &jsq);
     if (rc) return rc;
     if (b->db.dim == 0) return ED_OK;
-    return multi_launch<0>(mb, x, y, nullptr, nullptr, nullptr, jsq, st);
+    return multi_hv(mb, x, y, nullptr, nullptr, jsq, st);
 }
 
 int multi_stats(const ed_multi *mb, int64_t *terms, int64_t *shared_terms, void *stream)
@@ -786,7 +1110,7 @@ static int mlz_step(const ed_multi *mb, double jsq, const double2 *v, double2 *w
     auto &W = mb->lzw;
     MlzSector *sec = (MlzSector *)W.sector;
     MlzState *state = (MlzState *)W.state;
-    int rc = multi_launch<0>(mb, v, w, w, sec, nullptr, jsq, st);
+    int rc = multi_hv(mb, v, w, w, sec, jsq, st);
     if (rc) return rc;
     hipLaunchKernelGGL(k_mlz_dot, dim3(vgrid), dim3(kMlzThreads), 0, st, v, (const double2 *)w, D, K, W.partials);
     hipLaunchKernelGGL(k_mlz_alpha, dim3(1), dim3(kTotThreads), 0, st, (const double *)W.partials, vgrid, K, sec,

@@ -27,37 +27,6 @@ constexpr int kTermsWaves = kTermsThreads / kWave;
 constexpr int kMaxClasses = 1024;
 constexpr int kNextStride = kTermsNextStride;   // a counter per 128-byte line
 
-struct TermsDev {
-    const uint4 *words;
-    const uint64_t *off;
-    const uint32_t *cnt;
-    uint32_t stride;
-    int ibits, n_cls;
-    const double *cls;        // {kr, jz} or {kr, ki, jz, -} of every class
-    const double *cls_chi;    // chi or {re, im} of every class
-};
-
-static TermsDev terms_dev(const ed_basis *b)
-{
-    TermsDev td;
-    td.words = (const uint4 *)b->terms.words;
-    td.off = b->terms.off;
-    td.cnt = b->terms.cnt;
-    td.stride = b->terms.stride;
-    td.ibits = b->terms.ibits;
-    td.n_cls = b->terms.n_cls;
-    td.cls = b->terms.cls;
-    td.cls_chi = b->terms.cls_chi;
-    return td;
-}
-
-__device__ __forceinline__ uint4 load_words(const uint4 *p)
-{
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    // read once per pass: kept out of the way of the amplitudes in L2
-    const u32x4 v = __builtin_nontemporal_load((const u32x4 *)p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
 
 // ---------------------------------------------------------------------------
 // building
@@ -890,8 +859,10 @@ void free_rep_index(ed_basis *b)
 // Builds the table, if the sector can have one: a hash-slot basis with bonds,
 // a word that holds class and row, and a table of at most 1/16 of the device's
 // memory and half of what is free.  Anything else leaves the basis without
-// one, to the searching kernels; only an error of the device is returned.
-int terms_build(ed_basis *b, void *stream)
+// one, to the searching kernels; only an error of the device is returned.  A
+// batched basis gives the classes of its elements (equal characters in every
+// sector), whose coefficients are then the couplings alone.
+int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_elem_class)
 {
     hipStream_t st = (hipStream_t)stream;
     auto &t = b->terms;
@@ -901,7 +872,12 @@ int terms_build(ed_basis *b, void *stream)
     // distinct characters (fermions: and their negatives, for the sign)
     std::vector<uint16_t> cls((size_t)ng * 2);
     t.chi_vals.clear();
-    for (int sgn = 0; sgn < (b->fermion ? 2 : 1); ++sgn)
+    for (int k = 0; elem_class && k < n_elem_class; ++k) {
+        t.chi_vals.push_back(1.0);
+        t.chi_vals.push_back(0.0);
+    }
+    if (elem_class) std::copy(elem_class, elem_class + ng, cls.begin());
+    for (int sgn = 0; !elem_class && sgn < (b->fermion ? 2 : 1); ++sgn)
         for (int g = 0; g < ng; ++g) {
             const double re = sgn ? -b->chi_host[2 * g] : b->chi_host[2 * g];
             const double im = b->dm.is_complex ? (sgn ? -b->chi_host[2 * g + 1] : b->chi_host[2 * g + 1]) : 0.0;
@@ -973,10 +949,10 @@ int terms_build(ed_basis *b, void *stream)
     const size_t bytes = std::max<size_t>(groups, 1) * kGroupBytes;
     if (bytes + vec > std::min(total_b / 16, free_b / 2)) return give_up();
     // the scaled input exceeds the L2s (8 x 4 MB): slices from a counter
-    const bool counted = vec > (32u << 20);
+    const bool counted = vec > (32u << 20) && !elem_class;
     const size_t clsb = (size_t)t.n_cls * (b->dm.is_complex ? 32 : 16);
     void *d_cls = nullptr;   // chi classes and bond orbits, needed by the search only
-    if (!take(&t.words, bytes) || !take((void **)&t.xs, vec) || !take((void **)&t.cls, clsb) ||
+    if (!take(&t.words, bytes) || (!elem_class && !take((void **)&t.xs, vec)) || !take((void **)&t.cls, clsb) ||
         !take((void **)&t.cls_chi, clsb / 2) ||
         (counted && (!take((void **)&t.next, 8 * kNextStride * 4) || !take((void **)&t.dots, (size_t)slices * 8))) || hipMalloc(&d_cls, (cls.size() + orb.size()) * 2) != hipSuccess)
         return give_up();
@@ -993,7 +969,8 @@ int terms_build(ed_basis *b, void *stream)
     cls.insert(cls.end(), orb.begin(), orb.end());
     hipError_t e = hipMemcpyAsync(d_cls, cls.data(), cls.size() * 2, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(t.cls_chi, chi.data(), chi.size() * 8, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemsetAsync((char *)t.xs + vec - (b->dm.is_complex ? 16 : 8), 0, b->dm.is_complex ? 16 : 8, st);
+    if (e == hipSuccess && t.xs)
+        e = hipMemsetAsync((char *)t.xs + vec - (b->dm.is_complex ? 16 : 8), 0, b->dm.is_complex ? 16 : 8, st);
     int rc = ED_OK;
     if (e == hipSuccess) {
         const uint32_t pad = (uint32_t)(t.n_cls - 1) << t.ibits | (uint32_t)D;

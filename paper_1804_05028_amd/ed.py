@@ -220,6 +220,11 @@ class MultiBasis:
     def info(self):
         return L.ed_multi_info(self.handle)
 
+    def release_terms(self):
+        """Give back the device memory of the stored terms; H.v and Lanczos
+        then search each term again, with the same results up to rounding."""
+        L.ed_multi_release_terms(self.handle)
+
     def sector_dims(self):
         return L.ed_multi_sector_dims(self.handle, self.K)
 

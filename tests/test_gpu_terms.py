@@ -203,3 +203,58 @@ def test_captured_call_replays():
             got = y.clone()
             assert torch.equal(got, b.apply(w.J, v))
         b.close()
+
+
+def _multi_cases():
+    from tests.test_gpu_batched import CASES as B
+    from tests.test_gpu_batched_lanes import BENCH_INSTANCES
+    out = [(n, ws, None) for n, ws in B]
+    for n, make, tune, *_ in BENCH_INSTANCES:
+        out += [(f"{n}_{lanes}", make(), dict(tune, table_entry_bytes=2, search_mode=2, lanes_per_row=lanes)) for lanes in (1, 2, 4)]
+    c = lat.square((6, 0), (0, 4), rotations=False, superlattice=wl.SQ_2X2)
+    J = np.linspace(0.7, 1.3, lat.bond_orbits(c).max() + 1)[lat.bond_orbits(c)]
+    for K in (1, 2, 3, 5, 17, 24):   # every number of lanes per row up to 32, full and not
+        out.append((f"square24_K{K}", [wl.Workload("sq24", c, lat.characters(c, k), 10, J) for k in range(K)], None))
+    c = lat.chain(36, superlattice_period=9)   # 64 lanes per row
+    out.append(("chain36_K33", [wl.Workload("c36", c, lat.characters(c, k), 3, np.ones(36)) for k in range(33)], None))
+    return out
+
+
+MULTI = _multi_cases()
+
+
+@pytest.mark.parametrize("name,ws,tune", MULTI, ids=[m[0] for m in MULTI])
+def test_batched_stored_terms_equal_search(name, ws, tune):
+    """Batched H.v and Lanczos from stored terms against the searching kernel
+    on the same basis, with values that are not finite outside the sectors.
+    Both round each term a few times: a few times the terms' eps, below 1e-13
+    of the norm."""
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    mb = ed.MultiBasis.from_workloads(ws, tune)
+    try:
+        print(f"[terms] {name}: D={mb.dim} K={mb.K}", flush=True)
+        assert L.ed_multi_terms_bytes(mb.handle) > 0
+        rng = np.random.default_rng(5)
+        x = rng.standard_normal((mb.dim, mb.K)) + 1j * rng.standard_normal((mb.dim, mb.K))
+        out = ((mb.masks()[:, None] >> np.arange(mb.K, dtype=np.uint64)) & np.uint64(1)) == 0
+        x[out] = np.nan
+        x = torch.as_tensor(x).cuda()
+        v0 = torch.where(torch.isnan(x.real), torch.zeros_like(x), x)
+        y, r = mb.apply(ws[0].J, x), mb.lanczos(ws[0].J, v0, 4)
+        again = mb.apply(ws[0].J, x)
+        eager = mb.lanczos(ws[0].J, v0, 4, use_graph=False)
+        assert torch.equal(y, again)
+        assert np.array_equal(r["alpha"], eager["alpha"]) and np.array_equal(r["beta"], eager["beta"])
+        mb.release_terms()
+        assert L.ed_multi_terms_bytes(mb.handle) == 0
+        z, s = mb.apply(ws[0].J, x), mb.lanczos(ws[0].J, v0, 4)
+        assert not torch.isnan(y.real).any() and (y[torch.as_tensor(out).cuda()] == 0).all()
+        assert torch.linalg.vector_norm(y - z) <= 1e-13 * torch.linalg.vector_norm(z)
+        assert np.array_equal(r["n_done"], s["n_done"])
+        for k in range(mb.K):
+            n = int(r["n_done"][k])
+            if np.all(s["beta"][k, :max(n - 1, 0)] > 1e-6):   # no breakdown on the way
+                assert np.abs(r["alpha"][k, :n] - s["alpha"][k, :n]).max(initial=0.0) <= 1e-11
+    finally:
+        mb.close()
