@@ -119,8 +119,8 @@ typedef struct {
                                characters all +-1, staged as sign bits): then 0 = 1 lane for K <= 8,
                                and the count is raised to at least 2 for K > 8 and 4 for K > 16;
                                K > 32 always runs 4 lanes (ed_multi_info reports the count used)  */
-    int32_t lanczos_direct; /* ed_lanczos: 1 = launch each step's kernels directly; 0 = capture the
-                               step once per buffer assignment in a HIP graph and replay it        */
+    int32_t lanczos_direct; /* 0 or 1; ed_lanczos launches each step's two kernels directly either way
+                               (replaying them from a HIP graph measured no faster)                */
 } ed_tuning_t;
 
 #define ED_SEARCH_ONE_STAGE 1

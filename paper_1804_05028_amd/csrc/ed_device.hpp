@@ -568,14 +568,29 @@ struct Scalar<true> {
     using T = double2;
 };
 
-// Lanczos state at the start of a step.  Two copies alternate: a step's
-// kernels read one, and its last kernel writes the other for the next step,
-// so that no block reads what another block of its kernel writes.
+// Lanczos state of a step.  Two copies alternate: the H.v kernel of a step
+// reads the one that the step before wrote and writes the other (lz_begin), so
+// that no block reads what another block of its kernel writes.  Vectors are
+// kept as they come out of the recurrence, v_j = inv * (stored vector): the
+// division by beta needs no pass of its own.
 struct LzState {
-    int j;              // step index
-    int done;           // breakdown or finished
+    int j;              // step index (-1 before the first)
+    int done;           // breakdown or finished; j is then the number of steps
     double scale;       // running max(|alpha_k|, beta_k)
-    double beta_prev;
+    double beta_prev;   // beta_{j-1}
+    double inv, inv_prev;
+};
+
+// where a step's H.v finds the state, the |w|^2 partials of the step before
+// (first step: of the start vector), and the histories
+struct LzStep {
+    const LzState *cur;
+    LzState *next;
+    const double *norms;
+    int n_norms, n_steps;
+    const double *alpha;
+    double *beta;
+    double tol;
 };
 
 // One off-diagonal term, the same in every kernel that sums them (stored
@@ -705,6 +720,34 @@ __device__ __forceinline__ double total_of(const double *partials, int n, double
     if (threadIdx.x == 0) *res = t;
     __syncthreads();
     return *res;
+}
+
+// First thing of a step's H.v, by every thread of every block: beta of the
+// step before from its |w|^2 partials and with it this step's state, which
+// block 0 writes.  False: nothing left to do.
+__device__ __forceinline__ bool lz_begin(const LzStep &lz, double *sh, LzState &s)
+{
+    s = *lz.cur;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (!s.done) {
+        const double t = total_of(lz.norms, lz.n_norms, sh);
+        const double b = sqrt(t);
+        if (s.j < 0) {
+            s.beta_prev = 0.0;
+            s.inv_prev = 0.0;
+            s.inv = t > 0.0 ? 1.0 / b : 0.0;
+        } else {
+            s.scale = fmax(s.scale, fmax(fabs(lz.alpha[s.j]), b));
+            s.done = b <= lz.tol * s.scale || s.j + 1 >= lz.n_steps;
+            if (first) lz.beta[s.j] = b;
+            s.beta_prev = b;
+            s.inv_prev = s.inv;
+            s.inv = 1.0 / b;
+        }
+        s.j += 1;
+    }
+    if (first) *lz.next = s;
+    return !s.done;
 }
 
 // ---------------------------------------------------------------------------

@@ -178,8 +178,7 @@ struct ed_basis {
     // Lanczos workspace, kept between calls and freed with the handle
     struct {
         double *vec[3] = {nullptr, nullptr, nullptr};
-        double *partials = nullptr, *ahist = nullptr, *bhist = nullptr, *svec = nullptr;
-        void *state = nullptr;
+        double *partials = nullptr, *hist = nullptr;
         int cap_steps = 0;
         size_t cap_partials = 0;
     } lzw;
@@ -252,6 +251,8 @@ constexpr int kTermsNextStride = 32;
 int terms_apply(const ed_basis *b, const void *x, void *y, double jsq, void *stream);
 int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *vprev, double *partials, const void *lz,
                         double jsq, void *stream);
+int terms_lanczos_small(const ed_basis *b, const void *v0, int n_steps, double tol, double *alpha, double *beta, void *state,
+                        void *psi0, const double *svec, double jsq, void *stream);
 int sum_partials_cols(const double *partials, int nrows, int ncols, double *out, void *stream);
 int terms_backward(const ed_basis *b, const void *x, const void *gy, void *gx, double *gJ_host, double *scratch,
                    size_t scratch_doubles, double jsq, void *stream);

@@ -231,9 +231,10 @@ __device__ __forceinline__ void add_part(const TermsLds<CPLX> &tl, const uint4 (
 // y_i from the finished sums; returns Re(conj(x_i) y_i) in MODE 2
 template <bool CPLX, int MODE, bool FERMI>
 __device__ __forceinline__ double finish_row(const TermsLds<CPLX> &tl, int nb, uint64_t e, double ar, double ai, double anti,
-                                             typename Scalar<CPLX>::T xi, typename Scalar<CPLX>::T vp, double beta_prev,
+                                             typename Scalar<CPLX>::T xi, typename Scalar<CPLX>::T vp, const LzState &lz,
                                              double jsq, typename Scalar<CPLX>::T *y)
 {
+    const double beta_prev = lz.beta_prev, inv = lz.inv, inv_prev = lz.inv_prev;
     double d;
     if (FERMI) {
         const uint64_t s = e & kStateMask;
@@ -249,17 +250,27 @@ __device__ __forceinline__ double finish_row(const TermsLds<CPLX> &tl, int nb, u
     double dot = 0.0;
     typename Scalar<CPLX>::T out;
     if constexpr (CPLX) {
+        if (MODE == 2) {
+            xi.x *= inv;
+            xi.y *= inv;
+            ar *= inv;
+            ai *= inv;
+        }
         out.x = fma(rs, ar, d * xi.x);
         out.y = fma(rs, ai, d * xi.y);
         if (MODE == 2) {
-            out.x = fma(-beta_prev, vp.x, out.x);
-            out.y = fma(-beta_prev, vp.y, out.y);
+            out.x = fma(-beta_prev, inv_prev * vp.x, out.x);
+            out.y = fma(-beta_prev, inv_prev * vp.y, out.y);
             dot = fma(xi.x, out.x, xi.y * out.y);
         }
     } else {
+        if (MODE == 2) {
+            xi *= inv;
+            ar *= inv;
+        }
         out = fma(rs, ar, d * xi);
         if (MODE == 2) {
-            out = fma(-beta_prev, vp, out);
+            out = fma(-beta_prev, inv_prev * vp, out);
             dot = xi * out;
         }
     }
@@ -267,11 +278,11 @@ __device__ __forceinline__ double finish_row(const TermsLds<CPLX> &tl, int nb, u
     return dot;
 }
 
-template <bool CPLX, int MODE, bool FERMI, typename XS>
+template <bool CPLX, int MODE, bool FERMI, int U, typename XS>
 __device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const TermsDev &td, int nb, int64_t slice, int lane,
                                             const uint64_t *states, int64_t D, XS xs,
                                             const typename Scalar<CPLX>::T *x, typename Scalar<CPLX>::T *y,
-                                            const typename Scalar<CPLX>::T *vprev, double beta_prev, double jsq)
+                                            const typename Scalar<CPLX>::T *vprev, const LzState &lz, double jsq)
 {
     using T = typename Scalar<CPLX>::T;
     const int64_t i = slice * kWave + lane;
@@ -287,7 +298,6 @@ __device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const Term
     double ar = 0.0, ai = 0.0, anti = 0.0;
     // the words of the next groups are read while these are gathered
     const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
-    constexpr int U = 4;
     uint4 w[U], nx[U];
     load_part<U>(w, p, 0, groups, none);
     for (int g = 0; g < groups; g += U) {
@@ -296,7 +306,7 @@ __device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const Term
 #pragma unroll
         for (int u = 0; u < U; ++u) w[u] = nx[u];
     }
-    return ok ? finish_row<CPLX, MODE, FERMI>(tl, nb, e, ar, ai, anti, xi, vp, beta_prev, jsq, y + i) : 0.0;
+    return ok ? finish_row<CPLX, MODE, FERMI>(tl, nb, e, ar, ai, anti, xi, vp, lz, jsq, y + i) : 0.0;
 }
 
 // H.v from the stored terms: a coalesced read of the words and a gather of
@@ -312,23 +322,26 @@ __device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const Term
 //
 // Lines are shared only while they stay in L2, so few rows should be in work
 // at a time, and these should be neighbours.  Where the input exceeds the L2s,
-// one block per compute unit runs (four waves with 16 gathers of each lane in
-// flight) and a wave takes the next slice of its XCD's range from a counter:
+// one block per compute unit runs (four waves with 32 gathers of each lane in
+// flight; 2, 3, 5, 6 or 8 waves and 8 to 20 gathers were slower on one cluster
+// or the other) and a wave takes the next slice of its XCD's range from a counter:
 // with a fixed stride the waves drift apart and so do their rows.  32-site
 // square 4.68 ms with eight blocks and a fixed stride, 3.91 with one, 3.05
 // with the counter; 36-site triangular 5.20, 4.47, 3.46 ms.  The 1.4e6 rows of
 // the 28-site square (11 MB) gain nothing: 157, 171, 179 us.
-template <bool CPLX, int MODE, bool FERMI>
+template <bool CPLX, int MODE, bool FERMI, bool COUNTED>
 __global__ void __launch_bounds__(kTermsThreads)
     k_terms_apply(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int64_t D,
                   const typename Scalar<CPLX>::T *__restrict__ xs, const typename Scalar<CPLX>::T *__restrict__ x,
                   typename Scalar<CPLX>::T *__restrict__ y, const typename Scalar<CPLX>::T *__restrict__ vprev,
-                  double *partials, const LzState *lz, double jsq, int chunks, unsigned int *next)
+                  double *partials, LzStep step_of, double jsq, int chunks, unsigned int *next)
 {
     using T = typename Scalar<CPLX>::T;
     extern __shared__ __align__(16) double lds_d[];
-    if (MODE == 2 && lz->done) return;
-    const double beta_prev = MODE == 2 ? lz->beta_prev : 0.0;
+    constexpr int U = COUNTED ? 8 : 4;   // groups in flight
+    __shared__ double sh[kTermsWaves + 1];
+    LzState lz{};
+    if (MODE == 2 && !lz_begin(step_of, sh, lz)) return;
     const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int64_t n_slices = (D + kWave - 1) / kWave;
@@ -337,7 +350,7 @@ __global__ void __launch_bounds__(kTermsThreads)
     const int64_t last = min(first + per, n_slices);
     const int64_t step = (int64_t)(gridDim.x / chunks) * kTermsWaves;
     auto gather = [&](uint32_t j) { return *(const T *)((const char *)xs + (uint32_t)(j * (uint32_t)sizeof(T))); };
-    if (next) {
+    if constexpr (COUNTED) {
         // the counter's last value is taken by every wave of the range in turn
         // beyond its end; k_pack and k_lz_next set it back to 0
         unsigned int *ctr = next + kNextStride * (blockIdx.x % chunks);
@@ -346,7 +359,7 @@ __global__ void __launch_bounds__(kTermsThreads)
             const int64_t sl = first + (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
             if (sl >= last) return;
             mine = lane == 0 ? atomicAdd(ctr, 1u) : 0u;   // the one after, asked for early
-            const double t = terms_row<CPLX, MODE, FERMI>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, beta_prev, jsq);
+            const double t = terms_row<CPLX, MODE, FERMI, U>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, lz, jsq);
             // which wave takes a slice varies from run to run: one sum per slice
             if (MODE == 2) {
                 const double ws = wave_sum(t);
@@ -355,10 +368,9 @@ __global__ void __launch_bounds__(kTermsThreads)
         }
     }
     double dot = 0.0;
-    for (int64_t sl = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave; sl < last; sl += step)
-        dot += terms_row<CPLX, MODE, FERMI>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, beta_prev, jsq);
+    for (int64_t sl = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave; !COUNTED && sl < last; sl += step)
+        dot += terms_row<CPLX, MODE, FERMI, U>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, lz, jsq);
     if (MODE == 2) {
-        __shared__ double sh[kTermsWaves];
         const double t = block_sum(dot, sh);
         if (threadIdx.x == 0) partials[blockIdx.x] = t;
     }
@@ -406,7 +418,7 @@ __global__ void __launch_bounds__(kTermsThreads)
     const int64_t n_slices = (D + kWave - 1) / kWave;
     auto gather = [&](uint32_t j) { return xs[j]; };
     for (int64_t sl = (int64_t)blockIdx.x * kTermsWaves + wave; sl < n_slices; sl += (int64_t)gridDim.x * kTermsWaves)
-        terms_row<CPLX, 0, FERMI>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, nullptr, 0.0, jsq);
+        terms_row<CPLX, 0, FERMI, 4>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, nullptr, LzState{}, jsq);
 }
 
 // blocks of a pass over all slices: a multiple of 8 (see chunks) where there
@@ -437,13 +449,17 @@ static int launch_terms(const ed_basis *b, const void *x, void *y, const void *v
                            dim3(kTermsThreads), xb + lds, st, b->dm, terms_dev(b), b->db.states, b->db.dim, (const T *)x,
                            (T *)y, jsq);
     } else {
-        hipLaunchKernelGGL((k_terms_apply<CPLX, MODE, FERMI>), dim3(terms_grid(b)), dim3(kTermsThreads), lds, st, b->dm,
-                           terms_dev(b), b->db.states, b->db.dim, (const T *)b->terms.xs, (const T *)x, (T *)y,
-                           (const T *)vprev, b->terms.next ? b->terms.dots : partials, (const LzState *)lz, jsq,
-                           terms_chunks(b), b->terms.next);
+        const LzStep ls = lz ? *(const LzStep *)lz : LzStep{};
+#define ED_TERMS(COUNTED) \
+    hipLaunchKernelGGL((k_terms_apply<CPLX, MODE, FERMI, COUNTED>), dim3(terms_grid(b)), dim3(kTermsThreads), lds, st, b->dm, \
+                       terms_dev(b), b->db.states, b->db.dim, (const T *)b->terms.xs, (const T *)x, (T *)y, \
+                       (const T *)vprev, COUNTED ? b->terms.dots : partials, ls, jsq, terms_chunks(b), b->terms.next)
+        if (b->terms.next) ED_TERMS(true);
+        else ED_TERMS(false);
+#undef ED_TERMS
         if (MODE == 2 && b->terms.next)
             hipLaunchKernelGGL(k_terms_dots, dim3(kDotBlocks), dim3(kTermsThreads), 0, st, (const double *)b->terms.dots,
-                               (b->db.dim + kWave - 1) / kWave, partials, (const LzState *)lz);
+                               (b->db.dim + kWave - 1) / kWave, partials, (const LzState *)((const LzStep *)lz)->next);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "H.v launch failed: %s", hipGetErrorString(e));
@@ -472,6 +488,170 @@ int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *v
                         double jsq, void *stream)
 {
     return terms_dispatch<2>(b, v, w, vprev, partials, lz, jsq, stream);
+}
+
+// ---------------------------------------------------------------------------
+// Lanczos of a sector whose scaled vector fits LDS (terms_small): one block
+// does the whole iteration, its vectors in registers, two block sums per step
+// in place of kernels.  A step is bound by the latency of reading the words
+// from L2 through one compute unit and by the block sums: 1321 rows 7 us,
+// against 31 us with two kernels of a step replayed or launched.
+// ---------------------------------------------------------------------------
+constexpr int kSmallThreads = 1024;
+template <bool CPLX, bool FERMI>
+__global__ void __launch_bounds__(kSmallThreads)
+    k_terms_lanczos_small(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int D,
+                          const typename Scalar<CPLX>::T *__restrict__ v0, int n_steps, double tol, double *alpha, double *beta,
+                          LzState *state, typename Scalar<CPLX>::T *psi0, const double *svec, double jsq)
+{
+    using T = typename Scalar<CPLX>::T;
+    constexpr int R = CPLX ? 2 : 4;   // rows of a thread (terms_small)
+    constexpr int U = 3;
+    extern __shared__ __align__(16) double lds_d[];
+    __shared__ double sh[kSmallThreads / kWave + 1];
+    T *xs = (T *)lds_d;
+    const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d + ((((size_t)D + 1) * (CPLX ? 2 : 1) + 1) & ~(size_t)1));
+    const double *sqrts = (const double *)(dm.blob + dm.off_div);
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
+    auto gather = [&](uint32_t j) { return xs[j]; };
+    auto total = [&](double a) {
+        const double t = block_sum(a, sh);
+        if (threadIdx.x == 0) sh[kSmallThreads / kWave] = t;
+        __syncthreads();
+        return sh[kSmallThreads / kWave];
+    };
+    auto times = [](T v, double f) {
+        if constexpr (CPLX)
+            return make_double2(v.x * f, v.y * f);
+        else
+            return v * f;
+    };
+    auto norm2 = [](T v) {
+        if constexpr (CPLX)
+            return v.x * v.x + v.y * v.y;
+        else
+            return v * v;
+    };
+    T v[R], prev[R], psi[R];
+    uint64_t e[R];
+    double sq[R], acc = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = threadIdx.x + r * kSmallThreads;
+        v[r] = prev[r] = psi[r] = T{};
+        e[r] = 0;
+        sq[r] = 0.0;
+        if (i < D) {
+            e[r] = states[i];
+            sq[r] = sqrts[e[r] >> kNormShift];
+            v[r] = v0[i];
+        }
+        acc += norm2(v[r]);
+    }
+    const double n2 = total(acc);
+    LzState st{};
+    st.inv = st.inv_prev = 1.0;   // v and prev are kept normalised
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = times(v[r], n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0);
+    if (threadIdx.x == 0) xs[D] = T{};
+    while (!st.done) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = threadIdx.x + r * kSmallThreads;
+            if (i < D) xs[i] = times(v[r], sq[r]);
+        }
+        __syncthreads();
+        T w[R];
+        double dot = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[r] = T{};
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = threadIdx.x + r * kSmallThreads;
+            if (i - lane >= D) break;   // uniform: the wave's slice
+            const int64_t sl = i / kWave;
+            const int groups = (int)td.cnt[sl];
+            const uint4 *p = td.words + (td.off ? td.off[sl] : (uint64_t)sl * td.stride) * kWave + lane;
+            double ar = 0.0, ai = 0.0, anti = 0.0;
+            uint4 q[U], nx[U];
+            load_part<U>(q, p, 0, groups, none);
+            for (int g = 0; g < groups; g += U) {
+                load_part<U>(nx, p, g + U, groups, none);
+                add_part<CPLX, U>(tl, q, g, groups, td.ibits, gather, ar, ai, anti);
+#pragma unroll
+                for (int u = 0; u < U; ++u) q[u] = nx[u];
+            }
+            if (i < D) dot += finish_row<CPLX, 2, FERMI>(tl, dm.nb, e[r], ar, ai, anti, v[r], prev[r], st, jsq, &w[r]);
+        }
+        const double a = total(dot);
+        const double sj = psi0 ? svec[st.j] : 0.0;
+        acc = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (CPLX) {
+                w[r].x -= a * v[r].x;
+                w[r].y -= a * v[r].y;
+                psi[r].x += sj * v[r].x;
+                psi[r].y += sj * v[r].y;
+            } else {
+                w[r] -= a * v[r];
+                psi[r] += sj * v[r];
+            }
+            acc += norm2(w[r]);
+        }
+        const double b = sqrt(total(acc));
+        if (threadIdx.x == 0) {
+            alpha[st.j] = a;
+            beta[st.j] = b;
+        }
+        st.scale = fmax(st.scale, fmax(fabs(a), b));
+        st.j += 1;
+        st.done = b <= tol * st.scale || st.j >= n_steps;
+        st.beta_prev = b;
+        const double inv = st.done ? 0.0 : 1.0 / b;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            prev[r] = v[r];
+            v[r] = times(w[r], inv);
+        }
+    }
+    if (threadIdx.x < 2) state[threadIdx.x] = st;
+    if (psi0) {
+        acc = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc += norm2(psi[r]);
+        const double t = total(acc);
+        const double f = t > 0.0 ? 1.0 / sqrt(t) : 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = threadIdx.x + r * kSmallThreads;
+            if (i < D) psi0[i] = times(psi[r], f);
+        }
+    }
+}
+
+// the whole iteration (with psi0: its second pass) in one launch
+int terms_lanczos_small(const ed_basis *b, const void *v0, int n_steps, double tol, double *alpha, double *beta, void *state,
+                        void *psi0, const double *svec, double jsq, void *stream)
+{
+    const bool c = b->dm.is_complex;
+    const size_t lds = ((((size_t)b->db.dim + 1) * (c ? 16 : 8) + 15) & ~(size_t)15) + terms_lds_bytes(b);
+#define ED_SMALL(C, F) \
+    hipLaunchKernelGGL((k_terms_lanczos_small<C, F>), dim3(1), dim3(kSmallThreads), lds, (hipStream_t)stream, b->dm, \
+                       terms_dev(b), b->db.states, (int)b->db.dim, (const Scalar<C>::T *)v0, n_steps, tol, alpha, beta, \
+                       (LzState *)state, (Scalar<C>::T *)psi0, svec, jsq)
+    if (c) {
+        if (b->fermion) ED_SMALL(true, true);
+        else ED_SMALL(true, false);
+    } else {
+        if (b->fermion) ED_SMALL(false, true);
+        else ED_SMALL(false, false);
+    }
+#undef ED_SMALL
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "Lanczos launch failed: %s", hipGetErrorString(e));
+    return ED_OK;
 }
 
 // ---------------------------------------------------------------------------
