@@ -714,7 +714,17 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
 __device__ __forceinline__ double total_of(const double *partials, int n, double *sh)
 {
     double a = 0.0;
-    for (int k = threadIdx.x; k < n; k += blockDim.x) a += partials[k];
+    // eight reads at a time: they are one latency, not eight
+    for (int k0 = threadIdx.x; k0 < n; k0 += 8 * blockDim.x) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int k = k0 + u * (int)blockDim.x;
+            v[u] = k < n ? partials[k] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a += v[u];
+    }
     const double t = block_sum(a, sh);
     double *res = sh + blockDim.x / kWave;
     if (threadIdx.x == 0) *res = t;

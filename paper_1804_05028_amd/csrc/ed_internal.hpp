@@ -165,6 +165,7 @@ struct ed_basis {
         uint32_t stride = 0;
         double *xs = nullptr;          // [dim + 1] scaled input, its last entry 0
         double *pair = nullptr;        // [dim + 1] {x, gy} scaled, made by the first fused adjoint
+        double *adj = nullptr;         // per-bond partial sums, made by the first adjoint
         unsigned int *next = nullptr;  // slice counters of the 8 row ranges (nullptr: fixed stride)
         double *dots = nullptr;        // [n_slices] <v, w> of a Lanczos step, with the counters
         double *cls = nullptr;         // [n_cls] coefficients of the current couplings

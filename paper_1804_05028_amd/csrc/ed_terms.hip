@@ -20,6 +20,9 @@
 // give the same bits.
 #include "ed_device.hpp"
 
+#include <type_traits>
+#include <utility>
+
 namespace ed {
 
 constexpr int kTermsThreads = 256;
@@ -278,35 +281,50 @@ __device__ __forceinline__ double finish_row(const TermsLds<CPLX> &tl, int nb, u
     return dot;
 }
 
-template <bool CPLX, int MODE, bool FERMI, int U, typename XS>
-__device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const TermsDev &td, int nb, int64_t slice, int lane,
-                                            const uint64_t *states, int64_t D, XS xs,
-                                            const typename Scalar<CPLX>::T *x, typename Scalar<CPLX>::T *y,
-                                            const typename Scalar<CPLX>::T *vprev, const LzState &lz, double jsq)
-{
+// a slice's first words and its lane's row, requested together
+template <bool CPLX, int MODE, int U>
+struct TermsSlice {
     using T = typename Scalar<CPLX>::T;
-    const int64_t i = slice * kWave + lane;
-    const bool ok = i < D;
-    const int groups = (int)td.cnt[slice];
-    const uint4 *p = td.words + ((td.off ? td.off[slice] : (uint64_t)slice * td.stride) * kWave + lane);
-    const uint64_t e = ok ? states[i] : 0ull;
-    T xi{}, vp{};
-    if (ok) {
-        xi = x[i];
-        if (MODE == 2) vp = vprev[i];
+    int64_t i;
+    int groups;
+    bool ok;
+    const uint4 *p;
+    uint4 w[U];
+    uint64_t e;
+    T xi, vp;
+    __device__ __forceinline__ void request(const TermsDev &td, uint32_t none, int64_t slice, int lane, const uint64_t *states,
+                                            int64_t D, const T *x, const T *vprev)
+    {
+        i = slice * kWave + lane;
+        ok = i < D;
+        groups = (int)td.cnt[slice];
+        p = td.words + (td.off ? td.off[slice] : (uint64_t)slice * td.stride) * kWave + lane;
+        load_part<U>(w, p, 0, groups, none);
+        e = ok ? states[i] : 0ull;
+        xi = T{};
+        vp = T{};
+        if (ok) {
+            xi = x[i];
+            if (MODE == 2) vp = vprev[i];
+        }
     }
+};
+
+template <bool CPLX, int MODE, bool FERMI, int U, typename XS>
+__device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const TermsDev &td, uint32_t none, int nb,
+                                            TermsSlice<CPLX, MODE, U> &sl, XS xs, typename Scalar<CPLX>::T *y, const LzState &lz,
+                                            double jsq)
+{
     double ar = 0.0, ai = 0.0, anti = 0.0;
     // the words of the next groups are read while these are gathered
-    const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
-    uint4 w[U], nx[U];
-    load_part<U>(w, p, 0, groups, none);
-    for (int g = 0; g < groups; g += U) {
-        load_part<U>(nx, p, g + U, groups, none);
-        add_part<CPLX, U>(tl, w, g, groups, td.ibits, xs, ar, ai, anti);
+    uint4 nx[U];
+    for (int g = 0; g < sl.groups; g += U) {
+        load_part<U>(nx, sl.p, g + U, sl.groups, none);
+        add_part<CPLX, U>(tl, sl.w, g, sl.groups, td.ibits, xs, ar, ai, anti);
 #pragma unroll
-        for (int u = 0; u < U; ++u) w[u] = nx[u];
+        for (int u = 0; u < U; ++u) sl.w[u] = nx[u];
     }
-    return ok ? finish_row<CPLX, MODE, FERMI>(tl, nb, e, ar, ai, anti, xi, vp, lz, jsq, y + i) : 0.0;
+    return sl.ok ? finish_row<CPLX, MODE, FERMI>(tl, nb, sl.e, ar, ai, anti, sl.xi, sl.vp, lz, jsq, y + sl.i) : 0.0;
 }
 
 // H.v from the stored terms: a coalesced read of the words and a gather of
@@ -338,38 +356,48 @@ __global__ void __launch_bounds__(kTermsThreads)
 {
     using T = typename Scalar<CPLX>::T;
     extern __shared__ __align__(16) double lds_d[];
-    constexpr int U = COUNTED ? 8 : 4;   // groups in flight
+    constexpr int U = 8;   // groups in flight
     __shared__ double sh[kTermsWaves + 1];
-    LzState lz{};
-    if (MODE == 2 && !lz_begin(step_of, sh, lz)) return;
-    const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
     const int64_t n_slices = (D + kWave - 1) / kWave;
     const int64_t per = (n_slices + chunks - 1) / chunks;
     const int64_t first = per * (blockIdx.x % chunks);
     const int64_t last = min(first + per, n_slices);
     const int64_t step = (int64_t)(gridDim.x / chunks) * kTermsWaves;
     auto gather = [&](uint32_t j) { return *(const T *)((const char *)xs + (uint32_t)(j * (uint32_t)sizeof(T))); };
+    TermsSlice<CPLX, MODE, U> sl;
+    int64_t k = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave;
+    // the first slice is on its way while the tables are staged: a short sector
+    // is all latency
+    if (!COUNTED && k < last) sl.request(td, none, k, lane, states, D, x, vprev);
+    LzState lz{};
+    if (MODE == 2 && !lz_begin(step_of, sh, lz)) return;
+    const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d);
     if constexpr (COUNTED) {
         // the counter's last value is taken by every wave of the range in turn
-        // beyond its end; k_pack and k_lz_next set it back to 0
+        // beyond its end; k_pack and k_lz_update set it back to 0
         unsigned int *ctr = next + kNextStride * (blockIdx.x % chunks);
         unsigned int mine = lane == 0 ? atomicAdd(ctr, 1u) : 0u;
         while (true) {
-            const int64_t sl = first + (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
-            if (sl >= last) return;
+            k = first + (int64_t)(unsigned int)__builtin_amdgcn_readfirstlane((int)mine);
+            if (k >= last) return;
             mine = lane == 0 ? atomicAdd(ctr, 1u) : 0u;   // the one after, asked for early
-            const double t = terms_row<CPLX, MODE, FERMI, U>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, lz, jsq);
+            sl.request(td, none, k, lane, states, D, x, vprev);
+            const double t = terms_row<CPLX, MODE, FERMI, U>(tl, td, none, dm.nb, sl, gather, y, lz, jsq);
             // which wave takes a slice varies from run to run: one sum per slice
             if (MODE == 2) {
                 const double ws = wave_sum(t);
-                if (lane == 0) partials[sl] = ws;
+                if (lane == 0) partials[k] = ws;
             }
         }
     }
     double dot = 0.0;
-    for (int64_t sl = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave; !COUNTED && sl < last; sl += step)
-        dot += terms_row<CPLX, MODE, FERMI, U>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, vprev, lz, jsq);
+    while (!COUNTED && k < last) {
+        dot += terms_row<CPLX, MODE, FERMI, U>(tl, td, none, dm.nb, sl, gather, y, lz, jsq);
+        k += step;
+        if (k < last) sl.request(td, none, k, lane, states, D, x, vprev);
+    }
     if (MODE == 2) {
         const double t = block_sum(dot, sh);
         if (threadIdx.x == 0) partials[blockIdx.x] = t;
@@ -398,6 +426,12 @@ __global__ void __launch_bounds__(kTermsThreads)
 {
     using T = typename Scalar<CPLX>::T;
     extern __shared__ __align__(16) double lds_d[];
+    constexpr int U = 8;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t n_slices = (D + kWave - 1) / kWave, slice = (int64_t)blockIdx.x * kTermsWaves + wave;
+    const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
+    TermsSlice<CPLX, 0, U> sl;
+    if (slice < n_slices) sl.request(td, none, slice, lane, states, D, x, nullptr);
     T *xs = (T *)lds_d;
     const double *sq = (const double *)(dm.blob + dm.off_div);
     for (int k = threadIdx.x; k < (int)D; k += blockDim.x) {
@@ -414,11 +448,8 @@ __global__ void __launch_bounds__(kTermsThreads)
     if (threadIdx.x == 0) xs[D] = T{};
     // the class table starts on a 16-byte boundary
     const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d + (((D + 1) * (CPLX ? 2 : 1) + 1) & ~(int64_t)1));
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int64_t n_slices = (D + kWave - 1) / kWave;
     auto gather = [&](uint32_t j) { return xs[j]; };
-    for (int64_t sl = (int64_t)blockIdx.x * kTermsWaves + wave; sl < n_slices; sl += (int64_t)gridDim.x * kTermsWaves)
-        terms_row<CPLX, 0, FERMI, 4>(tl, td, dm.nb, sl, lane, states, D, gather, x, y, nullptr, LzState{}, jsq);
+    if (slice < n_slices) terms_row<CPLX, 0, FERMI, U>(tl, td, none, dm.nb, sl, gather, y, LzState{}, jsq);
 }
 
 // blocks of a pass over all slices: a multiple of 8 (see chunks) where there
@@ -675,13 +706,30 @@ __global__ void k_terms_pair(const typename Scalar<CPLX>::T *x, const typename S
     }
 }
 
-// Per-bond adjoint sums as k_backward_J forms them (same order, same bits),
-// the targets read from the stored terms; FUSED: gx = H gy in the same pass,
-// x_j and gy_j from one read of the pair array.  All lanes visit a bond
-// together; a lane's word is the one at its count of antiparallel bonds so
-// far.  Four bonds are read ahead, so that eight dependent reads of a lane are
-// two latencies.
-template <bool CPLX, bool FUSED>
+// f(0), ..., f(N - 1), each with its number as a type: arrays indexed by it
+// stay in registers
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// Per-bond adjoint sums, the targets read from the stored terms; FUSED: gx =
+// H gy in the same pass, x_j and gy_j from one read of the pair array.  All
+// lanes visit a bond together; a lane's word is the one at its count of
+// antiparallel bonds so far.  kAhead bonds are read ahead, so that twice as
+// many dependent reads of a lane are two latencies.
+// NB bounds the bonds: up to 128 have a register each in every lane for their
+// sum, added across lanes once at the end; more (NB = 0) are added across the
+// wave bond by bond and kept by lane b % 64.  The order is fixed either way.
+// 32-site square, 64 bonds: 5.9 ms with a sum across the wave per bond and four
+// bonds ahead, 5.4 with this; 24-site square 38 -> 25 us.
+template <bool CPLX, bool FUSED, int NB>
 __global__ void __launch_bounds__(kTermsThreads)
     k_terms_backward(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int64_t D,
                      const double *__restrict__ src, const typename Scalar<CPLX>::T *__restrict__ x,
@@ -689,7 +737,8 @@ __global__ void __launch_bounds__(kTermsThreads)
                      int chunks)
 {
     constexpr int W = CPLX ? 2 : 1;
-    constexpr int kAhead = 4;
+    constexpr int kAhead = 8;
+    constexpr int V = FUSED ? 2 * W : W;   // doubles per target
     extern __shared__ __align__(16) double lds_d[];
     // characters of the classes, 1/sqrt of the divisors, bonds; the block's
     // sums take their place at the end
@@ -711,7 +760,10 @@ __global__ void __launch_bounds__(kTermsThreads)
     const int64_t first = per * (blockIdx.x % chunks);
     const int64_t last = min(first + per, n_slices);
     const int64_t step = (int64_t)(gridDim.x / chunks) * kTermsWaves;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0, tot = 0.0;
+    double tot = 0.0;
+    double acc[NB > 0 ? NB : 4];   // NB = 0: bonds b of lane b % 64, 64 apart
+#pragma unroll
+    for (int b = 0; b < (NB > 0 ? NB : 4); ++b) acc[b] = 0.0;
     for (int64_t sl = first + (int64_t)(blockIdx.x / chunks) * kTermsWaves + wave; sl < last; sl += step) {
         const int64_t i = sl * kWave + lane;
         const bool valid = i < D;
@@ -733,13 +785,15 @@ __global__ void __launch_bounds__(kTermsThreads)
                 gx_r = g_r * *(const double *)&x[i];
             }
         }
-        tot += wave_sum(gx_r);
+        tot += gx_r;
         double anti_sum = 0.0, ar = 0.0, ai = 0.0;
         int pos = 0;
-        for (int b0 = 0; b0 < nb; b0 += kAhead) {
+        // kAhead bonds from b0; put(k, c) takes the contribution of bond b0 + k,
+        // k a compile-time number
+        auto bonds_from = [&](int b0, auto put) {
             bool anti[kAhead];
             uint32_t word[kAhead];
-            double v[kAhead][FUSED ? 2 * W : W];
+            double v[kAhead][V];
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) {
                 const int b = b0 + k;
@@ -756,29 +810,25 @@ __global__ void __launch_bounds__(kTermsThreads)
             }
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) {
+                for (int m = 0; m < V; ++m) v[k][m] = 0.0;
                 if (anti[k]) {
-                    const double *q = src + (size_t)(word[k] & im) * (FUSED ? 2 * W : W);
-                    if constexpr (FUSED && !CPLX) {
-                        const double2 a = *(const double2 *)q;
-                        v[k][0] = a.x;
-                        v[k][1] = a.y;
-                    } else if constexpr (FUSED) {
-                        const double2 a = *(const double2 *)q, g = *(const double2 *)(q + 2);
-                        v[k][0] = a.x;
-                        v[k][1] = a.y;
-                        v[k][2] = g.x;
-                        v[k][3] = g.y;
+                    const double *q = src + (size_t)(word[k] & im) * V;
+                    if constexpr (V == 1) {
+                        v[k][0] = *q;
                     } else {
-                        for (int m = 0; m < W; ++m) v[k][m] = q[m];
+#pragma unroll
+                        for (int m = 0; m < V; m += 2) {
+                            const double2 a = *(const double2 *)(q + m);
+                            v[k][m] = a.x;
+                            v[k][m + 1] = a.y;
+                        }
                     }
-                } else {
-                    for (int m = 0; m < (FUSED ? 2 * W : W); ++m) v[k][m] = 0.0;
                 }
             }
-#pragma unroll
-            for (int k = 0; k < kAhead; ++k) {
+            static_for<kAhead>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
                 const int b = b0 + k;
-                if (b >= nb || !__ballot(anti[k])) continue;
+                if (b >= nb) return;   // uniform
                 double contrib = 0.0;
                 if (anti[k]) {
                     const uint32_t cl = word[k] >> td.ibits;
@@ -790,18 +840,31 @@ __global__ void __launch_bounds__(kTermsThreads)
                     if (FUSED) {
                         const double jh = bonds[b].jhalf;
                         anti_sum += bonds[b].jzhalf;
-                        add_term<CPLX>(ar, ai, jh * cr, jh * ci, v[k][FUSED ? W : 0], CPLX ? v[k][FUSED ? 2 * W - 1 : 0] : 0.0);
+                        add_term<CPLX>(ar, ai, jh * cr, jh * ci, v[k][FUSED ? W : 0], CPLX ? v[k][V - 1] : 0.0);
                     }
                 }
-                const double wsum = wave_sum(contrib);
-                if (lane == (b & (kWave - 1))) {
-                    const int q = b >> 6;
-                    if (q == 0) a0 += wsum;
-                    else if (q == 1) a1 += wsum;
-                    else if (q == 2) a2 += wsum;
-                    else a3 += wsum;
-                }
-            }
+                put(kc, contrib);
+            });
+        };
+        if constexpr (NB > 0) {
+            static_for<NB / kAhead>([&](auto bc) {
+                constexpr int b0 = decltype(bc)::value * kAhead;
+                if (b0 >= nb) return;
+                bonds_from(b0, [&](auto kc, double c) { acc[b0 + decltype(kc)::value] += c; });
+            });
+        } else {
+            for (int b0 = 0; b0 < nb; b0 += kAhead)
+                bonds_from(b0, [&](auto kc, double c) {
+                    const int b = b0 + decltype(kc)::value;
+                    const double wsum = wave_sum(c);
+                    if (lane == (b & (kWave - 1))) {
+                        const int q = b >> 6;
+                        if (q == 0) acc[0] += wsum;
+                        else if (q == 1) acc[1] += wsum;
+                        else if (q == 2) acc[2] += wsum;
+                        else acc[3] += wsum;
+                    }
+                });
         }
         if (FUSED && valid) {
             const double d = jsq - anti_sum;
@@ -818,11 +881,21 @@ __global__ void __launch_bounds__(kTermsThreads)
     __syncthreads();
     double *red = lds_d;   // [waves][nb + 1]
     const int w1 = nb + 1;
-    for (int b = lane; b < nb; b += kWave) {
-        const int q = b >> 6;
-        red[wave * w1 + b] = q == 0 ? a0 : q == 1 ? a1 : q == 2 ? a2 : a3;
+    if constexpr (NB > 0) {
+        static_for<NB>([&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            if (b >= nb) return;
+            const double t = wave_sum(acc[b]);
+            if (lane == 0) red[wave * w1 + b] = t;
+        });
+    } else {
+        for (int b = lane; b < nb; b += kWave) {
+            const int q = b >> 6;
+            red[wave * w1 + b] = q == 0 ? acc[0] : q == 1 ? acc[1] : q == 2 ? acc[2] : acc[3];
+        }
     }
-    if (lane == 0) red[wave * w1 + nb] = tot;
+    const double t = wave_sum(tot);
+    if (lane == 0) red[wave * w1 + nb] = t;
     __syncthreads();
     for (int b = threadIdx.x; b < w1; b += blockDim.x) {
         double sum = 0.0;
@@ -840,10 +913,12 @@ int terms_backward(const ed_basis *bc, const void *x, const void *gy, void *gx, 
     hipStream_t st = (hipStream_t)stream;
     const int nb = b->t.nb, W = b->dm.is_complex ? 2 : 1;
     const int64_t D = b->db.dim;
-    // at most 4 blocks per compute unit, each of which leaves a row of partial
-    // sums, and slices at a fixed stride: the sums are the same on every run
+    // as many blocks per compute unit as the bonds' registers leave room for,
+    // each of which leaves a row of partial sums, and slices at a fixed stride:
+    // the sums are the same on every run
+    const int per_cu = nb <= 64 ? 2 : nb <= 128 ? 1 : 4;
     int64_t blocks = ((D + kWave - 1) / kWave + kTermsWaves - 1) / kTermsWaves;
-    if (blocks >= 8) blocks = std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * 4 & ~7));
+    if (blocks >= 8) blocks = std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * per_cu & ~7));
     const int grid = (int)blocks, chunks = grid % 8 == 0 ? 8 : 1;
     const size_t n_part = (size_t)grid * (nb + 1);
     if (gx && !b->terms.pair) {
@@ -857,23 +932,36 @@ int terms_backward(const ed_basis *bc, const void *x, const void *gy, void *gx, 
         b->device_bytes += (int64_t)bytes;
         b->terms.bytes += (int64_t)bytes;
     }
-    double *partials = nullptr, *out = nullptr;
-    if (scratch) {
-        if (n_part + (size_t)(nb + 1) > scratch_doubles)
-            return set_error(ED_ERR_UNSUPPORTED, "adjoint partials of %zu doubles exceed the %zu-double scratch array",
-                             n_part + (size_t)(nb + 1), scratch_doubles);
-        partials = scratch;
-    } else if (hipMalloc((void **)&partials, (n_part + nb + 1) * 8) != hipSuccess) {
-        (void)hipGetLastError();
-        return set_error(ED_ERR_OOM, "adjoint partials");
+    double *partials = scratch;
+    if (scratch && n_part + (size_t)(nb + 1) > scratch_doubles)
+        return set_error(ED_ERR_UNSUPPORTED, "adjoint partials of %zu doubles exceed the %zu-double scratch array",
+                         n_part + (size_t)(nb + 1), scratch_doubles);
+    if (!scratch) {   // kept with the terms: the grid never changes
+        if (!b->terms.adj) {
+            const size_t bytes = (n_part + nb + 1) * 8;
+            if (hipMalloc((void **)&b->terms.adj, bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                b->terms.adj = nullptr;
+                return set_error(ED_ERR_OOM, "adjoint partials");
+            }
+            b->device_bytes += (int64_t)bytes;
+            b->terms.bytes += (int64_t)bytes;
+        }
+        partials = b->terms.adj;
     }
-    out = partials + n_part;
+    double *out = partials + n_part;
     const size_t lds = std::max((size_t)b->terms.n_cls * W * 8 + (size_t)b->dm.n_div * 8 + (size_t)nb * sizeof(BondLds),
                                 (size_t)kTermsWaves * (nb + 1) * 8);
     const double *sq = (const double *)(b->dm.blob + b->dm.off_div);
     const dim3 pgrid((unsigned)std::min<int64_t>((D + 256) / 256, (int64_t)num_cus() * 16));
 #define ED_BACK(C, F) \
-    hipLaunchKernelGGL((k_terms_backward<C, F>), dim3(grid), dim3(kTermsThreads), lds, st, b->dm, terms_dev(b), b->db.states, \
+    do { \
+        if (nb <= 64) ED_BACK_NB(C, F, 64); \
+        else if (nb <= 128) ED_BACK_NB(C, F, 128); \
+        else ED_BACK_NB(C, F, 0); \
+    } while (0)
+#define ED_BACK_NB(C, F, NB) \
+    hipLaunchKernelGGL((k_terms_backward<C, F, NB>), dim3(grid), dim3(kTermsThreads), lds, st, b->dm, terms_dev(b), b->db.states, \
                        D, (const double *)(F ? b->terms.pair : b->terms.xs), (const Scalar<C>::T *)x, \
                        (const Scalar<C>::T *)gy, partials, (double *)gx, jsq, chunks)
     if (b->dm.is_complex) {
@@ -894,11 +982,11 @@ int terms_backward(const ed_basis *bc, const void *x, const void *gy, void *gx, 
         }
     }
 #undef ED_BACK
+#undef ED_BACK_NB
     int rc = sum_partials_cols(partials, grid, nb + 1, out, stream);
     double h[kMaxBondWords * 64 + 1];
     hipError_t e = rc ? hipSuccess : hipMemcpyAsync(h, out, (size_t)(nb + 1) * 8, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (!scratch) (void)hipFree(partials);
     if (rc) return rc;
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "adjoint failed: %s", hipGetErrorString(e));
     for (int k = 0; k < nb; ++k) gJ_host[k] = h[k] + 0.25 * h[nb];
@@ -913,12 +1001,12 @@ void terms_free(ed_basis *b)
 {
     auto &t = b->terms;
     for (void *p : {t.words, (void *)t.off, (void *)t.cnt, (void *)t.xs, (void *)t.pair, (void *)t.cls, (void *)t.cls_chi,
-                    (void *)t.next, (void *)t.dots})
+                    (void *)t.next, (void *)t.dots, (void *)t.adj})
         if (p) (void)hipFree(p);
     t.words = nullptr;
     t.off = nullptr;
     t.cnt = nullptr;
-    t.xs = t.pair = t.cls = t.cls_chi = t.dots = nullptr;
+    t.xs = t.pair = t.cls = t.cls_chi = t.dots = t.adj = nullptr;
     t.next = nullptr;
     b->device_bytes -= t.bytes;
     t.bytes = 0;
