@@ -768,6 +768,7 @@ struct TermsDev {
     const uint64_t *off;
     const uint32_t *cnt;
     uint32_t stride;
+    int64_t n_slices;
     int ibits, n_cls;
     const double *cls;        // {kr, jz} or {kr, ki, jz, -} of every class
     const double *cls_chi;    // chi or {re, im} of every class
@@ -780,6 +781,7 @@ inline TermsDev terms_dev(const ed_basis *b)
     td.off = b->terms.off;
     td.cnt = b->terms.cnt;
     td.stride = b->terms.stride;
+    td.n_slices = b->terms.n_slices;
     td.ibits = b->terms.ibits;
     td.n_cls = b->terms.n_cls;
     td.cls = b->terms.cls;

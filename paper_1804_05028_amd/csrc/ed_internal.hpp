@@ -157,8 +157,10 @@ struct ed_basis {
     bool want_terms = false;       // the basis may store its terms (not a batched one's)
     // stored terms: the target and coefficient class of every off-diagonal
     // term (ed_terms.hip), made with the basis where they fit, freed with it
-    // or by ed_basis_release_terms
+    // or by ed_basis_release_terms; or those of the first slices of 64 rows,
+    // by a Lanczos call for its duration
     struct {
+        int64_t n_slices = 0;          // slices stored
         void *words = nullptr;         // groups of 64 lanes x 4 words, slice by slice
         uint64_t *off = nullptr;       // [n_slices] first group of a slice (nullptr: slice * stride)
         uint32_t *cnt = nullptr;       // [n_slices] groups of a slice
@@ -240,11 +242,15 @@ int check_couplings(const ed_basis *b, const double *J);
 int scan_counts(const uint32_t *counts, uint64_t *offsets, uint64_t n, void *stream);
 // Stored terms (ed_terms.hip)
 bool terms_wanted(const ed_basis *b);
-int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class = nullptr, int n_elem_class = 0);
+int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class = nullptr, int n_elem_class = 0,
+                size_t call_limit = 0);
 void free_rep_index(ed_basis *b);
 void terms_free(ed_basis *b);
+bool terms_couplings_equal(const ed_basis *b, const double *J);
 int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream);
 inline bool terms_usable(const ed_basis *b) { return b->terms.words && b->terms.couplings_ok; }
+// rows stored: all, or in a Lanczos call the first ones
+inline int64_t terms_rows(const ed_basis *b) { return std::min<int64_t>(b->db.dim, 64 * b->terms.n_slices); }
 // a sector whose scaled input fits the LDS of every block: its H.v reads x itself
 inline bool terms_small(const ed_basis *b) { return b->db.dim <= (b->dm.is_complex ? 2048 : 4096); }
 int terms_dots(const ed_basis *b);

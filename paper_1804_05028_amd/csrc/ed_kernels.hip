@@ -38,7 +38,7 @@ template <bool CPLX, typename AT, int INDEX, int MODE, int NS, bool FERMI = fals
 __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const typename Scalar<CPLX>::T *__restrict__ x,
                                                 typename Scalar<CPLX>::T *__restrict__ y,
                                                 const typename Scalar<CPLX>::T *__restrict__ vprev, double *partials,
-                                                unsigned long long *stats, LzStep lz, double jsum_quarter)
+                                                unsigned long long *stats, LzStep lz, double jsum_quarter, int64_t row0)
 {
     extern __shared__ __align__(16) char lds[];
     __shared__ double sh[MODE == 2 ? 1024 / kWave + 1 : 1];
@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     // wave-uniform row loop: every lane of a wave runs the same iterations
-    for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; i0 < D; i0 += stride) {
+    for (int64_t i0 = row0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; i0 < D; i0 += stride) {
         const int64_t i = i0 + lane;
         const bool row_ok = i < D;
         const uint64_t e = row_ok ? db.states[i] : 0ull;
@@ -231,18 +231,25 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
 // where the scaled amplitudes sqrt(n_j) x_j of an H.v's input go: the stored
 // terms' dense array, the value fields of the hash slots, or nowhere (the
 // Limits kernels scale what they gather)
-enum { TO_TERMS = 0, TO_SLOTS = 1, TO_NONE = 2 };
+enum { TO_TERMS = 0, TO_SLOTS = 1, TO_NONE = 2, TO_BOTH = 3 };
+
+struct ScaledDst {
+    char *dense, *slots;
+    const uint32_t *slot_of;
+    unsigned int *next;   // the stored terms' slice counters
+};
 
 template <bool CPLX, int TO>
-__device__ __forceinline__ void put_scaled(char *dst, const uint32_t *slot_of, int64_t j, double sq,
-                                           typename Scalar<CPLX>::T v)
+__device__ __forceinline__ void put_scaled(const ScaledDst &d, int64_t j, double sq, typename Scalar<CPLX>::T v)
 {
-    if (TO == TO_NONE) return;
-    const size_t at = TO == TO_SLOTS ? (size_t)slot_of[j] * (CPLX ? 32 : 16) + (CPLX ? 16 : 8) : (size_t)j * sizeof v;
+    using T = typename Scalar<CPLX>::T;
+    T u;
     if constexpr (CPLX)
-        *(double2 *)(dst + at) = make_double2(v.x * sq, v.y * sq);
+        u = make_double2(v.x * sq, v.y * sq);
     else
-        *(double *)(dst + at) = v * sq;
+        u = v * sq;
+    if (TO == TO_TERMS || TO == TO_BOTH) ((T *)d.dense)[j] = u;
+    if (TO == TO_SLOTS || TO == TO_BOTH) *(T *)(d.slots + (size_t)d.slot_of[j] * (CPLX ? 32 : 16) + (CPLX ? 16 : 8)) = u;
 }
 
 // the stored terms' slice counters back to 0, before the H.v that follows
@@ -253,12 +260,11 @@ __device__ __forceinline__ void reset_slices(unsigned int *next)
 
 // scaled amplitudes of x; sqrts: the square roots of the divisors of |G|
 template <bool CPLX, int TO>
-__global__ void k_pack(const typename Scalar<CPLX>::T *x, const uint64_t *states, const double *sqrts,
-                       const uint32_t *slot_of, char *dst, int64_t D, unsigned int *next)
+__global__ void k_pack(const typename Scalar<CPLX>::T *x, const uint64_t *states, const double *sqrts, ScaledDst dst, int64_t D)
 {
-    if (TO == TO_TERMS) reset_slices(next);
+    if (TO == TO_TERMS || TO == TO_BOTH) reset_slices(dst.next);
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x)
-        put_scaled<CPLX, TO>(dst, slot_of, j, sqrts[states[j] >> kNormShift], x[j]);
+        put_scaled<CPLX, TO>(dst, j, sqrts[states[j] >> kNormShift], x[j]);
 }
 
 // ---------------------------------------------------------------------------
@@ -787,10 +793,10 @@ template <bool CPLX, int TO>
 __global__ void __launch_bounds__(kVecThreads)
     k_lz_update(typename Scalar<CPLX>::T *w, const typename Scalar<CPLX>::T *c, int64_t D, const double *dots, int n_dots,
                 double *norms, const LzState *lz, double *alpha_hist, typename Scalar<CPLX>::T *psi, const double *svec,
-                const uint64_t *states, const double *sqrts, const uint32_t *slot_of, char *dst, unsigned int *next)
+                const uint64_t *states, const double *sqrts, ScaledDst dst)
 {
     __shared__ double sh[kVecThreads / kWave + 1];
-    if (TO == TO_TERMS) reset_slices(next);
+    if (TO == TO_TERMS || TO == TO_BOTH) reset_slices(dst.next);
     if (lz->done) return;
     const int j = lz->j;
     const double inv = lz->inv;
@@ -814,7 +820,7 @@ __global__ void __launch_bounds__(kVecThreads)
             if (psi) psi[i] += sj * v;
         }
         w[i] = wi;
-        if (TO != TO_NONE) put_scaled<CPLX, TO>(dst, slot_of, i, sqrts[states[i] >> kNormShift], wi);
+        if (TO != TO_NONE) put_scaled<CPLX, TO>(dst, i, sqrts[states[i] >> kNormShift], wi);
     }
     const double t = block_sum(acc, sh);
     if (threadIdx.x == 0) norms[blockIdx.x] = t;
@@ -1396,10 +1402,14 @@ int launch_basis_build(ed_basis *b, void *stream)
 // place of both indexes)
 static int input_place(const ed_basis *b)
 {
-    return terms_usable(b) ? TO_TERMS : b->db.index_mode == IDX_HASH ? TO_SLOTS : TO_NONE;
+    if (terms_usable(b)) return terms_rows(b) == b->db.dim ? TO_TERMS : TO_BOTH;
+    return b->db.index_mode == IDX_HASH ? TO_SLOTS : TO_NONE;
 }
 
-static char *input_dst(const ed_basis *b, int to) { return to == TO_TERMS ? (char *)b->terms.xs : b->db.slots; }
+static ScaledDst input_dst(const ed_basis *b)
+{
+    return ScaledDst{(char *)b->terms.xs, b->db.slots, b->db.slot_of, b->terms.next};
+}
 
 static const double *sqrt_table(const ed_basis *b) { return (const double *)(b->dm.blob + b->dm.off_div); }
 
@@ -1410,16 +1420,17 @@ static int pack_input(const ed_basis *b, const void *x, hipStream_t st)
     const int64_t D = b->db.dim;
     const dim3 g((unsigned)std::min<int64_t>((D + 255) / 256, (int64_t)num_cus() * 16));
     const double *sq = sqrt_table(b);
-    char *dst = input_dst(b, to);
-#define ED_PACK(C, TO) \
-    hipLaunchKernelGGL((k_pack<C, TO>), g, dim3(256), 0, st, (const Scalar<C>::T *)x, b->db.states, sq, b->db.slot_of, dst, D, b->terms.next)
-    if (b->dm.is_complex) {
-        if (to == TO_TERMS) ED_PACK(true, TO_TERMS);
-        else ED_PACK(true, TO_SLOTS);
-    } else {
-        if (to == TO_TERMS) ED_PACK(false, TO_TERMS);
-        else ED_PACK(false, TO_SLOTS);
-    }
+#define ED_PACK_TO(C, TO) \
+    hipLaunchKernelGGL((k_pack<C, TO>), g, dim3(256), 0, st, (const Scalar<C>::T *)x, b->db.states, sq, input_dst(b), D)
+#define ED_PACK(C) \
+    do { \
+        if (to == TO_TERMS) ED_PACK_TO(C, TO_TERMS); \
+        else if (to == TO_BOTH) ED_PACK_TO(C, TO_BOTH); \
+        else ED_PACK_TO(C, TO_SLOTS); \
+    } while (0)
+    if (b->dm.is_complex) ED_PACK(true);
+    else ED_PACK(false);
+#undef ED_PACK_TO
 #undef ED_PACK
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "pack launch failed: %s", hipGetErrorString(e));
@@ -1440,7 +1451,7 @@ static int apply_impl(const ed_basis *b, const void *x, void *y, const void *vpr
         grid = b->grid_blocks;   // fixed grid so the reductions are deterministic
     }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, b->dm, b->db, (const T *)x, (T *)y, (const T *)vprev,
-                       partials, stats, lz ? *lz : LzStep{}, jsq);
+                       partials, stats, lz ? *lz : LzStep{}, jsq, MODE == 2 && terms_usable(b) ? terms_rows(b) : (int64_t)0);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "H.v launch failed: %s", hipGetErrorString(e));
     return ED_OK;
@@ -1808,8 +1819,33 @@ static void launch_lz_update(const ed_basis *b, int vgrid, double *w, const doub
 {
     using T = typename Scalar<CPLX>::T;
     hipLaunchKernelGGL((k_lz_update<CPLX, TO>), dim3(vgrid), dim3(kVecThreads), 0, st, (T *)w, (const T *)c, b->db.dim, dots,
-                       n_dots, norms, lz, ahist, (T *)psi, svec, b->db.states, sqrt_table(b), b->db.slot_of,
-                       input_dst(b, TO), b->terms.next);
+                       n_dots, norms, lz, ahist, (T *)psi, svec, b->db.states, sqrt_table(b), input_dst(b));
+}
+
+// Steps from which a Lanczos call stores the terms of a sector whose table is
+// too large to keep.  40-site square, 130 of 142 GB: 0.9 s for the search, up
+// to 3.9 s for an allocation that has to wait until the freed pages are cleared
+// (29 ms per GB), against 0.40 s saved per step (766 -> 366 ms; 20 steps 15.3
+// -> 8.1 s).
+constexpr int kStoreSteps = 16;
+
+// the rows, overwritten by the amplitudes of real sectors, for the search of the terms
+__global__ void k_slots_rows(const uint32_t *slot_of, char *slots, int slot_bytes, int64_t D)
+{
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x)
+        *(uint64_t *)(slots + (size_t)slot_of[j] * slot_bytes + 8) = (uint64_t)j;
+}
+
+// half of the free memory
+static int store_terms_for_call(ed_basis *b, hipStream_t st)
+{
+    size_t free_b = 0, total_b = 0;
+    if (b->db.index_mode != IDX_HASH || hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b < 2) return ED_OK;
+    const int64_t D = b->db.dim;
+    hipLaunchKernelGGL(k_slots_rows, dim3((unsigned)std::min<int64_t>((D + 255) / 256, 1 << 20)), dim3(256), 0, st,
+                       b->db.slot_of, b->db.slots, b->dm.is_complex ? 32 : 16, D);
+    HIP_TRY(hipGetLastError());
+    return terms_build(b, st, nullptr, 0, free_b / 2);
 }
 
 int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const void *v0, int n_steps, double *alpha,
@@ -1821,11 +1857,10 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     if (!rc && Jz) rc = check_couplings(b, Jz);
     if (rc) return rc;
     double jsq;
-    rc = upload_couplings(b, J, Jz, st, &jsq);
-    if (rc) return rc;
     const int64_t D = b->db.dim;
     *n_done = 0;
     if (D == 0 || n_steps <= 0) return ED_OK;
+    const int passes = psi0 ? 2 : 1;
     const bool cplx = b->dm.is_complex;
     const int64_t nd = cplx ? 2 * D : D;   // doubles per vector
     {
@@ -1834,12 +1869,9 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         b->grid_blocks = grid;   // fixed launch geometry -> deterministic reductions
     }
     const int vgrid = (int)std::min<int64_t>((nd + kVecThreads - 1) / kVecThreads, (int64_t)num_cus() * 8);
-    const int to = input_place(b);
-    const bool small = to == TO_TERMS && terms_small(b);   // one launch does all steps
-    const int np_apply = to == TO_TERMS ? terms_dots(b) : b->grid_blocks;
     const size_t vb = (size_t)nd * 8;
     auto &W = b->lzw;
-    const size_t npart = (size_t)std::max(np_apply, vgrid);
+    const size_t npart = (size_t)b->grid_blocks + (size_t)num_cus() * 8;   // any of the reductions
     // the vectors are sized by the basis and kept between calls; only the
     // coefficient histories grow with n_steps
     if (!W.vec[0] || W.cap_partials < npart) {
@@ -1873,7 +1905,26 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     std::vector<double> back((size_t)2 * n_steps + kStateDoubles);
     double *norms = partials + W.cap_partials;    // |w|^2 partials, beside the <v, w> ones
     std::vector<double> svec_host(n_steps, 0.0);
-    const int passes = psi0 ? 2 : 1;
+    struct CallTerms {   // a table of this call's own goes with it
+        ed_basis *b = nullptr;
+        ~CallTerms()
+        {
+            if (b) terms_free(b);
+        }
+    } call_terms;
+    if (!b->terms.words && n_steps * passes >= kStoreSteps && terms_couplings_equal(b, J) &&
+        (!Jz || terms_couplings_equal(b, Jz))) {
+        call_terms.b = b;
+        rc = store_terms_for_call(b, st);
+        if (rc) return rc;
+    }
+    rc = upload_couplings(b, J, Jz, st, &jsq);
+    if (rc) return rc;
+    const int to = input_place(b);
+    const bool small = to == TO_TERMS && terms_small(b);   // one launch does all steps
+    // <v, w> partials: of the stored rows, then of the searched ones
+    const int np_terms = terms_usable(b) ? terms_dots(b) : 0;
+    const int np_apply = np_terms + (to == TO_TERMS ? 0 : b->grid_blocks);
     for (int pass = 0; pass < passes; ++pass) {
         double *psi = pass == 1 ? (double *)psi0 : nullptr;
         LzState init[2] = {};
@@ -1916,17 +1967,20 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         for (; !small && step < n_steps; ++step) {
             double *w = W.vec[(step + 1) % 3];
             const LzStep ls = step_of(step);
-            rc = to == TO_TERMS ? terms_lanczos_apply(b, cur, w, prev, partials, &ls, jsq, st)
-                                : apply_dispatch<2>(b, cur, w, prev, partials, nullptr, &ls, jsq, st);
+            if (np_terms) rc = terms_lanczos_apply(b, cur, w, prev, partials, &ls, jsq, st);
+            if (!rc && to != TO_TERMS)
+                rc = apply_dispatch<2>(b, cur, w, prev, partials + np_terms, nullptr, &ls, jsq, st);
             if (rc) return rc;
 #define ED_UPDATE(CP, TO) \
     launch_lz_update<CP, TO>(b, vgrid, w, cur, partials, np_apply, norms, ls.next, ahist, psi, svec, st)
             if (cplx) {
                 if (to == TO_TERMS) ED_UPDATE(true, TO_TERMS);
+                else if (to == TO_BOTH) ED_UPDATE(true, TO_BOTH);
                 else if (to == TO_SLOTS) ED_UPDATE(true, TO_SLOTS);
                 else ED_UPDATE(true, TO_NONE);
             } else {
                 if (to == TO_TERMS) ED_UPDATE(false, TO_TERMS);
+                else if (to == TO_BOTH) ED_UPDATE(false, TO_BOTH);
                 else if (to == TO_SLOTS) ED_UPDATE(false, TO_SLOTS);
                 else ED_UPDATE(false, TO_NONE);
             }

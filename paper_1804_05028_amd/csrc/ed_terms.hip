@@ -18,6 +18,10 @@
 // that a wave reads its words as one 1 KB load.  A row's terms are in bond
 // order, as in the searching kernels, and summed by the same operations: both
 // give the same bits.
+//
+// A sector whose table is too large to keep (40-site square: 142 GB) gets one
+// for the duration of a long Lanczos call, in half of the free memory; where
+// that holds the first slices only, the searching kernel does the other rows.
 #include "ed_device.hpp"
 
 #include <type_traits>
@@ -63,16 +67,15 @@ __global__ void __launch_bounds__(256) k_terms_count(DevModel dm, const uint64_t
 
 // Searches every term.  A wave takes a slice, or, where there are few slices,
 // every parts-th term of one.  As in k_apply, the index entry (without an
-// index, the slot) of the next term is
-// requested before the current one is resolved.  The index costs a third of
-// the lines of hashed slots, since neighbouring rows share entries: 32-site
+// index, the slot) of the next term is requested before the current one is
+// resolved.  The index costs a third of the lines of hashed slots, since neighbouring rows share entries: 32-site
 // square 15.3 -> 6.5 ms, 30-site complex sector 3.9 -> 2.1 ms; the 864-element
 // group, bound by its search, 29.9 -> 27.8 ms.
 template <typename AT, int NSC, bool FERMI>
 __global__ void __launch_bounds__(1024) k_terms_fill(DevModel dm, DevBasis db, RepIndex ix, const uint64_t *off, uint32_t stride,
                                                      uint32_t *cnt, uint32_t *words, const uint16_t *chi_class,
                                                      const uint16_t *bond_orbit, int n_orb, int ibits, uint32_t pad,
-                                                     int parts)
+                                                     int parts, int64_t n_slices)
 {
     extern __shared__ __align__(16) char lds[];
     const Ctx<AT> c = stage<AT>(dm, lds);
@@ -81,7 +84,7 @@ __global__ void __launch_bounds__(1024) k_terms_fill(DevModel dm, DevBasis db, R
     const uint64_t smask = (1ull << db.slot_log2) - 1ull;
     const int lane = threadIdx.x & (kWave - 1);
     const int sshift = dm.is_complex ? 5 : 4;
-    const int64_t n_units = (D + kWave - 1) / kWave * parts;
+    const int64_t n_units = n_slices * parts;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int64_t n_waves = (int64_t)gridDim.x * blockDim.x / kWave;
     for (int64_t unit = wave; unit < n_units; unit += n_waves) {
@@ -360,7 +363,7 @@ __global__ void __launch_bounds__(kTermsThreads)
     __shared__ double sh[kTermsWaves + 1];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
-    const int64_t n_slices = (D + kWave - 1) / kWave;
+    const int64_t n_slices = td.n_slices;
     const int64_t per = (n_slices + chunks - 1) / chunks;
     const int64_t first = per * (blockIdx.x % chunks);
     const int64_t last = min(first + per, n_slices);
@@ -457,7 +460,7 @@ __global__ void __launch_bounds__(kTermsThreads)
 // else at most 8
 int terms_grid(const ed_basis *b)
 {
-    const int64_t blocks = ((b->db.dim + kWave - 1) / kWave + kTermsWaves - 1) / kTermsWaves;
+    const int64_t blocks = (b->terms.n_slices + kTermsWaves - 1) / kTermsWaves;
     if (blocks < 8) return (int)std::max<int64_t>(blocks, 1);
     return (int)std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * (b->terms.next ? 1 : 8) & ~7));
 }
@@ -490,7 +493,7 @@ static int launch_terms(const ed_basis *b, const void *x, void *y, const void *v
 #undef ED_TERMS
         if (MODE == 2 && b->terms.next)
             hipLaunchKernelGGL(k_terms_dots, dim3(kDotBlocks), dim3(kTermsThreads), 0, st, (const double *)b->terms.dots,
-                               (b->db.dim + kWave - 1) / kWave, partials, (const LzState *)((const LzStep *)lz)->next);
+                               b->terms.n_slices, partials, (const LzState *)((const LzStep *)lz)->next);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "H.v launch failed: %s", hipGetErrorString(e));
@@ -1013,6 +1016,20 @@ void terms_free(ed_basis *b)
     t.couplings_ok = false;
 }
 
+// One coefficient per orbit: couplings that differ in their last bits within an
+// orbit (the check allows 1e-12) run the searching kernels, which read them
+// bond by bond.
+bool terms_couplings_equal(const ed_basis *b, const double *J)
+{
+    std::vector<int> first(b->t.nb, -1);
+    for (int k = 0; k < b->t.nb; ++k) {
+        int &f = first[b->t.bond_orbit[k]];
+        if (f < 0) f = k;
+        if (J[k] != J[f]) return false;
+    }
+    return true;
+}
+
 // class coefficients of new couplings (ordered on the stream, which the
 // caller synchronises before the host arrays here go: none do, they are
 // copied first)
@@ -1021,14 +1038,8 @@ int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream
     auto &t = b->terms;
     if (!t.words) return ED_OK;
     hipStream_t st = (hipStream_t)stream;
-    // one coefficient per orbit: couplings that differ in their last bits
-    // within an orbit (the check allows 1e-12) run the searching kernels,
-    // which read them bond by bond
     t.couplings_ok = false;
-    for (int k = 0; k < b->t.nb; ++k) {
-        const int f = t.orbit_bond[b->t.bond_orbit[k]];
-        if (J[k] != J[f] || Jz[k] != Jz[f]) return ED_OK;
-    }
+    if (!terms_couplings_equal(b, J) || !terms_couplings_equal(b, Jz)) return ED_OK;
     const int W = b->dm.is_complex ? 4 : 2;
     std::vector<double> tab((size_t)t.n_cls * W, 0.0);
     const int n_chi = (int)t.chi_vals.size() / 2;
@@ -1056,14 +1067,14 @@ static int fill_impl(ed_basis *b, const uint16_t *chi_class, const uint16_t *orb
         per_cu = 1;
     // few slices: several waves share one, so that a short table is not one
     // wave's chain of searches
-    const int64_t slices = (b->db.dim + kWave - 1) / kWave, waves = (int64_t)per_cu * num_cus() * (th / kWave);
+    const int64_t slices = b->terms.n_slices, waves = (int64_t)per_cu * num_cus() * (th / kWave);
     int parts = 1;
     while (parts < 16 && slices * parts * 2 <= waves) parts *= 2;
     const int64_t need = (slices * parts + th / kWave - 1) / (th / kWave);
     const int grid = (int)std::max<int64_t>(std::min<int64_t>((int64_t)per_cu * num_cus(), need), 1);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(th), b->dm.lds_total, st, b->dm, b->db, b->rep_index, (const uint64_t *)b->terms.off,
                        b->terms.stride, b->terms.cnt, (uint32_t *)b->terms.words, chi_class, orbit, b->terms.n_orb,
-                       b->terms.ibits, pad, parts);
+                       b->terms.ibits, pad, parts, slices);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "term search launch failed: %s", hipGetErrorString(e));
     return ED_OK;
@@ -1105,15 +1116,43 @@ static int fill_ns(ed_basis *b, const uint16_t *cc, const uint16_t *orb, uint32_
     }
 }
 
+static bool terms_possible(const ed_basis *b)
+{
+    return b->want_terms && b->db.index_mode == 0 && b->db.dim >= 1 && b->t.nb >= 1;
+}
+
 // whether terms_build may find room: a quarter of the bonds, antiparallel in
 // about half of the rows, is a safe lower bound of the words
 bool terms_wanted(const ed_basis *b)
 {
     size_t free_b = 0, total_b = 0;
-    if (!b->want_terms || b->db.index_mode != 0 || b->db.dim < 1 || b->t.nb < 1) return false;
+    if (!terms_possible(b)) return false;
     if (b->db.dim < (1 << 16)) return true;
     return hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
            (uint64_t)b->db.dim * (uint64_t)b->t.nb <= std::min(total_b / 16, free_b / 2);
+}
+
+// the first slices whose words take at most bytes; *groups: their groups.
+// off is on the device: a binary search by single reads
+static int64_t slices_that_fit(const uint64_t *off, int64_t slices, size_t bytes, uint64_t *groups, hipStream_t st)
+{
+    const uint64_t most = bytes / ((size_t)kWave * 16);
+    int64_t lo = 0, hi = slices - 1;   // slices [0, lo) fit, their end is off[lo]
+    *groups = 0;
+    while (lo < hi) {
+        const int64_t mid = hi - (hi - lo) / 2;
+        uint64_t end = 0;
+        if (hipMemcpyAsync(&end, off + mid, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return 0;
+        if (end <= most) {
+            lo = mid;
+            *groups = end;
+        } else {
+            hi = mid - 1;
+        }
+    }
+    return lo;
 }
 
 void free_rep_index(ed_basis *b)
@@ -1129,14 +1168,16 @@ void free_rep_index(ed_basis *b)
 // memory and half of what is free.  Anything else leaves the basis without
 // one, to the searching kernels; only an error of the device is returned.  A
 // batched basis gives the classes of its elements (equal characters in every
-// sector), whose coefficients are then the couplings alone.
-int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_elem_class)
+// sector), whose coefficients are then the couplings alone.  A call's own
+// table may take call_limit bytes; it holds the first slices where not all fit
+// (an eighth at least, or none).
+int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_elem_class, size_t call_limit)
 {
     hipStream_t st = (hipStream_t)stream;
     auto &t = b->terms;
     const int64_t D = b->db.dim;
     const int nb = b->t.nb, ng = b->t.ng;
-    if (!terms_wanted(b)) return ED_OK;
+    if (call_limit ? !terms_possible(b) : !terms_wanted(b)) return ED_OK;
     // distinct characters (fermions: and their negatives, for the sign)
     std::vector<uint16_t> cls((size_t)ng * 2);
     t.chi_vals.clear();
@@ -1214,15 +1255,22 @@ int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_ele
         HIP_TRY(hipStreamSynchronize(st));
         groups = last_off + last_cnt;
     }
+    const size_t limit = call_limit ? call_limit : std::min(total_b / 16, free_b / 2);
+    t.n_slices = slices;
+    if (groups * kGroupBytes + vec > limit) {
+        if (!call_limit || t.stride || limit < vec) return give_up();
+        t.n_slices = slices_that_fit(t.off, slices, limit - vec, &groups, st);
+        if (t.n_slices < std::max<int64_t>(slices / 8, 1)) return give_up();
+    }
     const size_t bytes = std::max<size_t>(groups, 1) * kGroupBytes;
-    if (bytes + vec > std::min(total_b / 16, free_b / 2)) return give_up();
     // the scaled input exceeds the L2s (8 x 4 MB): slices from a counter
     const bool counted = vec > (32u << 20) && !elem_class;
     const size_t clsb = (size_t)t.n_cls * (b->dm.is_complex ? 32 : 16);
     void *d_cls = nullptr;   // chi classes and bond orbits, needed by the search only
     if (!take(&t.words, bytes) || (!elem_class && !take((void **)&t.xs, vec)) || !take((void **)&t.cls, clsb) ||
         !take((void **)&t.cls_chi, clsb / 2) ||
-        (counted && (!take((void **)&t.next, 8 * kNextStride * 4) || !take((void **)&t.dots, (size_t)slices * 8))) || hipMalloc(&d_cls, (cls.size() + orb.size()) * 2) != hipSuccess)
+        (counted && (!take((void **)&t.next, 8 * kNextStride * 4) || !take((void **)&t.dots, (size_t)t.n_slices * 8))) ||
+        hipMalloc(&d_cls, (cls.size() + orb.size()) * 2) != hipSuccess)
         return give_up();
     std::vector<double> chi((size_t)t.n_cls * (b->dm.is_complex ? 2 : 1), 0.0);
     for (int k = 0; k + 1 < t.n_cls; ++k) {
@@ -1266,6 +1314,7 @@ extern "C" int64_t ed_basis_terms_bytes(const ed_basis_t *b) { return b && b->te
 extern "C" int ed_basis_release_terms(ed_basis_t *b)
 {
     if (!b) return ed::set_error(ED_ERR_ARG, "null basis");
+    b->want_terms = false;
     if (!b->terms.words) return ED_OK;
     if (hipDeviceSynchronize() != hipSuccess) return ed::set_error(ED_ERR_HIP, "device synchronisation");
     ed::terms_free(b);

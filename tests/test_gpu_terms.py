@@ -168,6 +168,51 @@ def test_slice_counter(name, k, n_up, counted):
         b.close()
 
 
+def test_terms_of_a_lanczos_call():
+    """A sector whose terms are too many to keep: a Lanczos call of 16 steps
+    stores all of them, or (here, where little memory is free) those of the
+    first rows, and gives the memory back.  The sums add the rows in another
+    order than the searching call: a few times sqrt(rows) eps of terms of order
+    20, below 1e-9.  A coupling that differs by a bit within its orbit is
+    searched, and so is every call after the release."""
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    w = wl.square_40_j1j2(n_sub=4)
+    b = ed.Basis.from_workload(w)
+    try:
+        print(f"[terms] square40: D={b.dim}", flush=True)
+        assert L.ed_basis_terms_bytes(b.handle) == 0
+        states = b.states_device()
+        x = vec.hashed_amplitudes_torch(states, salt=1, complex_=False)
+        del states
+        torch.cuda.empty_cache()
+        few = b.lanczos(w.J, x, 4)                    # searched; the vectors stay with the basis
+        y = b.apply(w.J, x)
+        free, held = torch.cuda.mem_get_info()[0], b.info()["device_bytes"]
+        most = b.lanczos(w.J, x, 16)
+        fill = torch.empty(torch.cuda.mem_get_info()[0] - (80 << 30), dtype=torch.uint8, device="cuda")
+        some = b.lanczos(w.J, x, 8, want_psi0=True)   # 16 steps in two passes
+        psi0 = some["psi0"]
+        hp = b.apply(w.J, psi0)
+        del fill
+        J2 = w.J.copy()
+        J2[0] = np.nextafter(J2[0], 2.0)
+        other = b.lanczos(J2, x, 16)
+        assert torch.equal(y, b.apply(w.J, x))
+        torch.cuda.empty_cache()
+        assert L.ed_basis_terms_bytes(b.handle) == 0 and b.info()["device_bytes"] == held
+        b.release_terms()
+        s = b.lanczos(w.J, x, 16)
+        for r, n in ((few, 4), (most, 16), (some, 8), (other, 16)):
+            assert r["n_done"] == n
+            assert np.abs(r["alpha"][:n] - s["alpha"][:n]).max() <= 1e-9
+            assert np.abs(r["beta"][:n - 1] - s["beta"][:n - 1]).max() <= 1e-9
+        assert abs(float(torch.dot(psi0, hp)) - some["eigenvalues"][0]) <= 1e-9
+        assert torch.cuda.mem_get_info()[0] >= free - 2 * x.numel() * 8 - (1 << 30)
+    finally:
+        b.close()
+
+
 def test_refusals_and_release():
     from paper_1804_05028_amd import _lib as L
     from paper_1804_05028_amd import ed
