@@ -216,7 +216,7 @@ void ed_free_basis(ed_basis_t *b);
  * at most 1/16 of the device's memory and half of what is free (hash-slot
  * index; row index and coefficient class must fit the 32 bits); H.v, Lanczos
  * and adjoint then read it instead of searching, with the same results bit for
- * bit.  For a larger sector, a Lanczos call of 16 steps or more (counting both
+ * bit.  For a larger sector, a Lanczos call of 8 steps or more (counting both
  * passes where psi0 is asked for) stores terms while it lasts, in up to half
  * of the memory that is then free: all, or those of the first rows.
  * ed_basis_terms_bytes: device memory the basis keeps for it (0: none).

@@ -1823,11 +1823,11 @@ static void launch_lz_update(const ed_basis *b, int vgrid, double *w, const doub
 }
 
 // Steps from which a Lanczos call stores the terms of a sector whose table is
-// too large to keep.  40-site square, 130 of 142 GB: 0.9 s for the search, up
-// to 3.9 s for an allocation that has to wait until the freed pages are cleared
-// (29 ms per GB), against 0.40 s saved per step (766 -> 366 ms; 20 steps 15.3
-// -> 8.1 s).
-constexpr int kStoreSteps = 16;
+// too large to keep.  40-site square, 130 of 142 GB: 0.9 s for the search
+// against 0.40 s saved per step (766 -> 366 ms; 20 steps 15.3 -> 8.1 s), so
+// that 3 steps pay; but a later allocation may have to wait until the freed
+// pages are cleared (29 ms per GB, 3.9 s), which 12 steps pay.
+constexpr int kStoreSteps = 8;
 
 // the rows, overwritten by the amplitudes of real sectors, for the search of the terms
 __global__ void k_slots_rows(const uint32_t *slot_of, char *slots, int slot_bytes, int64_t D)

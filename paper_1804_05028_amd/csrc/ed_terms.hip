@@ -234,25 +234,25 @@ __device__ __forceinline__ void add_part(const TermsLds<CPLX> &tl, const uint4 (
     }
 }
 
+template <bool CPLX, bool FERMI>
+__device__ __forceinline__ double diagonal(const TermsLds<CPLX> &tl, int nb, uint64_t e, double anti, double jsq)
+{
+    if (!FERMI) return jsq - anti;
+    const uint64_t s = e & kStateMask;
+    double d = 0.0;
+    for (int k = 0; k < nb; ++k) {
+        const uint64_t bm = tl.bonds[k].mask;
+        if ((s & bm) == bm) d += tl.bonds[k].jzhalf;
+    }
+    return d;
+}
+
 // y_i from the finished sums; returns Re(conj(x_i) y_i) in MODE 2
-template <bool CPLX, int MODE, bool FERMI>
-__device__ __forceinline__ double finish_row(const TermsLds<CPLX> &tl, int nb, uint64_t e, double ar, double ai, double anti,
-                                             typename Scalar<CPLX>::T xi, typename Scalar<CPLX>::T vp, const LzState &lz,
-                                             double jsq, typename Scalar<CPLX>::T *y)
+template <bool CPLX, int MODE>
+__device__ __forceinline__ double finish_row(double rs, double ar, double ai, double d, typename Scalar<CPLX>::T xi,
+                                             typename Scalar<CPLX>::T vp, const LzState &lz, typename Scalar<CPLX>::T *y)
 {
     const double beta_prev = lz.beta_prev, inv = lz.inv, inv_prev = lz.inv_prev;
-    double d;
-    if (FERMI) {
-        const uint64_t s = e & kStateMask;
-        d = 0.0;
-        for (int k = 0; k < nb; ++k) {
-            const uint64_t bm = tl.bonds[k].mask;
-            if ((s & bm) == bm) d += tl.bonds[k].jzhalf;
-        }
-    } else {
-        d = jsq - anti;
-    }
-    const double rs = tl.rsqrt[e >> kNormShift];
     double dot = 0.0;
     typename Scalar<CPLX>::T out;
     if constexpr (CPLX) {
@@ -327,7 +327,9 @@ __device__ __forceinline__ double terms_row(const TermsLds<CPLX> &tl, const Term
 #pragma unroll
         for (int u = 0; u < U; ++u) sl.w[u] = nx[u];
     }
-    return sl.ok ? finish_row<CPLX, MODE, FERMI>(tl, nb, sl.e, ar, ai, anti, sl.xi, sl.vp, lz, jsq, y + sl.i) : 0.0;
+    return sl.ok ? finish_row<CPLX, MODE>(tl.rsqrt[sl.e >> kNormShift], ar, ai, diagonal<CPLX, FERMI>(tl, nb, sl.e, anti, jsq),
+                                          sl.xi, sl.vp, lz, y + sl.i)
+                 : 0.0;
 }
 
 // H.v from the stored terms: a coalesced read of the words and a gather of
@@ -527,33 +529,76 @@ int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *v
 // ---------------------------------------------------------------------------
 // Lanczos of a sector whose scaled vector fits LDS (terms_small): one block
 // does the whole iteration, its vectors in registers, two block sums per step
-// in place of kernels.  A step is bound by the latency of reading the words
-// from L2 through one compute unit and by the block sums: 1321 rows 7 us,
-// against 31 us with two kernels of a step replayed or launched.
+// in place of kernels.  The diagonal stays in a register, and the words of as
+// many slices as fit the rest of LDS stay there, 16 bits each (where class and
+// row fit them), instead of coming from L2 through one compute unit in every
+// step.  A step is then bound by its reads of LDS.  20-site square, J1-J2,
+// 1321 rows, 24 steps: 182 us (249 with the words read from L2, a sum by one
+// thread and three barriers per total), 4x4 square 85 us (120); two kernels per
+// step take 31 us each.
 // ---------------------------------------------------------------------------
 constexpr int kSmallThreads = 1024;
+constexpr int kSmallSlices = 64;
+
+// the wave's sum, in lane 63
+__device__ __forceinline__ double wave_sum_last(double v)
+{
+    // in registers, where __shfl_xor goes through LDS: row_shr 1, 2, 4, 8 within 16 lanes, then row_bcast 15 and 31
+    auto from = [&](auto ctrl, auto rows) {
+        const long long b = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)b, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+        v += __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+    };
+    using all = std::integral_constant<int, 0xf>;
+    from(std::integral_constant<int, 0x111>{}, all{});
+    from(std::integral_constant<int, 0x112>{}, all{});
+    from(std::integral_constant<int, 0x114>{}, all{});
+    from(std::integral_constant<int, 0x118>{}, all{});
+    from(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+    from(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+    return v;
+}
+
 template <bool CPLX, bool FERMI>
 __global__ void __launch_bounds__(kSmallThreads)
     k_terms_lanczos_small(DevModel dm, TermsDev td, const uint64_t *__restrict__ states, int D,
                           const typename Scalar<CPLX>::T *__restrict__ v0, int n_steps, double tol, double *alpha, double *beta,
-                          LzState *state, typename Scalar<CPLX>::T *psi0, const double *svec, double jsq)
+                          LzState *state, typename Scalar<CPLX>::T *psi0, const double *svec, double jsq, int room, int words_at)
 {
     using T = typename Scalar<CPLX>::T;
     constexpr int R = CPLX ? 2 : 4;   // rows of a thread (terms_small)
-    constexpr int U = 3;
+    constexpr int U = CPLX ? 2 : 3, H = 2;
     extern __shared__ __align__(16) double lds_d[];
-    __shared__ double sh[kSmallThreads / kWave + 1];
+    constexpr int kWaves = kSmallThreads / kWave;
+    __shared__ __align__(16) double sh[2][kWaves];
+    __shared__ int first[kSmallSlices + 1];   // groups before every slice
     T *xs = (T *)lds_d;
+    uint2 *kept = (uint2 *)(lds_d + words_at);   // room groups of 64 x 4 words of 16 bits
     const TermsLds<CPLX> tl = stage_terms<CPLX, FERMI>(dm, td, lds_d + ((((size_t)D + 1) * (CPLX ? 2 : 1) + 1) & ~(size_t)1));
-    const double *sqrts = (const double *)(dm.blob + dm.off_div);
+    double *sqrts = lds_d + words_at - dm.n_div;
+    for (int k = threadIdx.x; k < dm.n_div; k += kSmallThreads) sqrts[k] = ((const double *)(dm.blob + dm.off_div))[k];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t none = (uint32_t)(td.n_cls - 1) << td.ibits | (uint32_t)D;
     auto gather = [&](uint32_t j) { return xs[j]; };
+    auto uniform = [](int n) { return __builtin_amdgcn_readfirstlane(n); };
+    // sums over the block in a fixed order, one barrier each: the two buffers
+    // take turns
+    int turn = 0;
     auto total = [&](double a) {
-        const double t = block_sum(a, sh);
-        if (threadIdx.x == 0) sh[kSmallThreads / kWave] = t;
+        const double t = wave_sum_last(a);
+        double *part = sh[turn];
+        turn ^= 1;
+        if (lane == kWave - 1) part[threadIdx.x / kWave] = t;
         __syncthreads();
-        return sh[kSmallThreads / kWave];
+        double p[kWaves];
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) p[k] = part[k];
+#pragma unroll
+        for (int o = 1; o < kWaves; o *= 2)
+#pragma unroll
+            for (int k = 0; k < kWaves; k += 2 * o) p[k] += p[k + o];
+        return p[0];
     };
     auto times = [](T v, double f) {
         if constexpr (CPLX)
@@ -567,21 +612,51 @@ __global__ void __launch_bounds__(kSmallThreads)
         else
             return v * v;
     };
+    if (threadIdx.x < kSmallSlices) {
+        int n = threadIdx.x < td.n_slices ? (int)td.cnt[threadIdx.x] : 0;
+        for (int o = 1; o < kSmallSlices; o *= 2) {
+            const int m = __shfl_up(n, o, 64);
+            if (lane >= o) n += m;
+        }
+        first[threadIdx.x + 1] = n;
+        if (threadIdx.x == 0) first[0] = 0;
+    }
+    __syncthreads();
+    const int ib = 32 - __clz(D);   // bits of a row or D
+    const uint32_t im = (1u << td.ibits) - 1u;
+    const uint32_t none16 = ((uint32_t)(td.n_cls - 1) << ib | (uint32_t)D) * 0x10001u;
+    const bool one_class = td.n_cls == 2;   // and the padding
+    const double c0 = tl.cls[0];
     T v[R], prev[R], psi[R];
-    uint64_t e[R];
-    double sq[R], acc = 0.0;
+    uint32_t div = 0;   // the rows' stabiliser sizes, 8 bits each
+    double diag[R], acc = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = threadIdx.x + r * kSmallThreads;
         v[r] = prev[r] = psi[r] = T{};
-        e[r] = 0;
-        sq[r] = 0.0;
+        uint64_t e = 0;
         if (i < D) {
-            e[r] = states[i];
-            sq[r] = sqrts[e[r] >> kNormShift];
+            e = states[i];
+            div |= (uint32_t)(e >> kNormShift) << 8 * r;
             v[r] = v0[i];
         }
         acc += norm2(v[r]);
+        diag[r] = 0.0;
+        if (i - lane < D) {   // uniform: the wave's slice
+            const int sl = uniform(i / kWave), from = uniform(first[sl]), groups = uniform(first[sl + 1]) - from;
+            const uint4 *p = td.words + (td.off ? td.off[sl] : (uint64_t)sl * td.stride) * kWave + lane;
+            double anti = 0.0;
+            auto half = [&](uint32_t w) {
+                anti += tl.cls[(CPLX ? 4 : 2) * (w >> td.ibits) + (CPLX ? 2 : 1)];
+                return (w >> td.ibits << ib) | (w & im);
+            };
+            for (int g = 0; g < groups; ++g) {
+                const uint4 w = load_words(p + (size_t)g * kWave);
+                const uint32_t a = half(w.x), b = half(w.y), c = half(w.z), d = half(w.w);
+                if (from + groups <= room) kept[(from + g) * kWave + lane] = make_uint2(a | b << 16, c | d << 16);
+            }
+            diag[r] = diagonal<CPLX, FERMI>(tl, dm.nb, e, anti, jsq);
+        }
     }
     const double n2 = total(acc);
     LzState st{};
@@ -589,37 +664,68 @@ __global__ void __launch_bounds__(kSmallThreads)
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = times(v[r], n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0);
     if (threadIdx.x == 0) xs[D] = T{};
+    double keep_a = 0.0, keep_b = 0.0;
     while (!st.done) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i = threadIdx.x + r * kSmallThreads;
-            if (i < D) xs[i] = times(v[r], sq[r]);
+            if (i < D) xs[i] = times(v[r], sqrts[div >> 8 * r & 255u]);
         }
         __syncthreads();
         T w[R];
         double dot = 0.0;
+        const double sj = psi0 ? svec[st.j] : 0.0;
 #pragma unroll
         for (int r = 0; r < R; ++r) w[r] = T{};
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i = threadIdx.x + r * kSmallThreads;
             if (i - lane >= D) break;   // uniform: the wave's slice
-            const int64_t sl = i / kWave;
-            const int groups = (int)td.cnt[sl];
-            const uint4 *p = td.words + (td.off ? td.off[sl] : (uint64_t)sl * td.stride) * kWave + lane;
+            const int sl = uniform(i / kWave), from = uniform(first[sl]), groups = uniform(first[sl + 1]) - from;
             double ar = 0.0, ai = 0.0, anti = 0.0;
-            uint4 q[U], nx[U];
-            load_part<U>(q, p, 0, groups, none);
-            for (int g = 0; g < groups; g += U) {
-                load_part<U>(nx, p, g + U, groups, none);
-                add_part<CPLX, U>(tl, q, g, groups, td.ibits, gather, ar, ai, anti);
+            if (from + groups <= room) {
+                const uint2 *p = kept + from * kWave + lane;
+                const uint32_t hm = (1u << ib) - 1u;
+                for (int g = 0; g < groups; g += H) {
+                    uint2 q[H];
+                    T x[4 * H];
 #pragma unroll
-                for (int u = 0; u < U; ++u) q[u] = nx[u];
+                    for (int u = 0; u < H; ++u)
+                        if (g + u < groups) q[u] = p[(g + u) * kWave];
+                        else q[u] = make_uint2(none16, none16);
+                    auto each = [&](auto &&f) {
+#pragma unroll
+                        for (int u = 0; u < H; ++u) {
+                            f(4 * u, q[u].x & 0xffffu);
+                            f(4 * u + 1, q[u].x >> 16);
+                            f(4 * u + 2, q[u].y & 0xffffu);
+                            f(4 * u + 3, q[u].y >> 16);
+                        }
+                    };
+                    each([&](int k, uint32_t h) { x[k] = xs[h & hm]; });
+                    each([&](int k, uint32_t h) {
+                        if constexpr (CPLX) {
+                            const double2 c = *(const double2 *)(tl.cls + 4 * (h >> ib));
+                            add_term<true>(ar, ai, c.x, c.y, x[k].x, x[k].y);
+                        } else {
+                            add_term<false>(ar, ai, one_class ? (h >> ib ? 0.0 : c0) : tl.cls[2 * (h >> ib)], 0.0, x[k], 0.0);
+                        }
+                    });
+                }
+            } else {
+                const uint4 *p = td.words + (td.off ? td.off[sl] : (uint64_t)sl * td.stride) * kWave + lane;
+                uint4 q[U], nx[U];
+                load_part<U>(q, p, 0, groups, none);
+                for (int g = 0; g < groups; g += U) {
+                    load_part<U>(nx, p, g + U, groups, none);
+                    add_part<CPLX, U>(tl, q, g, groups, td.ibits, gather, ar, ai, anti);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) q[u] = nx[u];
+                }
             }
-            if (i < D) dot += finish_row<CPLX, 2, FERMI>(tl, dm.nb, e[r], ar, ai, anti, v[r], prev[r], st, jsq, &w[r]);
+            if (i < D) dot += finish_row<CPLX, 2>(tl.rsqrt[div >> 8 * r & 255u], ar, ai, diag[r], v[r], prev[r], st, &w[r]);
         }
         const double a = total(dot);
-        const double sj = psi0 ? svec[st.j] : 0.0;
         acc = 0.0;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -635,13 +741,21 @@ __global__ void __launch_bounds__(kSmallThreads)
             acc += norm2(w[r]);
         }
         const double b = sqrt(total(acc));
-        if (threadIdx.x == 0) {
-            alpha[st.j] = a;
-            beta[st.j] = b;
+        // coefficients are kept, not stored in every step: a barrier would wait
+        if (threadIdx.x == (st.j & (kSmallThreads - 1))) {
+            keep_a = a;
+            keep_b = b;
         }
         st.scale = fmax(st.scale, fmax(fabs(a), b));
         st.j += 1;
         st.done = b <= tol * st.scale || st.j >= n_steps;
+        if (st.done || (st.j & (kSmallThreads - 1)) == 0) {
+            const int from = (st.j - 1) & ~(kSmallThreads - 1);
+            if (from + (int)threadIdx.x < st.j) {
+                alpha[from + threadIdx.x] = keep_a;
+                beta[from + threadIdx.x] = keep_b;
+            }
+        }
         st.beta_prev = b;
         const double inv = st.done ? 0.0 : 1.0 / b;
 #pragma unroll
@@ -670,11 +784,20 @@ int terms_lanczos_small(const ed_basis *b, const void *v0, int n_steps, double t
                         void *psi0, const double *svec, double jsq, void *stream)
 {
     const bool c = b->dm.is_complex;
-    const size_t lds = ((((size_t)b->db.dim + 1) * (c ? 16 : 8) + 15) & ~(size_t)15) + terms_lds_bytes(b);
+    const size_t tables = (((((size_t)b->db.dim + 1) * (c ? 16 : 8) + 15) & ~(size_t)15) + terms_lds_bytes(b) + 7 +
+                           (size_t)b->dm.n_div * 8) & ~(size_t)7;
+    // groups of words kept in LDS (512 bytes each), beside a few hundred static bytes
+    int cbits = 1, ib = 1;
+    while ((1 << cbits) < b->terms.n_cls) ++cbits;
+    while ((1ll << ib) <= b->db.dim) ++ib;
+    const size_t limit = lds_limit() - 1024;
+    const int64_t most = (int64_t)b->terms.n_slices * ((b->dm.nb + 3) / 4);
+    const int room = cbits + ib > 16 || limit < tables ? 0 : (int)std::min<int64_t>((int64_t)(limit - tables) / 512, most);
+    const size_t lds = tables + (size_t)room * 512;
 #define ED_SMALL(C, F) \
     hipLaunchKernelGGL((k_terms_lanczos_small<C, F>), dim3(1), dim3(kSmallThreads), lds, (hipStream_t)stream, b->dm, \
                        terms_dev(b), b->db.states, (int)b->db.dim, (const Scalar<C>::T *)v0, n_steps, tol, alpha, beta, \
-                       (LzState *)state, (Scalar<C>::T *)psi0, svec, jsq)
+                       (LzState *)state, (Scalar<C>::T *)psi0, svec, jsq, room, (int)(tables / 8))
     if (c) {
         if (b->fermion) ED_SMALL(true, true);
         else ED_SMALL(true, false);

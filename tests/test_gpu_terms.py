@@ -213,6 +213,52 @@ def test_terms_of_a_lanczos_call():
         b.close()
 
 
+def _square20(k, n_up):
+    c = lat.square((4, 2), (-2, 4), j2=True, rotations=False, superlattice=wl.SQ_2X2)
+    return wl.Workload("square20", c, lat.characters(c, k), n_up, wl.couplings_by_kind(c.bond_kind, [1.0, 0.5]))
+
+
+def _identity16(n_up):
+    """32 bond orbits of the 4x4 square: 33 classes, 6 bits."""
+    c = lat.square((4, 0), (0, 4), rotations=False, superlattice=wl.SQ_2X2)
+    c.perm, c.flip = c.perm[:1], c.flip[:1]
+    return wl.Workload("square16", c, np.ones(1, complex), n_up, np.linspace(0.5, 1.5, c.n_bonds))
+
+
+# words of the one-launch Lanczos: 16 bits in LDS for all slices, for some
+# (31 slices of about 12 groups), or for none (class and row take 17 bits)
+ONE_LAUNCH = [("all", lambda: _identity16(3), 24), ("some", lambda: _square20(0, 6), 24), ("none", lambda: _identity16(4), 24),
+              ("complex_all", lambda: _chain(20, 4, 1, 6), 24), ("complex_none", lambda: _square20(1, 6), 24),
+              ("more_steps_than_threads", lambda: _square20(0, 6), 1100)]
+
+
+@pytest.mark.parametrize("name,make,steps", ONE_LAUNCH, ids=[c[0] for c in ONE_LAUNCH])
+def test_lanczos_in_one_launch(name, make, steps):
+    """Against the steps of the searching kernels: the first 12 coefficients
+    differ by a few times sqrt(rows) eps of terms of order 10 each step, the
+    extremal Ritz values stay with the sector's (converged after 1100 steps)."""
+    from paper_1804_05028_amd import ed
+    w = make()
+    b = ed.Basis.from_workload(w)
+    try:
+        print(f"[terms] {name}: D={b.dim}", flush=True)
+        assert b.dim <= (2048 if b.is_complex else 4096)
+        x, _ = _vectors(b)
+        r, again = b.lanczos(w.J, x, steps, want_psi0=True), b.lanczos(w.J, x, steps)
+        assert np.array_equal(r["alpha"], again["alpha"]) and np.array_equal(r["beta"], again["beta"])
+        b.release_terms()
+        s = b.lanczos(w.J, x, steps)
+        assert r["n_done"] == s["n_done"] == steps
+        assert np.abs(r["alpha"][:12] - s["alpha"][:12]).max() <= 1e-11
+        assert np.abs(r["beta"][:12] - s["beta"][:12]).max() <= 1e-11
+        if steps > 1000:
+            for k in (0, -1):
+                assert abs(r["eigenvalues"][k] - s["eigenvalues"][k]) <= 1e-10
+            assert torch.linalg.vector_norm(b.apply(w.J, r["psi0"]) - s["eigenvalues"][0] * r["psi0"]) <= 1e-7
+    finally:
+        b.close()
+
+
 def test_refusals_and_release():
     from paper_1804_05028_amd import _lib as L
     from paper_1804_05028_amd import ed
