@@ -288,37 +288,25 @@ def bond_orbits_from(perm, bonds):
     return orbit
 
 
-def _mean_over(orbit, v):
-    """orbit_mean of a float64 numpy vector, in the same order of summation."""
-    sums = np.bincount(orbit, weights=v)
-    return (sums / np.bincount(orbit))[orbit]
-
-
 class _ApplyH(torch.autograd.Function):
-    """y = H(Jbar) x with the hand-written adjoint: dx = H gy, dJbar_b = Re(gy^H H_b x).
-    With orbit (numpy), J is averaged over bond orbits first; that average is
-    its own adjoint."""
+    """y = H(Jbar) x with the hand-written adjoint: dx = H gy, dJbar_b = Re(gy^H H_b x)."""
 
     @staticmethod
-    def forward(ctx, J, x, basis, orbit=None):
-        Jn = J.detach().cpu().numpy()
-        y = basis.apply(Jn if orbit is None else _mean_over(orbit, Jn), x.detach().contiguous())
-        ctx.basis, ctx.orbit = basis, orbit
-        ctx.save_for_backward(J, x)
+    def forward(ctx, Jbar, x, basis):
+        y = basis.apply(Jbar.detach().cpu().numpy(), x.detach().contiguous())
+        ctx.basis = basis
+        ctx.save_for_backward(Jbar, x)
         return y
 
     @staticmethod
     def backward(ctx, gy):
-        J, x = ctx.saved_tensors
-        basis, orbit = ctx.basis, ctx.orbit
+        Jbar, x = ctx.saved_tensors
+        basis = ctx.basis
         need_J, need_x = ctx.needs_input_grad[0], ctx.needs_input_grad[1]
-        Jn = J.detach().cpu().numpy()
-        gx, gJ = basis.backward(Jn if orbit is None else _mean_over(orbit, Jn), x.detach().contiguous(), gy.contiguous(),
+        gx, gJ = basis.backward(Jbar.detach().cpu().numpy(), x.detach().contiguous(), gy.contiguous(),
                                 want_gx=need_x, want_gJ=need_J)
-        if need_J and orbit is not None:
-            gJ = _mean_over(orbit, gJ)
-        gJt = torch.from_numpy(gJ).to(J.dtype) if need_J else None
-        return gJt, gx, None, None
+        gJt = torch.from_numpy(gJ).to(Jbar.dtype) if need_J else None
+        return gJt, gx, None
 
 
 def orbit_mean(J, orbit):
@@ -341,11 +329,5 @@ def apply_H(basis: Basis, J, x, orbit=None):
     if not torch.is_tensor(J):
         J = torch.as_tensor(np.asarray(J, np.float64))
     if orbit is not None:
-        o = orbit if isinstance(orbit, np.ndarray) else None
-        if (o is not None and o.dtype.kind in "iu" and o.ndim == 1 and o.size and o.min() >= 0 and J.dtype == torch.float64
-                and not J.is_cuda and tuple(J.shape) == o.shape):
-            # the average inside the function: as a graph of its own it cost
-            # 56 us per forward and backward, more than the kernels of a small sector
-            return _ApplyH.apply(J, x, basis, o)
         J = orbit_mean(J, orbit)
     return _ApplyH.apply(J, x, basis)

@@ -349,28 +349,3 @@ def test_batched_stored_terms_equal_search(name, ws, tune):
                 assert np.abs(r["alpha"][k, :n] - s["alpha"][k, :n]).max(initial=0.0) <= 1e-11
     finally:
         mb.close()
-
-
-def test_orbit_average_inside_the_function():
-    """apply_H averages J over orbits inside its autograd function where it can;
-    value and gradients equal those of orbit_mean as a graph of its own."""
-    from paper_1804_05028_amd import ed
-    w = _square24(0)
-    b = ed.Basis.from_workload(w)
-    try:
-        o = ed.bond_orbits_from(w.cluster.perm, w.cluster.bonds)
-        J0 = torch.as_tensor(vec.random_couplings(len(o), 3))
-        x0, gy = _vectors(b)
-        got = []
-        for how in range(2):
-            J, x = J0.clone().requires_grad_(True), x0.clone().requires_grad_(True)
-            y = ed.apply_H(b, J, x, o) if how == 0 else ed.apply_H(b, ed.orbit_mean(J, o), x)
-            y.backward(gy)
-            got.append((y.detach(), J.grad, x.grad))
-        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][2], got[1][2])
-        assert (got[0][1] - got[1][1]).abs().max() <= 4e-16 * len(o) * got[1][1].abs().max()
-        # forms the function does not take: the graph
-        y = ed.apply_H(b, J0, x0, list(o))
-        assert torch.equal(y, got[0][0])
-    finally:
-        b.close()
