@@ -255,6 +255,37 @@ def test_tridiag_eigh_matches_numpy():
         assert abs(abs(vec @ V[:, 0]) - 1) < 1e-10
 
 
+@pytest.mark.parametrize("m", list(range(1, 18)) + [24, 25])
+def test_tridiag_eigenvalues_side_by_side(m):
+    """Eigenvalues come eight at a time; each as bisected alone, bit for bit:
+    here in Python, with the same operations."""
+    rng = np.random.default_rng(m)
+    tiny = np.finfo(np.float64).tiny
+    for scale in (1.0, 1e-9, 0.0):
+        a, b = rng.standard_normal(m), scale * np.abs(rng.standard_normal(m - 1))
+        b2 = b * b
+        r = np.append(0.0, np.abs(b)) + np.append(np.abs(b), 0.0)
+        lo, hi = min(a[0], (a - r).min()), max(a[0], (a + r).max())
+        span = max(hi - lo, max(abs(hi), abs(lo)) * np.finfo(np.float64).eps) + tiny
+        lo, hi = lo - 1e-12 * span, hi + 1e-12 * span
+        want = []
+        for k in range(m):
+            x, y = lo, hi
+            for _ in range(200):
+                mid = 0.5 * (x + y)
+                if mid <= x or mid >= y:
+                    break
+                q, count = 1.0, 0
+                for j in range(m):
+                    q = a[j] - mid - (b2[j - 1] / q if j else 0.0)
+                    q = -16 * tiny if q == 0.0 else q
+                    count += q < 0.0
+                x, y = (x, mid) if count > k else (mid, y)
+            want.append(0.5 * (x + y))
+        ev, _ = L.ed_tridiag_eigh(a, b, want_vec=False)
+        assert np.array_equal(ev, np.array(want))
+
+
 def test_validate_limits_and_malformed_input():
     c = lat.chain(40, superlattice_period=2)
     _expect("ED_ERR_UNSUPPORTED", lambda: L.ed_tables_create(L.ModelArrays(40, c.bonds, 2, c.perm, c.flip)))
