@@ -1,8 +1,9 @@
 """Benchmark: symmetry-sector H.v throughput inside FP64 Lanczos on one MI355X.
 
-A step is one Lanczos iteration of the sector Hamiltonian: one fused H.v
-(representative search, index lookup, bond-loop gather) plus the FP64 vector
-updates, all in the library's HIP kernels.  value = H.v terms per second =
+A step is one Lanczos iteration of the sector Hamiltonian: one fused H.v (from
+stored terms, or with a representative search and an index lookup per term)
+plus the FP64 vector updates, all in the library's HIP kernels.  Terms that a
+Lanczos call stores for itself are stored within the timed call.  value = H.v terms per second =
 (D + kept off-diagonal terms) per H.v x steps / elapsed seconds, with every
 input already resident in HBM.  The basis build is timed and reported
 separately.
@@ -34,26 +35,25 @@ HBM_PEAK_GBS = 8000.0
 # one 8 B index probe.  Complex sectors add 8 B to x_i, x_j and y_i.
 BYTES_ROW_REAL, BYTES_TERM_REAL = 25.0, 17.0
 BYTES_ROW_CPLX, BYTES_TERM_CPLX = 41.0, 25.0
+# the same for a basis that stores its terms: the state, x_i and y_i; a 4-byte
+# word and the scaled x_j
+BYTES_STORED = {False: (24.0, 12.0), True: (40.0, 20.0)}
 
 # Measured HBM bytes per H.v launch: FETCH_SIZE and WRITE_SIZE runs of
 # rocprofv3, scaled by what the same counters read for a plain device copy of
 # known size (x2.0 and x1.0).  A figure is valid only for the kernel sources it
-# was taken on (sha256 of ed_kernels.hip + ed_device.hpp + ed_internal.hpp,
-# concatenated) and the same configuration; otherwise traffic is reported as
+# was taken on (sha256 of ed_kernels.hip + ed_terms.hip + ed_device.hpp +
+# ed_internal.hpp, concatenated) and the same configuration; otherwise traffic is reported as
 # null.
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1804_05028_amd", "csrc", f)
-               for f in ("ed_kernels.hip", "ed_device.hpp", "ed_internal.hpp")]
+               for f in ("ed_kernels.hip", "ed_terms.hip", "ed_device.hpp", "ed_internal.hpp")]
+KERNEL_DIGEST = "b825e2ee8c81ae21680036402c8d1e444b89a1720857b744a5b98737db06e5ed"
 MEASURED_TRAFFIC = {
     # (workload, n_sublat, index, chunk_bits): (kernel sha256, fetch bytes, write bytes, profile)
-    ("square40_j1j2", 4, "hash-slot", 5): (
-        "65f865045fddf0948f6d1fd330e70d6f17e56c8eb5eeaf09e04b20826133bfd4", 4.69342e+12, 3.44728e+09,
-        "profiles/k_apply_square40_j1j2_ns4.md"),
-    ("triangular36_k1", 4, "hash-slot", 5): (
-        "65f865045fddf0948f6d1fd330e70d6f17e56c8eb5eeaf09e04b20826133bfd4", 1.92584e+12, 4.03337e+09,
-        "profiles/k_apply_triangular36_k1_complex.md"),
-    ("triangular36_tV", 4, "hash-slot", 5): (
-        "65f865045fddf0948f6d1fd330e70d6f17e56c8eb5eeaf09e04b20826133bfd4", 3.03372e+11, 3.36083e+08,
-        "profiles/k_apply_fermions_triangular36_tV.md"),
+    ("square40_j1j2", 4, "hash-slot", 5): (KERNEL_DIGEST, 4.69361e+12, 3.44728e+09, "profiles/k_apply_square40_j1j2_ns4.md"),
+    ("triangular36_k1", 4, "hash-slot", 5): (KERNEL_DIGEST, 1.97794e+12, 4.03337e+09, "profiles/k_apply_triangular36_k1_complex.md"),
+    ("triangular36_tV", 4, "hash-slot", 5): (KERNEL_DIGEST, 7.59186e+10, 3.57121e+08, "profiles/k_terms_apply.md"),
+    ("triangular36", 4, "hash-slot", 3): (KERNEL_DIGEST, 2.12459e+10, 8.94871e+07, "profiles/k_terms_apply.md"),
 }
 
 
@@ -328,9 +328,7 @@ def time_adjoint(basis, J, x, reps, hv_ms):
           flush=True)
     return {"backward_ms": full_ms, "per_bond_sums_ms": gj_ms, "hv_ms": hv_ms, "backward_over_hv": full_ms / hv_ms,
             "n_bonds": int(basis.n_bonds),
-            "path": ("one fused pass for gx and the per-bond sums (real sector, hash slots; its 32-byte adjoint "
-                     "slot table allocated by the untimed first call)") if not basis.is_complex
-            else "H gy and the per-bond sums as two passes"}
+            "path": "one fused pass for gx and the per-bond sums, from the stored terms where the basis holds them"}
 
 
 def vec_seed_target():
@@ -484,7 +482,7 @@ def main():
     ap.add_argument("--table-entry-bytes", type=int, default=0)
     ap.add_argument("--search-mode", type=int, default=0, help="1 one-stage, 2 two-stage representative search")
     ap.add_argument("--lanczos-direct", action="store_true",
-                    help="launch the Lanczos step kernels directly instead of replaying a HIP graph")
+                    help="ed_tuning_t.lanczos_direct = 1 (the Lanczos step kernels are launched directly either way)")
     ap.add_argument("--block-threads", type=int, default=0)
     ap.add_argument("--blocks-per-cu", type=int, default=0)
     ap.add_argument("--hv-reps", type=int, default=5, help="extra timed H.v launches for the roofline")
@@ -541,6 +539,7 @@ def main():
     torch.cuda.synchronize()
     build_s = time.perf_counter() - t0
     info = basis.info()
+    stored = ed.L.ed_basis_terms_bytes(basis.handle)
     D = basis.dim
     _, kept, dropped = basis.stats()
     terms = D + kept
@@ -593,6 +592,9 @@ def main():
 
     cplx = basis.is_complex
     br, bt = (BYTES_ROW_CPLX, BYTES_TERM_CPLX) if cplx else (BYTES_ROW_REAL, BYTES_TERM_REAL)
+    if stored:
+        br, bt = BYTES_STORED[cplx]
+    kernel = "k_terms_apply" if stored else "k_apply"
     alg_bytes = D * br + kept * bt
     achieved = alg_bytes / (kernel_ms * 1e-3) / 1e9
     index_name = ["hash-slot", "limits"][info["index_mode"]]
@@ -605,16 +607,16 @@ def main():
                                    "not measured in this run") if meas else None,
                 "traffic_gbs": round(traffic / (kernel_ms * 1e-3) / 1e9, 1) if traffic else None,
                 "lines_per_term": round(meas[0] / 128.0 / kept, 3) if meas and kept else None,
-                "kernel": "k_apply (fused H.v)", "alg_bytes_per_launch": alg_bytes,
+                "kernel": f"{kernel} (fused H.v)", "stored_terms_bytes": stored, "alg_bytes_per_launch": alg_bytes,
                 "alg_bytes_per_unit": {"row": br, "kept_term": bt},
                 "launch_ms": round(kernel_ms, 3), "scatter_ms": round(pack_ms, 3),
-                "timing": "HIP events recorded on the launch stream around the k_apply kernel, mean of "
+                "timing": f"HIP events recorded on the launch stream around the {kernel} kernel, mean of "
                           f"{args.hv_reps} launches"}
 
     int_ops = MEASURED_INT_OPS.get(key) if traffic else None
     del x, y, res
     probe = random_read_probe(slot_bytes=32 if cplx else 16)
-    if meas:
+    if meas and not stored:
         # line requests the H.v kernel issues per second, against the probe's rate
         kernel_lines = meas[0] / 128.0 / (kernel_ms * 1e-3)
         probe["kernel_line_requests_per_s"] = round(kernel_lines, 1)

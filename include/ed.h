@@ -94,7 +94,8 @@ typedef struct {
 /* Optional tuning; zero fields mean "choose automatically". */
 typedef struct {
     int32_t limits_bits;    /* index_mode 1: state bits after the top block used in the Limits key    */
-    int32_t index_mode;     /* 0 = hash-slot index with the input amplitude stored beside the key;
+    int32_t index_mode;     /* 0 = hash-slot index with the input amplitude stored beside the key,
+                               read where no terms are stored (see ed_basis_terms_bytes);
                                1 = the paper's Limits ranges plus binary search of the sorted states    */
     int32_t block_threads;  /* threads per block of the H.v kernel (64..1024, multiple of 64)            */
     int32_t blocks_per_cu;  /* persistent blocks per compute unit of the H.v kernel                      */

@@ -10,6 +10,10 @@
 //               vector is scattered into the slots before each H.v, so that one
 //               16-byte read usually returns the index check, the norm and the
 //               amplitude of a target together.
+//   terms       where they fit (ed_terms.hip), one word per off-diagonal term:
+//               H.v, Lanczos and adjoint then read these and a dense scaled
+//               input instead of searching; the kernels here that search serve
+//               the other sectors, bit for bit alike.
 //   limits[K+1] uint32: the paper's Limits ranges (index mode 1): begin offset
 //               of every key (top-block rank, next q bits), then binary search.
 //   x, y[D]     double (or double2), ascending-representative order.
@@ -1824,9 +1828,10 @@ static void launch_lz_update(const ed_basis *b, int vgrid, double *w, const doub
 
 // Steps from which a Lanczos call stores the terms of a sector whose table is
 // too large to keep.  40-site square, 130 of 142 GB: 0.9 s for the search
-// against 0.40 s saved per step (766 -> 366 ms; 20 steps 15.3 -> 8.1 s), so
-// that 3 steps pay; but a later allocation may have to wait until the freed
-// pages are cleared (29 ms per GB, 3.9 s), which 12 steps pay.
+// against 0.40 s saved per step (766 -> 366 ms; 20 steps 15.3 -> 8.1 s, also
+// one call after the other), so that 3 steps pay; but where free memory runs
+// short, a later allocation waits until the freed pages are cleared (29 ms per
+// GB, 3.8 s), which 12 steps pay.
 constexpr int kStoreSteps = 8;
 
 // the rows, overwritten by the amplitudes of real sectors, for the search of the terms
@@ -1836,7 +1841,9 @@ __global__ void k_slots_rows(const uint32_t *slot_of, char *slots, int slot_byte
         *(uint64_t *)(slots + (size_t)slot_of[j] * slot_bytes + 8) = (uint64_t)j;
 }
 
-// half of the free memory
+// In half of the free memory, so that the next call finds as much that need not
+// be cleared first: in three quarters all 142 GB fit and a step takes 0.31 s,
+// but 20 steps right after such a call take 11.1 s.
 static int store_terms_for_call(ed_basis *b, hipStream_t st)
 {
     size_t free_b = 0, total_b = 0;

@@ -29,7 +29,7 @@ class Basis:
     an optional dict with the fields of ed_tuning_t (all 0 = automatic):
     index_mode, limits_bits, block_threads, blocks_per_cu, chunk_bits,
     hash_load_pct, table_entry_bytes, search_mode (1 one-stage, 2 two-stage
-    representative search) and lanczos_direct (1 = no graph replay).
+    representative search) and lanczos_direct (0 or 1: the steps are launched either way).
     """
 
     _build = staticmethod(L.ed_build_basis)
