@@ -47,7 +47,7 @@ BYTES_STORED = {False: (24.0, 12.0), True: (40.0, 20.0)}
 # null.
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1804_05028_amd", "csrc", f)
                for f in ("ed_kernels.hip", "ed_terms.hip", "ed_device.hpp", "ed_internal.hpp")]
-KERNEL_DIGEST = "b825e2ee8c81ae21680036402c8d1e444b89a1720857b744a5b98737db06e5ed"
+KERNEL_DIGEST = "f010e4706167bc49b126f7e6ba108888d0c10cffdf8415b6ac7145b4e6e6e59e"
 MEASURED_TRAFFIC = {
     # (workload, n_sublat, index, chunk_bits): (kernel sha256, fetch bytes, write bytes, profile)
     ("square40_j1j2", 4, "hash-slot", 5): (KERNEL_DIGEST, 4.69361e+12, 3.44728e+09, "profiles/k_apply_square40_j1j2_ns4.md"),

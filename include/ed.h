@@ -219,7 +219,8 @@ void ed_free_basis(ed_basis_t *b);
  * and adjoint then read it instead of searching, with the same results bit for
  * bit.  For a larger sector, a Lanczos call of 8 steps or more (counting both
  * passes where psi0 is asked for) stores terms while it lasts, in up to half
- * of the memory that is then free: all, or those of the first rows.
+ * of the memory that is then free: all, or those of the first rows (on which
+ * the last bits of alpha and beta depend).
  * ed_basis_terms_bytes: device memory the basis keeps for it (0: none).
  * ed_basis_release_terms gives that memory back; later calls search again.
  * Synchronises the device.

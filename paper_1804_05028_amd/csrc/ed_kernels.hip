@@ -1834,13 +1834,6 @@ static void launch_lz_update(const ed_basis *b, int vgrid, double *w, const doub
 // GB, 3.8 s), which 12 steps pay.
 constexpr int kStoreSteps = 8;
 
-// the rows, overwritten by the amplitudes of real sectors, for the search of the terms
-__global__ void k_slots_rows(const uint32_t *slot_of, char *slots, int slot_bytes, int64_t D)
-{
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x)
-        *(uint64_t *)(slots + (size_t)slot_of[j] * slot_bytes + 8) = (uint64_t)j;
-}
-
 // In half of the free memory, so that the next call finds as much that need not
 // be cleared first: in three quarters all 142 GB fit and a step takes 0.31 s,
 // but 20 steps right after such a call take 11.1 s.
@@ -1848,10 +1841,6 @@ static int store_terms_for_call(ed_basis *b, hipStream_t st)
 {
     size_t free_b = 0, total_b = 0;
     if (b->db.index_mode != IDX_HASH || hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b < 2) return ED_OK;
-    const int64_t D = b->db.dim;
-    hipLaunchKernelGGL(k_slots_rows, dim3((unsigned)std::min<int64_t>((D + 255) / 256, 1 << 20)), dim3(256), 0, st,
-                       b->db.slot_of, b->db.slots, b->dm.is_complex ? 32 : 16, D);
-    HIP_TRY(hipGetLastError());
     return terms_build(b, st, nullptr, 0, free_b / 2);
 }
 

@@ -1239,6 +1239,14 @@ static int fill_ns(ed_basis *b, const uint16_t *cc, const uint16_t *orb, uint32_
     }
 }
 
+// the rows, overwritten by the amplitudes of real sectors since the basis was
+// built, for a search without the index
+__global__ void k_slots_rows(const uint32_t *slot_of, char *slots, int slot_bytes, int64_t D)
+{
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < D; j += (int64_t)gridDim.x * blockDim.x)
+        *(uint64_t *)(slots + (size_t)slot_of[j] * slot_bytes + 8) = (uint64_t)j;
+}
+
 static bool terms_possible(const ed_basis *b)
 {
     return b->want_terms && b->db.index_mode == 0 && b->db.dim >= 1 && b->t.nb >= 1;
@@ -1410,6 +1418,11 @@ int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_ele
     if (e == hipSuccess) e = hipMemcpyAsync(t.cls_chi, chi.data(), chi.size() * 8, hipMemcpyHostToDevice, st);
     if (e == hipSuccess && t.xs)
         e = hipMemsetAsync((char *)t.xs + vec - (b->dm.is_complex ? 16 : 8), 0, b->dm.is_complex ? 16 : 8, st);
+    if (e == hipSuccess && call_limit) {
+        hipLaunchKernelGGL(k_slots_rows, dim3((unsigned)std::min<int64_t>((D + 255) / 256, 1 << 20)), dim3(256), 0, st,
+                           b->db.slot_of, b->db.slots, b->dm.is_complex ? 32 : 16, D);
+        e = hipGetLastError();
+    }
     int rc = ED_OK;
     if (e == hipSuccess) {
         const uint32_t pad = (uint32_t)(t.n_cls - 1) << t.ibits | (uint32_t)D;
