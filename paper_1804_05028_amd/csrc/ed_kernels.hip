@@ -1450,6 +1450,11 @@ static int apply_impl(const ed_basis *b, const void *x, void *y, const void *vpr
     int grid, threads;
     size_t lds = b->dm.lds_total;
     launch_cfg(b, kern, lds, &grid, &threads);
+    // a complex slot is read as two loads of a line that has to stay in L2 from
+    // the first to the second: 16 waves per compute unit, also where more fit
+    // (36-site momentum sector: 404.5 ms, with 24 waves 411.4)
+    if (CPLX && INDEX == IDX_HASH && MODE == 0 && b->tuning.blocks_per_cu <= 0)
+        grid = std::min(grid, std::max(1024 / threads, 1) * num_cus());
     if (MODE == 2) {
         lds = std::max(lds, (size_t)threads * 8);
         grid = b->grid_blocks;   // fixed grid so the reductions are deterministic
