@@ -1141,7 +1141,8 @@ void terms_free(ed_basis *b)
 
 // One coefficient per orbit: couplings that differ in their last bits within an
 // orbit (the check allows 1e-12) run the searching kernels, which read them
-// bond by bond.
+// bond by bond.  The classes get the first bond's then, for a captured H.v that
+// reads stored terms when it is replayed.
 bool terms_couplings_equal(const ed_basis *b, const double *J)
 {
     std::vector<int> first(b->t.nb, -1);
@@ -1162,7 +1163,6 @@ int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream
     if (!t.words) return ED_OK;
     hipStream_t st = (hipStream_t)stream;
     t.couplings_ok = false;
-    if (!terms_couplings_equal(b, J) || !terms_couplings_equal(b, Jz)) return ED_OK;
     const int W = b->dm.is_complex ? 4 : 2;
     std::vector<double> tab((size_t)t.n_cls * W, 0.0);
     const int n_chi = (int)t.chi_vals.size() / 2;
@@ -1176,7 +1176,7 @@ int terms_couplings(ed_basis *b, const double *J, const double *Jz, void *stream
         }
     HIP_TRY(hipMemcpyAsync(t.cls, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
-    t.couplings_ok = true;
+    t.couplings_ok = terms_couplings_equal(b, J) && terms_couplings_equal(b, Jz);
     return ED_OK;
 }
 
