@@ -216,11 +216,12 @@ void ed_free_basis(ed_basis_t *b);
  * therefore searches every term once and keeps 4 bytes per term, where that is
  * at most 1/16 of the device's memory and half of what is free (hash-slot
  * index; row index and coefficient class must fit the 32 bits); H.v, Lanczos
- * and adjoint then read it instead of searching, with the same results bit for
- * bit.  For a larger sector, a Lanczos call of 8 steps or more (counting both
+ * and adjoint then read it instead of searching.  y and gx are the same bit for
+ * bit either way; so are alpha, beta and psi0 of sectors whose vectors exceed
+ * 32 MB.  Those of smaller sectors, and gJ, agree up to the rounding of their
+ * sums.  For a larger sector, a Lanczos call of 8 steps or more (counting both
  * passes where psi0 is asked for) stores terms while it lasts, in up to half
- * of the memory that is then free: all, or those of the first rows (on which
- * the last bits of alpha and beta depend).
+ * of the memory that is then free: all, or those of the first rows.
  * ed_basis_terms_bytes: device memory the basis keeps for it (0: none).
  * ed_basis_release_terms gives that memory back; later calls search again.
  * Synchronises the device.

@@ -709,27 +709,32 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
     return t;
 }
 
-// the sum of n partial sums, by all threads of a block in a fixed order; every
-// thread gets it (sh: one double per wave and one more)
+// the sum of n partial sums, by four waves' worth of lanes in an order that does
+// not depend on the block's size; every thread gets it (sh: one double per wave
+// and one more, at least four)
 __device__ __forceinline__ double total_of(const double *partials, int n, double *sh)
 {
-    double a = 0.0;
-    // eight reads at a time: they are one latency, not eight
-    for (int k0 = threadIdx.x; k0 < n; k0 += 8 * blockDim.x) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u * (int)blockDim.x;
-            v[u] = k < n ? partials[k] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a += v[u];
-    }
-    const double t = block_sum(a, sh);
-    double *res = sh + blockDim.x / kWave;
-    if (threadIdx.x == 0) *res = t;
+    constexpr int kSumWaves = 4;
+    const int lane = threadIdx.x & (kWave - 1);
     __syncthreads();
-    return *res;
+    for (int w = threadIdx.x / kWave; w < kSumWaves; w += blockDim.x / kWave) {
+        double a = 0.0;
+        // eight reads at a time: they are one latency, not eight
+        for (int k0 = w * kWave + lane; k0 < n; k0 += 8 * kSumWaves * kWave) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + u * kSumWaves * kWave;
+                v[u] = k < n ? partials[k] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a += v[u];
+        }
+        a = wave_sum(a);
+        if (lane == 0) sh[w] = a;
+    }
+    __syncthreads();
+    return sh[0] + sh[1] + sh[2] + sh[3];
 }
 
 // First thing of a step's H.v, by every thread of every block: beta of the

@@ -169,7 +169,6 @@ struct ed_basis {
         double *pair = nullptr;        // [dim + 1] {x, gy} scaled, made by the first fused adjoint
         double *adj = nullptr;         // per-bond partial sums, made by the first adjoint
         unsigned int *next = nullptr;  // slice counters of the 8 row ranges (nullptr: fixed stride)
-        double *dots = nullptr;        // [n_slices] <v, w> of a Lanczos step, with the counters
         double *cls = nullptr;         // [n_cls] coefficients of the current couplings
         double *cls_chi = nullptr;     // [n_cls] characters
         std::vector<double> chi_vals;  // distinct characters (re, im)
@@ -182,6 +181,7 @@ struct ed_basis {
     struct {
         double *vec[3] = {nullptr, nullptr, nullptr};
         double *partials = nullptr, *hist = nullptr;
+        double *dots = nullptr;        // <v, w> of every slice of 64 rows (lz_per_slice)
         int cap_steps = 0;
         size_t cap_partials = 0;
     } lzw;
@@ -253,7 +253,19 @@ inline bool terms_usable(const ed_basis *b) { return b->terms.words && b->terms.
 inline int64_t terms_rows(const ed_basis *b) { return std::min<int64_t>(b->db.dim, 64 * b->terms.n_slices); }
 // a sector whose scaled input fits the LDS of every block: its H.v reads x itself
 inline bool terms_small(const ed_basis *b) { return b->db.dim <= (b->dm.is_complex ? 2048 : 4096); }
-int terms_dots(const ed_basis *b);
+int terms_grid(const ed_basis *b);
+// Sectors whose input exceeds the L2s (8 x 4 MB) leave one <v, w> per slice of
+// 64 rows, whether these are stored or searched: alpha and beta then depend on
+// the sector and the start vector alone, and not on how many rows a table
+// holds.  (Its slices come from a counter, so that sums per block or wave would
+// differ from run to run.)
+constexpr int64_t kCountedBytes = 32 << 20;
+inline bool lz_per_slice(const ed_basis *b)
+{
+    return b->db.index_mode == 0 && (b->db.dim + 1) * (b->dm.is_complex ? 16 : 8) > kCountedBytes;
+}
+constexpr int kDotBlocks = 64;   // partial sums of the slices' <v, w>
+int sum_slices(const double *dots, int64_t n, double *partials, const void *lz, void *stream);
 constexpr int kTermsNextStride = 32;
 int terms_apply(const ed_basis *b, const void *x, void *y, double jsq, void *stream);
 int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *vprev, double *partials, const void *lz,

@@ -30,7 +30,8 @@ namespace ed {
 // One thread per row, persistent blocks, every y_i written once.  NS encodes
 // sublattices * 8 + chunks fixed at compile time (0: read at run time).
 // MODE 0: y = H x.  MODE 1: count kept/dropped terms.  MODE 2: Lanczos
-// w = H v - beta_prev v_prev with per-block <v, w> partial sums.
+// w = H v - beta_prev v_prev with <v, w> partial sums, one per block or
+// (per_slice) one per slice of 64 rows, as the stored terms leave them.
 // ---------------------------------------------------------------------------
 
 // FERMI: fermions in the occupation-number basis (4-byte or FermiU16 tables, hash
@@ -42,7 +43,8 @@ template <bool CPLX, typename AT, int INDEX, int MODE, int NS, bool FERMI = fals
 __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const typename Scalar<CPLX>::T *__restrict__ x,
                                                 typename Scalar<CPLX>::T *__restrict__ y,
                                                 const typename Scalar<CPLX>::T *__restrict__ vprev, double *partials,
-                                                unsigned long long *stats, LzStep lz, double jsum_quarter, int64_t row0)
+                                                unsigned long long *stats, LzStep lz, double jsum_quarter, int64_t row0,
+                                                bool per_slice)
 {
     extern __shared__ __align__(16) char lds[];
     __shared__ double sh[MODE == 2 ? 1024 / kWave + 1 : 1];
@@ -180,45 +182,52 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
                 }
             }
         }
-        if (MODE == 1 || !row_ok) continue;
-        const double d = FERMI ? fdiag : jsum_quarter - anti_sum;
-        if (CPLX) {
-            double2 xi = MODE == 2 ? *(const double2 *)&xi_pf : *(const double2 *)&x[i];
-            if (MODE == 2) {
-                xi.x *= inv;
-                xi.y *= inv;
-                ar *= inv;
-                ai *= inv;
+        if (MODE == 1) continue;
+        if (row_ok) {
+            const double d = FERMI ? fdiag : jsum_quarter - anti_sum;
+            if (CPLX) {
+                double2 xi = MODE == 2 ? *(const double2 *)&xi_pf : *(const double2 *)&x[i];
+                if (MODE == 2) {
+                    xi.x *= inv;
+                    xi.y *= inv;
+                    ar *= inv;
+                    ai *= inv;
+                }
+                double2 out;
+                out.x = fma(rs_i, ar, d * xi.x);
+                out.y = fma(rs_i, ai, d * xi.y);
+                if (MODE == 2) {
+                    const double2 vp = *(const double2 *)&vp_pf;
+                    out.x = fma(-beta_prev, inv_prev * vp.x, out.x);
+                    out.y = fma(-beta_prev, inv_prev * vp.y, out.y);
+                    acc_part = fma(xi.x, out.x, fma(xi.y, out.y, acc_part));   // Re(conj(v) w)
+                }
+                *(double2 *)&y[i] = out;
+            } else {
+                double xi = MODE == 2 ? *(const double *)&xi_pf : *(const double *)&x[i];
+                if (MODE == 2) {
+                    xi *= inv;
+                    ar *= inv;
+                }
+                double out = fma(rs_i, ar, d * xi);
+                if (MODE == 2) {
+                    out = fma(-beta_prev, inv_prev * *(const double *)&vp_pf, out);
+                    acc_part = fma(xi, out, acc_part);
+                }
+                *(double *)&y[i] = out;
             }
-            double2 out;
-            out.x = fma(rs_i, ar, d * xi.x);
-            out.y = fma(rs_i, ai, d * xi.y);
-            if (MODE == 2) {
-                const double2 vp = *(const double2 *)&vp_pf;
-                out.x = fma(-beta_prev, inv_prev * vp.x, out.x);
-                out.y = fma(-beta_prev, inv_prev * vp.y, out.y);
-                acc_part = fma(xi.x, out.x, fma(xi.y, out.y, acc_part));   // Re(conj(v) w)
-            }
-            *(double2 *)&y[i] = out;
-        } else {
-            double xi = MODE == 2 ? *(const double *)&xi_pf : *(const double *)&x[i];
-            if (MODE == 2) {
-                xi *= inv;
-                ar *= inv;
-            }
-            double out = fma(rs_i, ar, d * xi);
-            if (MODE == 2) {
-                out = fma(-beta_prev, inv_prev * *(const double *)&vp_pf, out);
-                acc_part = fma(xi, out, acc_part);
-            }
-            *(double *)&y[i] = out;
+        }
+        if (MODE == 2 && per_slice) {
+            const double ws = wave_sum(acc_part);
+            if (lane == 0) partials[i0 / kWave] = ws;
+            acc_part = 0.0;
         }
     }
     if (MODE == 1) {
         atomicAdd(&stats[0], kept);
         atomicAdd(&stats[1], dropped);
     }
-    if (MODE == 2) {
+    if (MODE == 2 && !per_slice) {
         // deterministic block reduction in LDS (the tables are no longer needed)
         __syncthreads();
         double *red = (double *)lds;
@@ -792,7 +801,8 @@ __global__ void __launch_bounds__(kVecThreads) k_scale_by_norm(const double *vin
 }
 
 // alpha = sum of <v, w> partials; w -= alpha v, v = inv * c; partial |w|^2;
-// sqrt(n) w to where the next H.v reads it; psi += s_j v (second pass)
+// sqrt(n) w to where the next H.v reads it; psi += s_j v (second pass).  The
+// operations are written out, so that every instance gives the same bits.
 template <bool CPLX, int TO>
 __global__ void __launch_bounds__(kVecThreads)
     k_lz_update(typename Scalar<CPLX>::T *w, const typename Scalar<CPLX>::T *c, int64_t D, const double *dots, int n_dots,
@@ -813,15 +823,15 @@ __global__ void __launch_bounds__(kVecThreads)
         if constexpr (CPLX) {
             v.x *= inv;
             v.y *= inv;
-            wi.x -= a * v.x;
-            wi.y -= a * v.y;
-            acc += wi.x * wi.x + wi.y * wi.y;
-            if (psi) psi[i] = make_double2(psi[i].x + sj * v.x, psi[i].y + sj * v.y);
+            wi.x = fma(-a, v.x, wi.x);
+            wi.y = fma(-a, v.y, wi.y);
+            acc = fma(wi.x, wi.x, fma(wi.y, wi.y, acc));
+            if (psi) psi[i] = make_double2(fma(sj, v.x, psi[i].x), fma(sj, v.y, psi[i].y));
         } else {
             v *= inv;
-            wi -= a * v;
-            acc += wi * wi;
-            if (psi) psi[i] += sj * v;
+            wi = fma(-a, v, wi);
+            acc = fma(wi, wi, acc);
+            if (psi) psi[i] = fma(sj, v, psi[i]);
         }
         w[i] = wi;
         if (TO != TO_NONE) put_scaled<CPLX, TO>(dst, i, sqrts[states[i] >> kNormShift], wi);
@@ -1460,7 +1470,8 @@ static int apply_impl(const ed_basis *b, const void *x, void *y, const void *vpr
         grid = b->grid_blocks;   // fixed grid so the reductions are deterministic
     }
     hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, b->dm, b->db, (const T *)x, (T *)y, (const T *)vprev,
-                       partials, stats, lz ? *lz : LzStep{}, jsq, MODE == 2 && terms_usable(b) ? terms_rows(b) : (int64_t)0);
+                       partials, stats, lz ? *lz : LzStep{}, jsq, MODE == 2 && terms_usable(b) ? terms_rows(b) : (int64_t)0,
+                       MODE == 2 && lz_per_slice(b));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "H.v launch failed: %s", hipGetErrorString(e));
     return ED_OK;
@@ -1814,7 +1825,7 @@ void free_lanczos_workspace(ed_basis *b)
         if (p) (void)hipFree(p);
         p = nullptr;
     }
-    for (double **p : {&W.partials, &W.hist}) {
+    for (double **p : {&W.partials, &W.hist, &W.dots}) {
         if (*p) (void)hipFree(*p);
         *p = nullptr;
     }
@@ -1873,6 +1884,7 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     const size_t vb = (size_t)nd * 8;
     auto &W = b->lzw;
     const size_t npart = (size_t)b->grid_blocks + (size_t)num_cus() * 8;   // any of the reductions
+    const bool per_slice = lz_per_slice(b);
     // the vectors are sized by the basis and kept between calls; only the
     // coefficient histories grow with n_steps
     if (!W.vec[0] || W.cap_partials < npart) {
@@ -1880,6 +1892,7 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         bool ok = true;
         for (int k = 0; k < 3; ++k) ok = ok && hipMalloc((void **)&W.vec[k], vb) == hipSuccess;
         ok = ok && hipMalloc((void **)&W.partials, 2 * npart * 8) == hipSuccess;
+        if (per_slice) ok = ok && hipMalloc((void **)&W.dots, (size_t)((D + kWave - 1) / kWave) * 8) == hipSuccess;
         if (!ok) {
             (void)hipGetLastError();
             free_lanczos_workspace(b);
@@ -1923,9 +1936,10 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     if (rc) return rc;
     const int to = input_place(b);
     const bool small = to == TO_TERMS && terms_small(b);   // one launch does all steps
-    // <v, w> partials: of the stored rows, then of the searched ones
-    const int np_terms = terms_usable(b) ? terms_dots(b) : 0;
-    const int np_apply = np_terms + (to == TO_TERMS ? 0 : b->grid_blocks);
+    // <v, w> partials: of the stored rows, then of the searched ones, or one
+    // per slice of either
+    const int np_terms = terms_usable(b) && !per_slice ? terms_grid(b) : 0;
+    const int np_apply = per_slice ? kDotBlocks : np_terms + (to == TO_TERMS ? 0 : b->grid_blocks);
     for (int pass = 0; pass < passes; ++pass) {
         double *psi = pass == 1 ? (double *)psi0 : nullptr;
         LzState init[2] = {};
@@ -1955,7 +1969,7 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         auto step_of = [&](int step) {
             LzStep s;
             s.cur = lz + (step & 1);
-            s.next = lz + (step & 1 ^ 1);
+            s.next = lz + ((step & 1) ^ 1);
             s.norms = norms;
             s.n_norms = vgrid;
             s.n_steps = n_steps;
@@ -1968,9 +1982,10 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
         for (; !small && step < n_steps; ++step) {
             double *w = W.vec[(step + 1) % 3];
             const LzStep ls = step_of(step);
-            if (np_terms) rc = terms_lanczos_apply(b, cur, w, prev, partials, &ls, jsq, st);
-            if (!rc && to != TO_TERMS)
-                rc = apply_dispatch<2>(b, cur, w, prev, partials + np_terms, nullptr, &ls, jsq, st);
+            double *dots = per_slice ? W.dots : partials;
+            if (terms_usable(b)) rc = terms_lanczos_apply(b, cur, w, prev, dots, &ls, jsq, st);
+            if (!rc && to != TO_TERMS) rc = apply_dispatch<2>(b, cur, w, prev, dots + np_terms, nullptr, &ls, jsq, st);
+            if (!rc && per_slice) rc = sum_slices(W.dots, (D + kWave - 1) / kWave, partials, ls.next, st);
             if (rc) return rc;
 #define ED_UPDATE(CP, TO) \
     launch_lz_update<CP, TO>(b, vgrid, w, cur, partials, np_apply, norms, ls.next, ahist, psi, svec, st)

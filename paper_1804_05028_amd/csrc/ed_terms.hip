@@ -410,7 +410,6 @@ __global__ void __launch_bounds__(kTermsThreads)
 }
 
 // the slices' <v, w> in kDotBlocks partial sums
-constexpr int kDotBlocks = 64;
 __global__ void __launch_bounds__(kTermsThreads) k_terms_dots(const double *dots, int64_t n, double *partials, const LzState *lz)
 {
     __shared__ double sh[kTermsWaves];
@@ -467,9 +466,6 @@ int terms_grid(const ed_basis *b)
     return (int)std::min<int64_t>((blocks + 7) & ~7ll, (int64_t)(num_cus() * (b->terms.next ? 1 : 8) & ~7));
 }
 
-// partial sums that a Lanczos H.v leaves
-int terms_dots(const ed_basis *b) { return b->terms.next ? kDotBlocks : terms_grid(b); }
-
 static int terms_chunks(const ed_basis *b) { return terms_grid(b) % 8 == 0 ? 8 : 1; }
 
 template <bool CPLX, int MODE, bool FERMI>
@@ -489,13 +485,10 @@ static int launch_terms(const ed_basis *b, const void *x, void *y, const void *v
 #define ED_TERMS(COUNTED) \
     hipLaunchKernelGGL((k_terms_apply<CPLX, MODE, FERMI, COUNTED>), dim3(terms_grid(b)), dim3(kTermsThreads), lds, st, b->dm, \
                        terms_dev(b), b->db.states, b->db.dim, (const T *)b->terms.xs, (const T *)x, (T *)y, \
-                       (const T *)vprev, COUNTED ? b->terms.dots : partials, ls, jsq, terms_chunks(b), b->terms.next)
+                       (const T *)vprev, partials, ls, jsq, terms_chunks(b), b->terms.next)
         if (b->terms.next) ED_TERMS(true);
         else ED_TERMS(false);
 #undef ED_TERMS
-        if (MODE == 2 && b->terms.next)
-            hipLaunchKernelGGL(k_terms_dots, dim3(kDotBlocks), dim3(kTermsThreads), 0, st, (const double *)b->terms.dots,
-                               b->terms.n_slices, partials, (const LzState *)((const LzStep *)lz)->next);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(ED_ERR_HIP, "H.v launch failed: %s", hipGetErrorString(e));
@@ -518,6 +511,15 @@ static int terms_dispatch(const ed_basis *b, const void *x, void *y, const void 
 int terms_apply(const ed_basis *b, const void *x, void *y, double jsq, void *stream)
 {
     return terms_dispatch<0>(b, x, y, nullptr, nullptr, nullptr, jsq, stream);
+}
+
+int sum_slices(const double *dots, int64_t n, double *partials, const void *lz, void *stream)
+{
+    hipLaunchKernelGGL(k_terms_dots, dim3(kDotBlocks), dim3(kTermsThreads), 0, (hipStream_t)stream, dots, n, partials,
+                       (const LzState *)lz);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return set_error(ED_ERR_HIP, "slice sums: %s", hipGetErrorString(e));
+    return ED_OK;
 }
 
 int terms_lanczos_apply(const ed_basis *b, const void *v, void *w, const void *vprev, double *partials, const void *lz,
@@ -1127,12 +1129,12 @@ void terms_free(ed_basis *b)
 {
     auto &t = b->terms;
     for (void *p : {t.words, (void *)t.off, (void *)t.cnt, (void *)t.xs, (void *)t.pair, (void *)t.cls, (void *)t.cls_chi,
-                    (void *)t.next, (void *)t.dots, (void *)t.adj})
+                    (void *)t.next, (void *)t.adj})
         if (p) (void)hipFree(p);
     t.words = nullptr;
     t.off = nullptr;
     t.cnt = nullptr;
-    t.xs = t.pair = t.cls = t.cls_chi = t.dots = t.adj = nullptr;
+    t.xs = t.pair = t.cls = t.cls_chi = t.adj = nullptr;
     t.next = nullptr;
     b->device_bytes -= t.bytes;
     t.bytes = 0;
@@ -1394,13 +1396,13 @@ int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_ele
         if (t.n_slices < std::max<int64_t>(slices / 8, 1)) return give_up();
     }
     const size_t bytes = std::max<size_t>(groups, 1) * kGroupBytes;
-    // the scaled input exceeds the L2s (8 x 4 MB): slices from a counter
-    const bool counted = vec > (32u << 20) && !elem_class;
+    // the scaled input exceeds the L2s: slices from a counter
+    const bool counted = lz_per_slice(b) && !elem_class;
     const size_t clsb = (size_t)t.n_cls * (b->dm.is_complex ? 32 : 16);
     void *d_cls = nullptr;   // chi classes and bond orbits, needed by the search only
     if (!take(&t.words, bytes) || (!elem_class && !take((void **)&t.xs, vec)) || !take((void **)&t.cls, clsb) ||
         !take((void **)&t.cls_chi, clsb / 2) ||
-        (counted && (!take((void **)&t.next, 8 * kNextStride * 4) || !take((void **)&t.dots, (size_t)t.n_slices * 8))) ||
+        (counted && !take((void **)&t.next, 8 * kNextStride * 4)) ||
         hipMalloc(&d_cls, (cls.size() + orb.size()) * 2) != hipSuccess)
         return give_up();
     std::vector<double> chi((size_t)t.n_cls * (b->dm.is_complex ? 2 : 1), 0.0);

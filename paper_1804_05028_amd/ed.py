@@ -65,7 +65,8 @@ class Basis:
 
     def release_terms(self):
         """Give back the device memory of the stored terms; H.v, Lanczos and
-        adjoint then search each term again, with the same results."""
+        adjoint then search each term again: H.v and gx with the same bits, the
+        sums over rows (Lanczos of vectors up to 32 MB, gJ) up to rounding."""
         L.ed_basis_release_terms(self.handle)
 
     @property

@@ -1,5 +1,6 @@
-"""What a basis with stored terms keeps between calls: the coefficients that a
-captured H.v reads."""
+"""What a basis with stored terms keeps between calls, and what may not depend
+on it: the coefficients that a captured H.v reads, and the sums of a Lanczos
+call."""
 import numpy as np
 import pytest
 import torch
@@ -49,5 +50,48 @@ def test_replay_uses_the_current_exchange(make, last_bit):
             g.replay()
             torch.cuda.synchronize()
             assert torch.linalg.vector_norm(y - want) <= 1e-14 * torch.linalg.vector_norm(want)
+    finally:
+        b.close()
+
+
+def _square32(k, n_up):
+    c = lat.square((4, 4), (-4, 4), rotations=False, superlattice=wl.SQ_2X2)
+    return wl.Workload("square32", c, lat.characters(c, k), n_up, np.ones(c.n_bonds))
+
+
+# inputs above 32 MB: real, complex and fermionic
+LARGE = [("real", lambda: _square32(0, 12)), ("complex", lambda: _square32(1, 11)),
+         ("fermions", lambda: wl.triangular_36_tV(n_part=13))]
+
+
+def _basis(w, tuning=None):
+    from paper_1804_05028_amd import ed
+    return (ed.FermionBasis if hasattr(w, "t") else ed.Basis).from_workload(w, tuning)
+
+
+def _lanczos(b, w, v0, steps):
+    if hasattr(w, "t"):
+        return b.lanczos(w.t, v0, steps, want_psi0=True, V=w.V)
+    return b.lanczos(w.J, v0, steps, want_psi0=True)
+
+
+def _same(r, s, n):
+    return np.array_equal(r["alpha"][:n], s["alpha"][:n]) and np.array_equal(r["beta"][:n], s["beta"][:n])
+
+
+@pytest.mark.parametrize("name,make", LARGE, ids=[c[0] for c in LARGE])
+def test_lanczos_does_not_depend_on_the_table(name, make):
+    """Stored or searched, one start vector gives one alpha and beta."""
+    w = make()
+    b = _basis(w)
+    try:
+        print(f"[state] {name}: D={b.dim}", flush=True)
+        assert (b.dim + 1) * (16 if b.is_complex else 8) > 32 << 20
+        v0 = _vector(b)
+        r = _lanczos(b, w, v0, 5)
+        b.release_terms()
+        s = _lanczos(b, w, v0, 5)
+        assert _same(r, s, 5)
+        assert torch.equal(r["psi0"], s["psi0"])
     finally:
         b.close()
