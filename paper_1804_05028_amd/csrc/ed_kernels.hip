@@ -228,16 +228,9 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
         atomicAdd(&stats[1], dropped);
     }
     if (MODE == 2 && !per_slice) {
-        // deterministic block reduction in LDS (the tables are no longer needed)
-        __syncthreads();
-        double *red = (double *)lds;
-        red[threadIdx.x] = acc_part;
-        __syncthreads();
-        for (int o = blockDim.x >> 1; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
+        // wave by wave: blocks need not have a power of two of threads
+        const double t = block_sum(acc_part, sh);
+        if (threadIdx.x == 0) partials[blockIdx.x] = t;
     }
 }
 
@@ -1458,17 +1451,14 @@ static int apply_impl(const ed_basis *b, const void *x, void *y, const void *vpr
     using T = typename Scalar<CPLX>::T;
     auto kern = k_apply<CPLX, AT, INDEX, MODE, NS, FERMI>;
     int grid, threads;
-    size_t lds = b->dm.lds_total;
+    const size_t lds = b->dm.lds_total;
     launch_cfg(b, kern, lds, &grid, &threads);
     // a complex slot is read as two loads of a line that has to stay in L2 from
     // the first to the second: 16 waves per compute unit, also where more fit
     // (36-site momentum sector: 404.5 ms, with 24 waves 411.4)
     if (CPLX && INDEX == IDX_HASH && MODE == 0 && b->tuning.blocks_per_cu <= 0)
         grid = std::min(grid, std::max(1024 / threads, 1) * num_cus());
-    if (MODE == 2) {
-        lds = std::max(lds, (size_t)threads * 8);
-        grid = b->grid_blocks;   // fixed grid so the reductions are deterministic
-    }
+    if (MODE == 2) grid = b->grid_blocks;   // fixed grid so the reductions are deterministic
     hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, b->dm, b->db, (const T *)x, (T *)y, (const T *)vprev,
                        partials, stats, lz ? *lz : LzStep{}, jsq, MODE == 2 && terms_usable(b) ? terms_rows(b) : (int64_t)0,
                        MODE == 2 && lz_per_slice(b));
