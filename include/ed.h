@@ -224,7 +224,11 @@ void ed_free_basis(ed_basis_t *b);
  * of the memory that is then free: all, or those of the first rows.
  * ed_basis_terms_bytes: device memory the basis keeps for it (0: none).
  * ed_basis_release_terms gives that memory back; later calls search again.
- * Synchronises the device.
+ * Synchronises the device.  An H.v captured in a graph before it must not be
+ * replayed after it: the graph reads the freed table.
+ * A call on the handle that finds no room for memory it needs (the Lanczos
+ * vectors, the adjoint's buffers) gives the table back by itself and searches,
+ * unless an H.v of stored terms was captured from the handle.
  */
 int64_t ed_basis_terms_bytes(const ed_basis_t *b);
 int ed_basis_release_terms(ed_basis_t *b);

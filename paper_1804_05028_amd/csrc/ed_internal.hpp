@@ -154,7 +154,8 @@ struct ed_basis {
     // index for the search of the stored terms, freed after it
     ed::RepIndex rep_index{};
     uint16_t *rep_lists = nullptr;
-    bool want_terms = false;       // the basis may store its terms (not a batched one's)
+    bool want_terms = false;       // the basis may store its terms
+    struct ed_multi *owner = nullptr;  // the batched basis that this one's terms belong to
     // stored terms: the target and coefficient class of every off-diagonal
     // term (ed_terms.hip), made with the basis where they fit, freed with it
     // or by ed_basis_release_terms; or those of the first slices of 64 rows,
@@ -176,6 +177,7 @@ struct ed_basis {
         int n_orb = 0, n_cls = 0, ibits = 0;
         int64_t bytes = 0;
         bool couplings_ok = false;     // the current couplings are equal, bit for bit, on every orbit
+        bool captured = false;         // a captured H.v reads the table: it stays
     } terms;
     // Lanczos workspace, kept between calls and freed with the handle
     struct {
@@ -283,6 +285,9 @@ int multi_lanczos(ed_multi *mb, const double *J, const void *v0, int n_steps, do
                   int *n_done, int use_graph, void *stream);
 void multi_free_workspace(ed_multi *mb);
 int device_alloc(ed_basis *b, void **p, size_t bytes);
+hipError_t needed_malloc(ed_basis *b, void **p, size_t bytes);
+bool give_back(ed_basis *b);
+void note_capture(const ed_basis *b, hipStream_t st);
 void free_lanczos_workspace(ed_basis *b);
 const char *last_error();
 }  // namespace ed

@@ -845,13 +845,52 @@ __global__ void __launch_bounds__(kVecThreads) k_lz_finish(LzStep lz)
 // host side
 // ---------------------------------------------------------------------------
 
+// Gives back device memory that the handle holds only to be faster: the index
+// for the search of the terms, then the stored terms (unless a captured H.v may
+// read them when it is replayed).  False: nothing to give.
+bool give_back(ed_basis *b)
+{
+    if (b->rep_index.entries) {
+        free_rep_index(b);
+        return true;
+    }
+    if (!b->terms.words || b->terms.captured || hipDeviceSynchronize() != hipSuccess) return false;
+    if (b->owner)
+        multi_free_terms(b->owner);
+    else
+        terms_free(b);
+    return true;
+}
+
+// device memory that a call cannot do without
+hipError_t needed_malloc(ed_basis *b, void **p, size_t bytes)
+{
+    while (true) {
+        const hipError_t e = hipMalloc(p, bytes);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();
+        *p = nullptr;
+        if (!give_back(b)) return e;
+    }
+}
+
+// an H.v of stored terms on a stream that is being captured: its graph holds
+// the addresses of the table
+void note_capture(const ed_basis *bc, hipStream_t st)
+{
+    ed_basis *b = const_cast<ed_basis *>(bc);
+    if (!b->terms.words || b->terms.captured) return;
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) (void)hipGetLastError();
+    b->terms.captured = s != hipStreamCaptureStatusNone;
+}
+
 int device_alloc(ed_basis *b, void **p, size_t bytes)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(p, bytes);
+    const hipError_t e = needed_malloc(b, p, bytes);
     if (e != hipSuccess) {
-        (void)hipGetLastError();
         return set_error(ED_ERR_OOM, "hipMalloc(%zu bytes) failed: %s", bytes, hipGetErrorString(e));
     }
     b->allocs.push_back(*p);
@@ -1562,6 +1601,7 @@ int launch_apply(const ed_basis *b, const double *J, const double *Jz, const voi
     rc = upload_couplings(b, J, Jz, st, &jsq);
     if (rc) return rc;
     if (b->db.dim == 0) return ED_OK;
+    note_capture(b, st);
     if (terms_usable(b) && terms_small(b)) return terms_apply(b, x, y, jsq, stream);
     rc = pack_input(b, x, st);
     if (rc) return rc;
@@ -1673,9 +1713,8 @@ static int backward_impl(const ed_basis *b, const void *x, const void *gy, doubl
                              n_part + (size_t)(nb + 1), kScratchDoubles);
         partials = scratch_dev;
         out = scratch_dev + n_part;
-    } else if (hipMalloc((void **)&partials, n_part * 8) != hipSuccess ||
-               hipMalloc((void **)&out, (size_t)(nb + 1) * 8) != hipSuccess) {
-        (void)hipGetLastError();
+    } else if (needed_malloc(const_cast<ed_basis *>(b), (void **)&partials, n_part * 8) != hipSuccess ||
+               needed_malloc(const_cast<ed_basis *>(b), (void **)&out, (size_t)(nb + 1) * 8) != hipSuccess) {
         if (partials) (void)hipFree(partials);
         return set_error(ED_ERR_OOM, "adjoint partials");
     }
@@ -1755,7 +1794,9 @@ int launch_backward_J(const ed_basis *b, const double *J, const void *x, const v
             rc = pack_input(b, x, st);
             if (rc) return rc;
         }
-        return terms_backward(b, x, gy, gx, gJ_host, scratch_dev, kScratchDoubles, jsq, stream);
+        rc = terms_backward(b, x, gy, gx, gJ_host, scratch_dev, kScratchDoubles, jsq, stream);
+        // no room beside the table: it goes, and the terms are searched
+        if (rc != ED_ERR_OOM || !give_back(const_cast<ed_basis *>(b))) return rc;
     }
     // four sublattices with one to three chunks: search loops fixed at compile time
     const int nsc = (ix == IDX_HASH && b->dm.ns == 4 && b->dm.n_chunks <= 3) ? 32 + b->dm.n_chunks : 0;
@@ -1880,11 +1921,11 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     if (!W.vec[0] || W.cap_partials < npart) {
         free_lanczos_workspace(b);
         bool ok = true;
-        for (int k = 0; k < 3; ++k) ok = ok && hipMalloc((void **)&W.vec[k], vb) == hipSuccess;
-        ok = ok && hipMalloc((void **)&W.partials, 2 * npart * 8) == hipSuccess;
-        if (per_slice) ok = ok && hipMalloc((void **)&W.dots, (size_t)((D + kWave - 1) / kWave) * 8) == hipSuccess;
+        auto need = [&](void *at, size_t bytes) { ok = ok && needed_malloc(b, (void **)at, bytes) == hipSuccess; };
+        for (int k = 0; k < 3; ++k) need(&W.vec[k], vb);
+        need(&W.partials, 2 * npart * 8);
+        if (per_slice) need(&W.dots, (size_t)((D + kWave - 1) / kWave) * 8);
         if (!ok) {
-            (void)hipGetLastError();
             free_lanczos_workspace(b);
             return set_error(ED_ERR_OOM, "Lanczos vectors (3 x %zu bytes)", vb);
         }
@@ -1896,8 +1937,7 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
     if (W.cap_steps < n_steps) {
         if (W.hist) (void)hipFree(W.hist);
         W.hist = nullptr;
-        if (hipMalloc((void **)&W.hist, ((size_t)3 * n_steps + kStateDoubles) * 8) != hipSuccess) {
-            (void)hipGetLastError();
+        if (needed_malloc(b, (void **)&W.hist, ((size_t)3 * n_steps + kStateDoubles) * 8) != hipSuccess) {
             free_lanczos_workspace(b);
             return set_error(ED_ERR_OOM, "Lanczos coefficient history");
         }

@@ -908,6 +908,7 @@ static int multi_terms_build(ed_multi *mb, hipStream_t st)
     t.n_elem_classes = n_vec;
     int rc = terms_build(b, st, cls.data(), n_vec);
     if (rc || !b->terms.words) return rc;
+    b->owner = mb;
     const bool counted = (size_t)D * K * 16 > (32u << 20);
     if (!take((void **)&t.row_class, (size_t)D + 1) || !take(&t.row_table, rows.size() * sizeof(RowInfo)) ||
         !take(&t.chi, chi.size() * 8) || (counted && !take((void **)&t.next, 8 * kTermsNextStride * 4)))
@@ -1055,6 +1056,7 @@ int multi_apply(const ed_multi *mb, const double *J, const void *x, void *y, voi
     rc = upload_couplings(b, J, nullptr, st, &jsq);
     if (rc) return rc;
     if (b->db.dim == 0) return ED_OK;
+    note_capture(b, st);
     return multi_hv(mb, x, y, nullptr, nullptr, jsq, st);
 }
 
@@ -1149,12 +1151,12 @@ int multi_lanczos(ed_multi *mb, const double *J, const void *v0, int n_steps, do
     if (!W.vec[0] || W.cap_partials < npart) {
         multi_free_workspace(mb);
         bool ok = true;
-        for (int k = 0; k < 2; ++k) ok = ok && hipMalloc(&W.vec[k], vb) == hipSuccess;
-        ok = ok && hipMalloc((void **)&W.partials, npart * 8) == hipSuccess;
-        ok = ok && hipMalloc((void **)&W.sector, (size_t)K * sizeof(MlzSector)) == hipSuccess;
-        ok = ok && hipMalloc(&W.state, sizeof(MlzState)) == hipSuccess;
+        auto need = [&](void *at, size_t bytes) { ok = ok && needed_malloc(mb->base, (void **)at, bytes) == hipSuccess; };
+        for (int k = 0; k < 2; ++k) need(&W.vec[k], vb);
+        need(&W.partials, npart * 8);
+        need(&W.sector, (size_t)K * sizeof(MlzSector));
+        need(&W.state, sizeof(MlzState));
         if (!ok) {
-            (void)hipGetLastError();
             multi_free_workspace(mb);
             return set_error(ED_ERR_OOM, "batched Lanczos vectors (2 x %zu bytes)", vb);
         }
@@ -1166,9 +1168,9 @@ int multi_lanczos(ed_multi *mb, const double *J, const void *v0, int n_steps, do
             *p = nullptr;
         }
         bool ok = true;
-        for (double **p : {&W.ahist, &W.bhist}) ok = ok && hipMalloc((void **)p, (size_t)K * n_steps * 8) == hipSuccess;
+        for (double **p : {&W.ahist, &W.bhist})
+            ok = ok && needed_malloc(mb->base, (void **)p, (size_t)K * n_steps * 8) == hipSuccess;
         if (!ok) {
-            (void)hipGetLastError();
             multi_free_workspace(mb);
             return set_error(ED_ERR_OOM, "batched Lanczos coefficient history");
         }

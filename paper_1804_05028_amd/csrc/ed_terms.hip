@@ -1052,7 +1052,7 @@ int terms_backward(const ed_basis *bc, const void *x, const void *gy, void *gx, 
     if (gx && !b->terms.pair) {
         void *p = nullptr;
         const size_t bytes = ((size_t)D + 1) * 16 * W;
-        if (hipMalloc(&p, bytes) != hipSuccess) {
+        if (hipMalloc(&p, bytes) != hipSuccess) {   // the caller frees the table
             (void)hipGetLastError();
             return set_error(ED_ERR_OOM, "adjoint pairs (%zu bytes)", bytes);
         }
@@ -1138,7 +1138,7 @@ void terms_free(ed_basis *b)
     t.next = nullptr;
     b->device_bytes -= t.bytes;
     t.bytes = 0;
-    t.couplings_ok = false;
+    t.couplings_ok = t.captured = false;
 }
 
 // One coefficient per orbit: couplings that differ in their last bits within an

@@ -66,7 +66,8 @@ class Basis:
     def release_terms(self):
         """Give back the device memory of the stored terms; H.v, Lanczos and
         adjoint then search each term again: H.v and gx with the same bits, the
-        sums over rows (Lanczos of vectors up to 32 MB, gJ) up to rounding."""
+        sums over rows (Lanczos of vectors up to 32 MB, gJ) up to rounding.
+        Graphs captured before must not be replayed after it."""
         L.ed_basis_release_terms(self.handle)
 
     @property
@@ -223,7 +224,8 @@ class MultiBasis:
 
     def release_terms(self):
         """Give back the device memory of the stored terms; H.v and Lanczos
-        then search each term again, with the same results up to rounding."""
+        then search each term again, with the same results up to rounding.
+        Graphs captured before must not be replayed after it."""
         L.ed_multi_release_terms(self.handle)
 
     def sector_dims(self):

@@ -1,0 +1,133 @@
+"""Stored terms take memory that a basis can do without: calls that need more
+than is left beside the table free it and search."""
+import contextlib
+
+import numpy as np
+import pytest
+import torch
+
+from ed_inputs import lattice as lat
+from ed_inputs import vectors as vec
+from ed_inputs import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CHUNK = 32 << 20   # device memory that the filler leaves, at most
+
+
+def _square32(k, n_up):
+    c = lat.square((4, 4), (-4, 4), rotations=False, superlattice=wl.SQ_2X2)
+    return wl.Workload("square32", c, lat.characters(c, k), n_up, np.ones(c.n_bonds))
+
+
+def _vectors(b, shape=None):
+    if shape is None:
+        return [torch.as_tensor(vec.normal_vector(b.dim, seed=s, complex_=b.is_complex)).cuda() for s in (21, 22)]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    return torch.randn(shape, dtype=torch.complex128, device="cuda", generator=g)
+
+
+@contextlib.contextmanager
+def _little_left():
+    """All of the device's memory taken, without touching it, but less than a
+    chunk: the figure that the driver reports as free leaves some out."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    fill = [torch.empty(torch.cuda.mem_get_info()[0] - CHUNK, dtype=torch.uint8, device="cuda")]
+    try:
+        for _ in range(256):
+            try:
+                fill.append(torch.empty(CHUNK, dtype=torch.uint8, device="cuda"))
+            except torch.OutOfMemoryError:
+                break
+        print(f"[memory] {len(fill) - 1} chunks above the free figure", flush=True)
+        yield
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+
+
+def test_calls_that_need_the_tables_memory():
+    """Lanczos vectors, the fused adjoint's pairs and the batched Lanczos
+    vectors, each larger than what is left: the table goes, the results stay.
+    The searching kernels' sums over rows differ by a few times sqrt(rows) eps
+    of terms of order 20."""
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    w = _square32(0, 12)
+    dense = {"hash_load_pct": 90}   # the searching adjoint's slots fit where the table was
+    a, b = ed.Basis.from_workload(w), ed.Basis.from_workload(w, dense)
+    c = lat.square((4, 4), (-4, 4), rotations=False, superlattice=wl.SQ_2X2)
+    ws = [wl.Workload("square32", c, lat.characters(c, k), 10, np.ones(c.n_bonds)) for k in range(4)]
+    mb = ed.MultiBasis.from_workloads(ws)
+    try:
+        x, gy = _vectors(a)
+        gx = a.empty()
+        v0 = _vectors(mb, (mb.dim, mb.K))
+        ref = ed.Basis.from_workload(w, dense)
+        ref.release_terms()
+        want = ref.lanczos(w.J, x, 6)
+        want_gx = ref.empty()
+        want_gJ = L.ed_apply_H_backward(ref.handle, w.J, x, gy, want_gx, True, None)
+        ref.close()
+        mref = ed.MultiBasis.from_workloads(ws)
+        mref.release_terms()
+        mwant = mref.lanczos(w.J, v0, 4)
+        mref.close()
+        for h, bytes_of in ((a, L.ed_basis_terms_bytes), (b, L.ed_basis_terms_bytes), (mb, L.ed_multi_terms_bytes)):
+            assert bytes_of(h.handle) > 0
+        with _little_left():
+            print(f"[memory] Lanczos, D={a.dim}", flush=True)
+            r = a.lanczos(w.J, x, 6)
+        assert L.ed_basis_terms_bytes(a.handle) == 0
+        assert np.abs(r["alpha"] - want["alpha"]).max() <= 1e-11
+        assert np.abs(r["beta"] - want["beta"]).max() <= 1e-11
+        a.close()
+        with _little_left():
+            print("[memory] adjoint", flush=True)
+            gJ = L.ed_apply_H_backward(b.handle, w.J, x, gy, gx, True, None)
+        assert L.ed_basis_terms_bytes(b.handle) == 0
+        assert torch.equal(gx, want_gx)
+        assert np.abs(gJ - want_gJ).max() <= 1e-12 * np.abs(want_gJ).max()
+        b.close()
+        with _little_left():
+            print(f"[memory] batched Lanczos, D={mb.dim}", flush=True)
+            m = mb.lanczos(w.J, v0, 4)
+        assert L.ed_multi_terms_bytes(mb.handle) == 0
+        assert np.abs(m["alpha"] - mwant["alpha"]).max() <= 1e-11
+    finally:
+        for h in (a, b, mb):
+            h.close()
+
+
+def test_a_captured_table_stays():
+    """A table that a captured H.v reads is not freed: the call that does not
+    fit beside it fails as any does, and the graph replays."""
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    w = _square32(0, 12)
+    b = ed.Basis.from_workload(w)
+    try:
+        x, gy = _vectors(b)
+        buf, y = x.clone(), b.empty()
+        b.apply(w.J, buf, out=y)
+        want = b.apply(w.J, gy)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            b.apply(w.J, buf, out=y)
+        held = L.ed_basis_terms_bytes(b.handle)
+        with _little_left():
+            print(f"[memory] captured, D={b.dim}", flush=True)
+            with pytest.raises(L.EDError) as e:
+                b.lanczos(w.J, x, 6)
+            assert e.value.name == "ED_ERR_OOM" and L.ed_basis_terms_bytes(b.handle) == held > 0
+        buf.copy_(gy)
+        for _ in range(3):
+            y.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, want)
+    finally:
+        b.close()
