@@ -214,8 +214,9 @@ void ed_free_basis(ed_basis_t *b);
  * Stored terms.  The target of an off-diagonal term and the element that maps
  * it to its representative depend on the basis alone.  ed_build_basis(_fermions)
  * therefore searches every term once and keeps 4 bytes per term, where that is
- * at most 1/16 of the device's memory and half of what is free (hash-slot
- * index; row index and coefficient class must fit the 32 bits); H.v, Lanczos
+ * at most 1/16 of the device's memory and leaves half of it free, or takes less
+ * than 1/1024 of what is free (hash-slot index; row index and coefficient class
+ * must fit the 32 bits); H.v, Lanczos
  * and adjoint then read it instead of searching.  y and gx are the same bit for
  * bit either way; so are alpha, beta and psi0 of sectors whose vectors exceed
  * 32 MB.  Those of smaller sectors, and gJ, agree up to the rounding of their

@@ -1254,6 +1254,16 @@ static bool terms_possible(const ed_basis *b)
     return b->want_terms && b->db.index_mode == 0 && b->db.dim >= 1 && b->t.nb >= 1;
 }
 
+// Most bytes of a table that a basis keeps: 1/16 of the device's memory, and at
+// least half of it stays free, so that programs with many bases or large
+// tensors have what they had without tables (small tables, up to 1/1024 of what
+// is free, are kept in any case).
+static size_t keep_limit(size_t free_b, size_t total_b)
+{
+    const size_t half = total_b / 2;
+    return std::max(free_b / 1024, free_b > half ? std::min(total_b / 16, free_b - half) : (size_t)0);
+}
+
 // whether terms_build may find room: a quarter of the bonds, antiparallel in
 // about half of the rows, is a safe lower bound of the words
 bool terms_wanted(const ed_basis *b)
@@ -1262,7 +1272,7 @@ bool terms_wanted(const ed_basis *b)
     if (!terms_possible(b)) return false;
     if (b->db.dim < (1 << 16)) return true;
     return hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
-           (uint64_t)b->db.dim * (uint64_t)b->t.nb <= std::min(total_b / 16, free_b / 2);
+           (uint64_t)b->db.dim * (uint64_t)b->t.nb <= keep_limit(free_b, total_b);
 }
 
 // the first slices whose words take at most bytes; *groups: their groups.
@@ -1297,8 +1307,8 @@ void free_rep_index(ed_basis *b)
 }
 
 // Builds the table, if the sector can have one: a hash-slot basis with bonds,
-// a word that holds class and row, and a table of at most 1/16 of the device's
-// memory and half of what is free.  Anything else leaves the basis without
+// a word that holds class and row, and a table within keep_limit.  Anything
+// else leaves the basis without
 // one, to the searching kernels; only an error of the device is returned.  A
 // batched basis gives the classes of its elements (equal characters in every
 // sector), whose coefficients are then the couplings alone.  A call's own
@@ -1388,7 +1398,7 @@ int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_ele
         HIP_TRY(hipStreamSynchronize(st));
         groups = last_off + last_cnt;
     }
-    const size_t limit = call_limit ? call_limit : std::min(total_b / 16, free_b / 2);
+    const size_t limit = call_limit ? call_limit : keep_limit(free_b, total_b);
     t.n_slices = slices;
     if (groups * kGroupBytes + vec > limit) {
         if (!call_limit || t.stride || limit < vec) return give_up();

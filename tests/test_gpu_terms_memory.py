@@ -131,3 +131,28 @@ def test_a_captured_table_stays():
             assert torch.equal(y, want)
     finally:
         b.close()
+
+
+def test_half_of_the_memory_stays_free():
+    """Where more than half of the device's memory is in use, by tensors as by
+    other bases, a basis keeps no table of any size."""
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    torch.cuda.empty_cache()
+    free, total = torch.cuda.mem_get_info()
+    fill = torch.empty(max(free - total * 48 // 100, 1), dtype=torch.uint8, device="cuda")
+    try:
+        for w, kept in ((_square32(0, 12), False), (wl.square_4x4(), True)):
+            b = ed.Basis.from_workload(w)
+            try:
+                assert (L.ed_basis_terms_bytes(b.handle) > 0) == kept
+            finally:
+                b.close()
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    b = ed.Basis.from_workload(_square32(0, 12))
+    try:
+        assert L.ed_basis_terms_bytes(b.handle) > 0
+    finally:
+        b.close()
