@@ -122,6 +122,9 @@ typedef struct {
                                K > 32 always runs 4 lanes (ed_multi_info reports the count used)  */
     int32_t lanczos_direct; /* 0 or 1; ed_lanczos launches each step's two kernels directly either way
                                (replaying them from a HIP graph measured no faster)                */
+    int32_t stored_terms_mb; /* stored terms (see ed_basis_terms_bytes): 0 = as described there; -1 = none,
+                               neither with the basis nor for a Lanczos call; n > 0 = none of more
+                               than n MiB, within the limits described there                       */
 } ed_tuning_t;
 
 #define ED_SEARCH_ONE_STAGE 1
@@ -216,7 +219,7 @@ void ed_free_basis(ed_basis_t *b);
  * therefore searches every term once and keeps 4 bytes per term, where that is
  * at most 1/16 of the device's memory and leaves half of it free, or takes less
  * than 1/1024 of what is free (hash-slot index; row index and coefficient class
- * must fit the 32 bits); H.v, Lanczos
+ * must fit the 32 bits; tuning's stored_terms_mb); H.v, Lanczos
  * and adjoint then read it instead of searching.  y and gx are the same bit for
  * bit either way; so are alpha, beta and psi0 of sectors whose vectors exceed
  * 32 MB.  Those of smaller sectors, and gJ, agree up to the rounding of their

@@ -196,7 +196,7 @@ static int build_basis_common(const ed_lattice_t *lat, const ed_group_t *grp, co
         b->tuning.search_mode < 0 || b->tuning.search_mode > ED_SEARCH_TWO_STAGE ||
         (b->tuning.lanes_per_row != 0 && b->tuning.lanes_per_row != 1 && b->tuning.lanes_per_row != 2 &&
          b->tuning.lanes_per_row != 4) ||
-        (b->tuning.lanczos_direct != 0 && b->tuning.lanczos_direct != 1)) {
+        (b->tuning.lanczos_direct != 0 && b->tuning.lanczos_direct != 1) || b->tuning.stored_terms_mb < -1) {
         delete b;
         return set_error(ED_ERR_ARG, "tuning fields out of range");
     }
@@ -237,7 +237,7 @@ static int build_basis_common(const ed_lattice_t *lat, const ed_group_t *grp, co
     b->staged = two_stage_ok && (b->tuning.search_mode == ED_SEARCH_TWO_STAGE ||
                                  (b->tuning.search_mode == 0 && b->mean_candidates >= kTwoStageMinCandidates));
     dm.staged = b->staged;
-    b->want_terms = true;
+    b->want_terms = b->tuning.stored_terms_mb >= 0;
     rc = ed::launch_basis_build(b, stream);
     if (!rc && own_terms) {   // a batched basis stores its terms in multi_setup
         rc = ed::terms_build(b, stream);

@@ -1254,14 +1254,19 @@ static bool terms_possible(const ed_basis *b)
     return b->want_terms && b->db.index_mode == 0 && b->db.dim >= 1 && b->t.nb >= 1;
 }
 
+static size_t tuned_limit(const ed_basis *b)
+{
+    return b->tuning.stored_terms_mb > 0 ? (size_t)b->tuning.stored_terms_mb << 20 : SIZE_MAX;
+}
+
 // Most bytes of a table that a basis keeps: 1/16 of the device's memory, and at
 // least half of it stays free, so that programs with many bases or large
 // tensors have what they had without tables (small tables, up to 1/1024 of what
 // is free, are kept in any case).
-static size_t keep_limit(size_t free_b, size_t total_b)
+static size_t keep_limit(const ed_basis *b, size_t free_b, size_t total_b)
 {
     const size_t half = total_b / 2;
-    return std::max(free_b / 1024, free_b > half ? std::min(total_b / 16, free_b - half) : (size_t)0);
+    return std::min(tuned_limit(b), std::max(free_b / 1024, free_b > half ? std::min(total_b / 16, free_b - half) : (size_t)0));
 }
 
 // whether terms_build may find room: a quarter of the bonds, antiparallel in
@@ -1272,7 +1277,7 @@ bool terms_wanted(const ed_basis *b)
     if (!terms_possible(b)) return false;
     if (b->db.dim < (1 << 16)) return true;
     return hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
-           (uint64_t)b->db.dim * (uint64_t)b->t.nb <= keep_limit(free_b, total_b);
+           (uint64_t)b->db.dim * (uint64_t)b->t.nb <= keep_limit(b, free_b, total_b);
 }
 
 // the first slices whose words take at most bytes; *groups: their groups.
@@ -1398,7 +1403,7 @@ int terms_build(ed_basis *b, void *stream, const uint16_t *elem_class, int n_ele
         HIP_TRY(hipStreamSynchronize(st));
         groups = last_off + last_cnt;
     }
-    const size_t limit = call_limit ? call_limit : keep_limit(free_b, total_b);
+    const size_t limit = call_limit ? std::min(call_limit, tuned_limit(b)) : keep_limit(b, free_b, total_b);
     t.n_slices = slices;
     if (groups * kGroupBytes + vec > limit) {
         if (!call_limit || t.stride || limit < vec) return give_up();

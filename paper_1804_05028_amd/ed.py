@@ -29,7 +29,8 @@ class Basis:
     an optional dict with the fields of ed_tuning_t (all 0 = automatic):
     index_mode, limits_bits, block_threads, blocks_per_cu, chunk_bits,
     hash_load_pct, table_entry_bytes, search_mode (1 one-stage, 2 two-stage
-    representative search) and lanczos_direct (0 or 1: the steps are launched either way).
+    representative search), lanczos_direct (0 or 1: the steps are launched either way)
+    and stored_terms_mb (-1 = no stored terms, else the most MiB they may take).
     """
 
     _build = staticmethod(L.ed_build_basis)

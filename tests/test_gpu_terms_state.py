@@ -95,3 +95,66 @@ def test_lanczos_does_not_depend_on_the_table(name, make):
         assert torch.equal(r["psi0"], s["psi0"])
     finally:
         b.close()
+
+
+def _fermions24(k):
+    c = lat.square((6, 0), (0, 4), rotations=False, superlattice=wl.SQ_2X2)
+    return wl.FermionWorkload("fermions24", c, lat.characters(c, k), 12, np.ones(c.n_bonds), np.full(c.n_bonds, 0.7))
+
+
+# sector, a limit in MiB that holds some of its rows (about a third to two thirds
+# of its words): the call stores the first rows and searches the others
+PARTIAL = [("real", lambda: _square24(0), 8), ("complex", lambda: _square24(5), 9),
+           ("fermions", lambda: _fermions24(0), 8), ("fermions_complex", lambda: _fermions24(5), 9),
+           ("real_large", lambda: _square32(0, 12), 500), ("complex_large", lambda: _square32(1, 11), 320),
+           ("fermions_large", lambda: wl.triangular_36_tV(n_part=13), 1000)]
+
+
+@pytest.mark.parametrize("name,make,mb", PARTIAL, ids=[c[0] for c in PARTIAL])
+def test_lanczos_call_with_a_partial_table(name, make, mb):
+    """No table (-1), one that holds the first rows only, and one of all rows:
+    the same coefficients, bit for bit above 32 MB per vector, else within a few
+    times sqrt(rows) eps of terms of order 10 to 20 for the first steps; H.v is
+    the same in between."""
+    from paper_1804_05028_amd import _lib as L
+    w = make()
+    out = []
+    for limit in (-1, mb, 0):
+        b = _basis(w, {"stored_terms_mb": limit})
+        try:
+            held = L.ed_basis_terms_bytes(b.handle)
+            print(f"[state] {name}: D={b.dim} limit {limit} MiB, kept {held >> 20}", flush=True)
+            assert (held > 0) == (limit == 0)
+            if limit == 0:   # the smaller limit holds an eighth at least, and not all
+                assert held / 8 < mb << 20 < held * 0.95
+            x = _vector(b)
+            y = b.apply(w.t, x, V=w.V) if hasattr(w, "t") else b.apply(w.J, x)
+            r = _lanczos(b, w, x, 12)
+            z = b.apply(w.t, x, V=w.V) if hasattr(w, "t") else b.apply(w.J, x)
+            assert torch.equal(y, z) and L.ed_basis_terms_bytes(b.handle) == held
+            out.append((r, y))
+            large = (b.dim + 1) * (16 if b.is_complex else 8) > 32 << 20
+        finally:
+            b.close()
+    (s, y), rest = out[0], out[1:]
+    assert large == name.endswith("large")
+    for r, z in rest:
+        assert torch.equal(y, z) and r["n_done"] == s["n_done"] == 12
+        if large:
+            assert _same(r, s, 12) and torch.equal(r["psi0"], s["psi0"])
+        else:
+            assert np.abs(r["alpha"] - s["alpha"]).max() <= 1e-11
+            assert np.abs(r["beta"] - s["beta"]).max() <= 1e-11
+            # the same vector: s_j and v_j differ by what alpha and beta do
+            d = torch.vdot(r["psi0"], s["psi0"]).abs().item()
+            assert abs(d - 1.0) <= 1e-9
+
+
+def test_table_limit_is_checked():
+    from paper_1804_05028_amd import _lib as L
+    with pytest.raises(L.EDError) as e:
+        _basis(wl.square_4x4(), {"stored_terms_mb": -2})
+    assert e.value.name == "ED_ERR_ARG"
+    b = _basis(wl.square_4x4(), {"stored_terms_mb": 1})
+    assert 0 < L.ed_basis_terms_bytes(b.handle) <= 1 << 20
+    b.close()
