@@ -223,9 +223,13 @@ void ed_free_basis(ed_basis_t *b);
  * and adjoint then read it instead of searching.  y and gx are the same bit for
  * bit either way; so are alpha, beta and psi0 of sectors whose vectors exceed
  * 32 MB.  Those of smaller sectors, and gJ, agree up to the rounding of their
- * sums.  For a larger sector, a Lanczos call of 8 steps or more (counting both
+ * sums.  For a larger sector, a Lanczos call of 12 steps or more (counting both
  * passes where psi0 is asked for) stores terms while it lasts, in up to half
- * of the memory that is then free: all, or those of the first rows.
+ * of the memory that is then free: all, or those of the first rows.  The
+ * driver clears freed memory before it is used again, so that an allocation
+ * soon after such a call, of more than the other half, waits for it (29 ms per
+ * GB freed).  Until the call returns, other threads and handles find that half
+ * taken; stored_terms_mb bounds it or leaves it out.
  * ed_basis_terms_bytes: device memory the basis keeps for it (0: none).
  * ed_basis_release_terms gives that memory back; later calls search again.
  * Synchronises the device.  An H.v captured in a graph before it must not be

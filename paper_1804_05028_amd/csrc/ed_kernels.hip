@@ -1876,10 +1876,10 @@ static void launch_lz_update(const ed_basis *b, int vgrid, double *w, const doub
 // Steps from which a Lanczos call stores the terms of a sector whose table is
 // too large to keep.  40-site square, 130 of 142 GB: 0.9 s for the search
 // against 0.40 s saved per step (766 -> 366 ms; 20 steps 15.3 -> 8.1 s, also
-// one call after the other), so that 3 steps pay; but where free memory runs
-// short, a later allocation waits until the freed pages are cleared (29 ms per
-// GB, 3.8 s), which 12 steps pay.
-constexpr int kStoreSteps = 8;
+// one call after the other), so that 3 steps pay; but an allocation after the
+// call that needs the freed pages waits until they are cleared (29 ms per GB,
+// 3.8 s).  From 12 steps on the call gains more than both together.
+constexpr int kStoreSteps = 12;
 
 // In half of the free memory, so that the next call finds as much that need not
 // be cleared first: in three quarters all 142 GB fit and a step takes 0.31 s,
@@ -1956,7 +1956,7 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
             if (b) terms_free(b);
         }
     } call_terms;
-    if (!b->terms.words && n_steps * passes >= kStoreSteps && terms_couplings_equal(b, J) &&
+    if (!b->terms.words && (int64_t)n_steps * passes >= kStoreSteps && terms_couplings_equal(b, J) &&
         (!Jz || terms_couplings_equal(b, Jz))) {
         call_terms.b = b;
         rc = store_terms_for_call(b, st);
