@@ -1269,15 +1269,17 @@ static size_t keep_limit(const ed_basis *b, size_t free_b, size_t total_b)
     return std::min(tuned_limit(b), std::max(free_b / 1024, free_b > half ? std::min(total_b / 16, free_b - half) : (size_t)0));
 }
 
-// whether terms_build may find room: a quarter of the bonds, antiparallel in
-// about half of the rows, is a safe lower bound of the words
+// whether terms_build may find room, by half of the mean number of antiparallel
+// bonds over all configurations (a sector's rows have more or less than that
+// mean, by far less than a factor of two)
 bool terms_wanted(const ed_basis *b)
 {
     size_t free_b = 0, total_b = 0;
     if (!terms_possible(b)) return false;
     if (b->db.dim < (1 << 16)) return true;
+    const double n = b->n_up, N = b->t.N, anti = 2.0 * n * (N - n) / (N * (N - 1.0));
     return hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
-           (uint64_t)b->db.dim * (uint64_t)b->t.nb <= keep_limit(b, free_b, total_b);
+           (double)b->db.dim * b->t.nb * 4.0 * 0.5 * anti <= (double)keep_limit(b, free_b, total_b);
 }
 
 // the first slices whose words take at most bytes; *groups: their groups.

@@ -1,6 +1,7 @@
 """Stored terms take memory that a basis can do without: calls that need more
 than is left beside the table free it and search."""
 import contextlib
+import itertools
 
 import numpy as np
 import pytest
@@ -154,5 +155,22 @@ def test_half_of_the_memory_stays_free():
     b = ed.Basis.from_workload(_square32(0, 12))
     try:
         assert L.ed_basis_terms_bytes(b.handle) > 0
+    finally:
+        b.close()
+
+
+def test_a_table_that_fits_is_kept_at_low_filling():
+    """4 of 56 up: 0.13 of the 256 bonds are antiparallel, so that the words take
+    63 MiB, where a byte per row and bond would be 90."""
+    from paper_1804_05028_amd import _lib as L
+    from paper_1804_05028_amd import ed
+    pairs = np.array(list(itertools.combinations(range(56), 2)))
+    c = lat.chain(56, superlattice_period=7)
+    c.perm, c.flip = c.perm[:1], c.flip[:1]
+    c.bonds = pairs[np.random.default_rng(4).choice(len(pairs), 256, replace=False)].astype(c.bonds.dtype)
+    b = ed.Basis.from_workload(wl.Workload("random56", c, np.ones(1, complex), 4, np.ones(256)), {"stored_terms_mb": 75})
+    try:
+        assert b.dim == 367290
+        assert 60 << 20 < L.ed_basis_terms_bytes(b.handle) <= 75 << 20
     finally:
         b.close()
