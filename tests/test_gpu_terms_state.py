@@ -8,6 +8,8 @@ import torch
 from ed_inputs import lattice as lat
 from ed_inputs import vectors as vec
 from ed_inputs import workloads as wl
+from oracle import bruteforce as bf
+from oracle import lanczos as olz
 
 pytestmark = pytest.mark.gpu
 
@@ -158,3 +160,41 @@ def test_table_limit_is_checked():
     b = _basis(wl.square_4x4(), {"stored_terms_mb": 1})
     assert 0 < L.ed_basis_terms_bytes(b.handle) <= 1 << 20
     b.close()
+
+
+def _chain(n, sub, k, n_up):
+    c = lat.chain(n, superlattice_period=sub)
+    return wl.Workload(f"chain{n}", c, lat.characters(c, k), n_up, np.ones(c.n_bonds))
+
+
+def _open16():
+    c = lat.chain(16, superlattice_period=2)
+    c.perm, c.flip = c.perm[:1], c.flip[:1]
+    return wl.Workload("open16", c, np.ones(1, complex), 5, np.linspace(0.5, 1.5, c.n_bonds))
+
+
+# the sides of the 4096 (complex: 2048) rows up to which one launch does all steps
+ROUTES = [("square16", wl.square_4x4), ("square16_k5", lambda: wl.square_4x4(momentum_index=5)),
+          ("open16_4368", _open16), ("chain18_k1_2704", lambda: _chain(18, 3, 1, 9))]
+
+
+@pytest.mark.parametrize("released", [False, True])
+@pytest.mark.parametrize("name,make", ROUTES, ids=[c[0] for c in ROUTES])
+def test_every_lanczos_route_matches_the_oracle(name, make, released):
+    """One launch, two kernels a step over stored terms, and searched steps."""
+    w = make()
+    m = bf.Model.from_workload(w)
+    st, stab = bf.basis(m, w.n_up)
+    v0 = vec.normal_vector(len(st), seed=7, complex_=w.is_complex)
+    ref = olz.lanczos(lambda v: bf.apply(m, st, stab, v)[0], v0, 60)
+    b = _basis(w)
+    try:
+        if released:
+            b.release_terms()
+        r = b.lanczos(w.J, torch.as_tensor(v0).cuda(), 60, want_psi0=True)
+        assert np.abs(r["alpha"][:10] - ref["alpha"][:10]).max() < 1e-11
+        assert np.abs(r["beta"][:10] - ref["beta"][:10]).max() < 1e-11
+        assert abs(r["eigenvalues"][0] - ref["eigenvalues"][0]) < 1e-10
+        assert abs(torch.linalg.vector_norm(r["psi0"]).item() - 1.0) < 1e-12
+    finally:
+        b.close()
