@@ -6,7 +6,9 @@ per compute unit, one- or two-stage representative search), build the basis, tim
 on the current stream, and keep the fastest.  Configurations the library
 rejects (tables that do not fit in LDS, unsupported entry widths) are
 recorded and skipped.  Every candidate computes the same H.v; only its speed
-differs.  For batched sectors, autotune_batched picks the group size and
+differs.  These fields steer the searching kernels: where a basis stores its
+terms one kernel serves all of them, and the first candidate alone is timed
+(stored_terms_mb = -1 in the candidates tunes the search).  For batched sectors, autotune_batched picks the group size and
 the lanes per row of each group.
 """
 from __future__ import annotations
@@ -65,7 +67,11 @@ def autotune(make_workload, n_subs, candidates=None, reps=2, time_limit_s=None, 
     for ns in n_subs:
         w = make_workload(ns)
         sub_bits = w.cluster.n_sites // w.cluster.n_sublat
+        stored = False
         for tn in candidates(sub_bits):
+            # the same words, read by the same kernel
+            if stored and not tn.get("index_mode") and not tn.get("stored_terms_mb"):
+                continue
             if time_limit_s is not None and time.perf_counter() - t_start > time_limit_s:
                 break
             rec = {"n_sub": ns, "tuning": dict(tn)}
@@ -80,6 +86,7 @@ def autotune(make_workload, n_subs, candidates=None, reps=2, time_limit_s=None, 
             try:
                 rec["hv_ms"] = _time_apply(b, w.J, reps)
                 rec["info"] = b.info()
+                stored = stored or L.ed_basis_terms_bytes(b.handle) > 0
             finally:
                 b.close()
                 torch.cuda.empty_cache()
@@ -132,7 +139,8 @@ def autotune_batched(workloads, batches=(4, 8, 12, 16), lanes=(1, 2, 4), reps=1,
     The sectors run in consecutive groups of B (the last group holds the
     remainder).  For every B in `batches` and every group size that schedule
     needs, each lanes-per-row value is timed on the first sectors of that
-    size; the schedule with the smallest summed time wins.  Returns
+    size (the first value alone where the basis stores its terms, which it does
+    not steer); the schedule with the smallest summed time wins.  Returns
     {"batch", "groups": [(first, size, lanes_per_row)], "est_ms", "trials"}.
     """
     n = len(workloads)
@@ -140,18 +148,21 @@ def autotune_batched(workloads, batches=(4, 8, 12, 16), lanes=(1, 2, 4), reps=1,
     best_of = {}   # group size -> (ms, lanes)
     trials = []
     for K in schedule_sizes(n, batches):
-        for L in lanes:
-            mb = ed.MultiBasis.from_workloads(workloads[:K], {"lanes_per_row": L})
+        for n_lanes in lanes:
+            mb = ed.MultiBasis.from_workloads(workloads[:K], {"lanes_per_row": n_lanes})
             try:
                 ms = _time_batched(mb, J, reps)
+                stored = L.ed_multi_terms_bytes(mb.handle) > 0
             finally:
                 mb.close()
                 torch.cuda.empty_cache()
-            trials.append({"K": K, "lanes_per_row": L, "hv_ms": ms})
+            trials.append({"K": K, "lanes_per_row": n_lanes, "hv_ms": ms})
             if log:
-                log(f"[autotune] K={K} lanes_per_row={L}: {ms:.1f} ms")
+                log(f"[autotune] K={K} lanes_per_row={n_lanes}: {ms:.1f} ms")
             if K not in best_of or ms < best_of[K][0]:
-                best_of[K] = (ms, L)
+                best_of[K] = (ms, n_lanes)
+            if stored:
+                break
     return dict(plan_schedule(n, batches, best_of), trials=trials)
 
 
