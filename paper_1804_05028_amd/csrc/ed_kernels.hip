@@ -60,6 +60,12 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
     const double beta_prev = MODE == 2 ? st.beta_prev : 0.0;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    // The search's loops are a few instructions long and wait for their fetch, so
+    // that their place within 32 bytes shows where few waves run: at offset 16
+    // the Limits index takes 1.61 ms on the 20-site J1-J2 square and 149 us on
+    // 4x4, at offset 0 1.65 ms and 153 us, at others up to 1.77 ms and 159 us
+    // (hash slots 480 us and 56 us at either).
+    asm volatile(".p2align 6\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0");
     // wave-uniform row loop: every lane of a wave runs the same iterations
     for (int64_t i0 = row0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; i0 < D; i0 += stride) {
         const int64_t i = i0 + lane;
