@@ -2049,15 +2049,16 @@ int run_lanczos(const ed_basis *bc, const double *J, const double *Jz, const voi
             if (rc) return rc;
 #define ED_UPDATE(CP, TO) \
     launch_lz_update<CP, TO>(b, vgrid, w, cur, partials, np_apply, norms, ls.next, ahist, psi, svec, st)
+            const int upd = step + 1 < n_steps ? to : TO_NONE;   // the last w meets no H.v
             if (cplx) {
-                if (to == TO_TERMS) ED_UPDATE(true, TO_TERMS);
-                else if (to == TO_BOTH) ED_UPDATE(true, TO_BOTH);
-                else if (to == TO_SLOTS) ED_UPDATE(true, TO_SLOTS);
+                if (upd == TO_TERMS) ED_UPDATE(true, TO_TERMS);
+                else if (upd == TO_BOTH) ED_UPDATE(true, TO_BOTH);
+                else if (upd == TO_SLOTS) ED_UPDATE(true, TO_SLOTS);
                 else ED_UPDATE(true, TO_NONE);
             } else {
-                if (to == TO_TERMS) ED_UPDATE(false, TO_TERMS);
-                else if (to == TO_BOTH) ED_UPDATE(false, TO_BOTH);
-                else if (to == TO_SLOTS) ED_UPDATE(false, TO_SLOTS);
+                if (upd == TO_TERMS) ED_UPDATE(false, TO_TERMS);
+                else if (upd == TO_BOTH) ED_UPDATE(false, TO_BOTH);
+                else if (upd == TO_SLOTS) ED_UPDATE(false, TO_SLOTS);
                 else ED_UPDATE(false, TO_NONE);
             }
 #undef ED_UPDATE
