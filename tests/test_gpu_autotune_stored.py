@@ -1,5 +1,6 @@
 """The tuner on bases that store their terms: the fields it varies steer the
 searching kernels, so that it must not choose among them by noise."""
+import numpy as np
 import pytest
 
 from ed_inputs import lattice as lat
