@@ -68,6 +68,15 @@ MEASURED_INT_OPS = {
 }
 
 
+def lanes_run(mb):
+    """Lanes per row of the batched kernel that runs: from stored terms a lane
+    per sector (the next power of two), else what the search is tuned to."""
+    from paper_1804_05028_amd import _lib as L
+    if L.ed_multi_terms_bytes(mb.handle) > 0:
+        return 1 << (mb.K - 1).bit_length()
+    return mb.info()["lanes_per_row"]
+
+
 def kernel_digest():
     import hashlib
     h = hashlib.sha256()
@@ -163,7 +172,7 @@ def bench_allk(args):
         y.copy_(x)
         torch.cuda.synchronize()
         print(json.dumps({"hv_ms": ev0.elapsed_time(ev1) / reps, "K": mb.K, "shared_terms": int(sh),
-                          "lanes_per_row": mb.info()["lanes_per_row"], "copy_bytes_each_way": x.numel() * 16}))
+                          "lanes_per_row": lanes_run(mb), "copy_bytes_each_way": x.numel() * 16}))
         mb.close()
         return
 
@@ -387,7 +396,7 @@ def bench_gamma_batched(reps):
         b.close()
     mb = ed.MultiBasis.from_workloads(ws)
     try:
-        info = mb.info()
+        info, lanes = mb.info(), lanes_run(mb)
         gen = torch.Generator(device="cuda")
         gen.manual_seed(0)
         x = torch.randn((mb.dim, mb.K), dtype=torch.complex128, device="cuda", generator=gen)
@@ -410,7 +419,7 @@ def bench_gamma_batched(reps):
     return {"workload": "triangular36_gamma", "description": "36 T x C6v x flip, the 8 one-dimensional irreps at "
                                                               "Gamma, Sz=0", "n_sectors": len(ws),
             "per_sector_ms": per, "per_sector_total_ms": per_ms, "batched_ms": bat_ms, "speedup": per_ms / bat_ms,
-            "terms_per_hv": int(t.sum()), "shared_terms_per_hv": int(shared), "lanes_per_row": info["lanes_per_row"],
+            "terms_per_hv": int(t.sum()), "shared_terms_per_hv": int(shared), "lanes_per_row": lanes,
             "chi_in_lds": info["chi_in_lds"], "chi_signs": info["chi_signs"],
             "timing": f"torch.cuda events on the launch stream, mean of {reps}"}
 
@@ -482,7 +491,7 @@ def main():
     ap.add_argument("--table-entry-bytes", type=int, default=0)
     ap.add_argument("--search-mode", type=int, default=0, help="1 one-stage, 2 two-stage representative search")
     ap.add_argument("--lanczos-direct", action="store_true",
-                    help="ed_tuning_t.lanczos_direct = 1 (the Lanczos step kernels are launched directly either way)")
+                    help="sets ed_tuning_t.lanczos_direct, which has no effect")
     ap.add_argument("--block-threads", type=int, default=0)
     ap.add_argument("--blocks-per-cu", type=int, default=0)
     ap.add_argument("--hv-reps", type=int, default=5, help="extra timed H.v launches for the roofline")

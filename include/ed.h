@@ -113,15 +113,16 @@ typedef struct {
                                first and assemble only the candidates minimising it (2 to 4
                                sublattices, else ED_ERR_UNSUPPORTED); 0 = two-stage when a host
                                sample of the search averages at least 3 candidates               */
-    int32_t lanes_per_row;  /* batched H.v (ed_build_multi): 1, 2 or 4 lanes share a row, each
-                               running the row's searches and holding every lanes-th sector; 0 = 1 lane
+    int32_t lanes_per_row;  /* batched H.v without stored terms (ed_build_multi): 1, 2 or 4 lanes
+                               share a row, each running the row's searches and holding every lanes-th sector; 0 = 1 lane
                                for K <= 2, 2 lanes for K <= 8, else 4.  When |G| K 16 bytes of
                                characters exceed 32 KB they are read from HBM (or, for K <= 8 and
                                characters all +-1, staged as sign bits): then 0 = 1 lane for K <= 8,
                                and the count is raised to at least 2 for K > 8 and 4 for K > 16;
                                K > 32 always runs 4 lanes (ed_multi_info reports the count used)  */
-    int32_t lanczos_direct; /* 0 or 1; ed_lanczos launches each step's two kernels directly either way
-                               (replaying them from a HIP graph measured no faster)                */
+    int32_t lanczos_direct; /* 0 or 1, without effect (kept for callers that set it): ed_lanczos launches
+                               its kernels directly, replaying them from a HIP graph measured no
+                               faster                                                              */
     int32_t stored_terms_mb; /* stored terms (see ed_basis_terms_bytes): 0 = as described there; -1 = none,
                                neither with the basis nor for a Lanczos call; n > 0 = none of more
                                than n MiB, within the limits described there                       */
@@ -233,7 +234,9 @@ void ed_free_basis(ed_basis_t *b);
  * ed_basis_terms_bytes: device memory the basis keeps for it (0: none).
  * ed_basis_release_terms gives that memory back; later calls search again.
  * Synchronises the device.  An H.v captured in a graph before it must not be
- * replayed after it: the graph reads the freed table.
+ * replayed after it: the graph reads the freed table.  (A captured H.v keeps
+ * its path and sum_b Jz_b; the couplings it reads are the handle's current
+ * ones when it is replayed, of bonds of one orbit the first one's.)
  * A call on the handle that finds no room for memory it needs (the Lanczos
  * vectors, the adjoint's buffers) gives the table back by itself and searches,
  * unless an H.v of stored terms was captured from the handle.
@@ -268,10 +271,11 @@ int ed_apply_H(const ed_basis_t *b, const double *J, const void *x_dev, void *y_
 
 /*
  * Device timing of the H.v: reps (1..1000) launches of y = H x on stream,
- * with HIP events recorded on that stream around each launch's scatter of x
- * into the hash-slot index and around its H.v kernel.  *pack_ms and
- * *kernel_ms receive the mean duration of each per launch (the scatter is 0
- * for the Limits index).  Spin bases: J and Jz as for ed_apply_H_xxz;
+ * with HIP events recorded on that stream around each launch's scaling of x
+ * (into the stored terms' dense input or the hash slots) and around its H.v
+ * kernel.  *pack_ms and *kernel_ms receive the mean duration of each per
+ * launch (the Limits index, and sectors whose input fits LDS, have no scaling
+ * pass: *pack_ms is the time between two events).  Spin bases: J and Jz as for ed_apply_H_xxz;
  * fermionic bases: t and V of ed_apply_H_fermions.  Synchronises.
  */
 int ed_apply_H_timed(const ed_basis_t *b, const double *J, const double *Jz, const void *x_dev, void *y_dev,
@@ -380,10 +384,12 @@ int ed_lanczos_xxz(const ed_basis_t *b, const double *Jxy, const double *Jz, con
  * terms in the row form of ed_apply_H.  Synchronises if gJ_host is given.
  * gx must differ from gy and, when gJ is requested, from x (ED_ERR_ARG).
  * With both outputs on a basis with the hash-slot index, one pass computes
- * both from a second slot table holding x and gy, of 32 bytes per slot
- * (64 for complex sectors).  The first such call allocates that table, and
- * it is kept until ed_free_basis.  Its gx and gJ equal, bit for bit, those
- * of ed_apply_H on gy and of this call without gx.
+ * both.  With stored terms it reads pairs of x and gy, 16 bytes per row (32 for
+ * complex sectors), which the first such call allocates and which count in
+ * ed_basis_terms_bytes and go with the table.  Without, it reads a second slot
+ * table holding x and gy, of 32 bytes per slot (64), allocated by the first
+ * such call and kept until ed_free_basis.  Its gx and gJ equal, bit for bit,
+ * those of ed_apply_H on gy and of this call without gx.
  */
 int ed_apply_H_backward(const ed_basis_t *b, const double *J, const void *x_dev, const void *gy_dev,
                         void *gx_dev, double *gJ_host, void *stream);
@@ -425,9 +431,10 @@ typedef struct {
     int64_t n_slots;
     int64_t device_bytes;
     double build_ms;
-    int32_t lanes_per_row;      /* lanes per row of the batched H.v kernel     */
-    int32_t chi_in_lds;         /* 1: the character table is staged in LDS (counted in lds_bytes);
-                                   0: the kernel reads it from HBM through the caches            */
+    int32_t lanes_per_row;      /* lanes per row of the searching kernel; from stored terms the H.v runs a
+                                   lane per sector                             */
+    int32_t chi_in_lds;         /* searching kernel: 1: the character table is staged in LDS (counted in
+                                   lds_bytes); 0: the kernel reads it from HBM through the caches            */
     int32_t chi_signs;          /* 1: every character is +1 or -1 (real one-dimensional irreps)
                                    and the table is too large for LDS: the kernel stages one sign
                                    bit per sector and element instead (|G| bytes, in lds_bytes) */

@@ -157,9 +157,10 @@ struct ed_basis {
     bool want_terms = false;       // the basis may store its terms
     struct ed_multi *owner = nullptr;  // the batched basis that this one's terms belong to
     // stored terms: the target and coefficient class of every off-diagonal
-    // term (ed_terms.hip), made with the basis where they fit, freed with it
-    // or by ed_basis_release_terms; or those of the first slices of 64 rows,
-    // by a Lanczos call for its duration
+    // term (ed_terms.hip), made with the basis where they fit, freed with it,
+    // by ed_basis_release_terms or for an allocation that a call needs
+    // (give_back); or those of the first slices of 64 rows, by a Lanczos call
+    // for its duration
     struct {
         int64_t n_slices = 0;          // slices stored
         void *words = nullptr;         // groups of 64 lanes x 4 words, slice by slice
