@@ -1061,18 +1061,20 @@ static int upload_tables(ed_basis *b, hipStream_t st)
         return (uint32_t)pos;
     };
     // Entry widths that can hold an image: 1 byte (m <= 8, no position),
-    // 2 bytes (m <= 12) or 4 bytes, the wide ones with the block position.
+    // 2 bytes (m <= 12 and at most 16 blocks) or 4 bytes, the wide ones with the
+    // block position.
     // Automatic choice: fewest chunks (fewest lookups per block) that fit the
     // LDS budget, a wide entry if it fits at that chunk count; for a given
     // chunk count the narrowest equal split is the smallest table.
-    const int wide = m <= 12 ? 2 : 4;
+    const bool fits16 = m <= 12 && ns <= 16;   // image in bits 0-11, position in bits 12-15
+    const int wide = fits16 ? 2 : 4;
     // fermionic sign parities live in bit 15 of 2-byte entries (images of up
     // to 12 orbitals, block index below 8 in bits 12-14) or in bit 31 of
     // 4-byte ones; automatic choice: 2 bytes where they fit
     const bool fermi16 = m <= 12 && ns <= 8;
     int want_esz = b->fermion ? (b->tuning.table_entry_bytes == 4 || !fermi16 ? 4 : 2) : b->tuning.table_entry_bytes;
     if (want_esz == 1 && m > 8) want_esz = wide;
-    if (want_esz == 2 && m > 12) want_esz = 4;
+    if (want_esz == 2 && !fits16) want_esz = 4;
     int cb = m, esz = want_esz ? want_esz : wide;
     if (b->tuning.chunk_bits > 0) {
         cb = std::min(b->tuning.chunk_bits, m);

@@ -42,7 +42,7 @@ def table_layout(n_sub, sub_bits, n_perms, sym_entries, n_elems, n_bonds, comple
       * the bonds (24 B each);
       * for the two-stage search, 2 B per permutation (the source block at
         position 1 and its bit offset);
-      * the chunked action table, with 2-byte entries for blocks of up to 12 sites and
+      * the chunked action table, with 2-byte entries for up to 16 blocks of up to 12 sites and
         4-byte entries above.
     """
     pad = lambda n: (n + 15) // 16 * 16
@@ -51,7 +51,7 @@ def table_layout(n_sub, sub_bits, n_perms, sym_entries, n_elems, n_bonds, comple
     fixed = (pad(4 * n_sub * P) + pad(4 * (n_sub * P + sym_entries)) + pad(n_perms * n_sub)
              + pad((16 if complex_chi else 8) * n_elems) + pad(16 * n_div) + pad(4 * n_div)
              + pad(24 * max(n_bonds, 1)) + pad(2) + (pad(2 * n_perms) if two_stage else 0))
-    esz = 2 if sub_bits <= 12 else 4
+    esz = 2 if sub_bits <= 12 and n_sub <= 16 else 4
     for nc in range(1, sub_bits + 1):
         cb = math.ceil(sub_bits / nc)
         total = fixed + pad(n_perms * n_sub * nc * (1 << cb) * esz)
