@@ -173,22 +173,23 @@ __device__ __forceinline__ uint64_t find_rep(const Ctx<AT> &c, uint64_t s, uint3
 {
     const int N = c.N, m = c.m, ns = c.ns;
     const uint32_t P = c.mmask + 1;
-    uint32_t minr = 0xFFFFFFFFu, tie = 0;
+    uint32_t minr = 0xFFFFFFFFu;
+    uint64_t tie = 0;   // up to 56 blocks of one site
     for (int X = 0; X < ns; ++X) {
         const uint32_t sx = (uint32_t)(s >> (N - (X + 1) * m)) & c.mmask;
         const uint32_t r = c.rep[X * P + sx] & 0xFFFFu;
         if (r < minr) {
             minr = r;
-            tie = 1u << X;
+            tie = 1ull << X;
         } else if (r == minr) {
-            tie |= 1u << X;
+            tie |= 1ull << X;
         }
     }
     const uint64_t top = (uint64_t)minr << (N - m);
     uint64_t best = ~0ull;
     uint32_t bg = 0;
     while (tie) {
-        const int Y = __builtin_ctz(tie);
+        const int Y = __builtin_ctzll(tie);
         tie &= tie - 1;
         const uint32_t sy = (uint32_t)(s >> (N - (Y + 1) * m)) & c.mmask;
         const uint32_t off = c.rep[Y * P + sy] >> 16;

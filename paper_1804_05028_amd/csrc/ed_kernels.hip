@@ -21,6 +21,7 @@
 #include "ed_device.hpp"
 
 #include <mutex>
+#include <type_traits>
 
 namespace ed {
 
@@ -61,11 +62,11 @@ __global__ void __launch_bounds__(1024) k_apply(DevModel dm, DevBasis db, const 
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     // The search's loops are a few instructions long and wait for their fetch, so
-    // that their place within 32 bytes shows where few waves run: at offset 16
-    // the Limits index takes 1.61 ms on the 20-site J1-J2 square and 149 us on
-    // 4x4, at offset 0 1.65 ms and 153 us, at others up to 1.77 ms and 159 us
-    // (hash slots 480 us and 56 us at either).
-    asm volatile(".p2align 6\n s_nop 0\n s_nop 0\n s_nop 0\n s_nop 0");
+    // that their place within 32 bytes shows where few waves run: at offset 8
+    // the Limits index takes 1.61 ms on the 20-site J1-J2 square and 150 us on
+    // 4x4, at offsets 0, 16 and 24 1.62 to 1.65 ms and 152 to 155 us, without
+    // alignment up to 1.77 ms and 159 us (hash slots 479 to 485 and 57 us).
+    asm volatile(".p2align 6\n s_nop 0\n s_nop 0");
     // wave-uniform row loop: every lane of a wave runs the same iterations
     for (int64_t i0 = row0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; i0 < D; i0 += stride) {
         const int64_t i = i0 + lane;
@@ -561,10 +562,13 @@ __host__ __device__ inline uint64_t dead_block(const BuildParams &bp, uint64_t p
     return k < 0 ? 0ull : 1ull << (k < zeros ? k : zeros);
 }
 
-template <typename AT, bool EMIT>
+// WIDE: more than 32 sublattices (36-site chain, 4 of them: 53.7 ms with wide
+// words of tied blocks, 52.4 without)
+template <typename AT, bool EMIT, bool WIDE>
 __global__ void __launch_bounds__(1024) k_basis_enum(DevModel dm, BuildParams bp, uint32_t *counts, const uint64_t *offsets,
                                                      uint64_t *out, RepIndex ix)
 {
+    using Tie = std::conditional_t<WIDE, uint64_t, uint32_t>;
     extern __shared__ __align__(16) char lds[];
     const Ctx<AT> c = stage<AT>(dm, lds);
     const int N = c.N, m = c.m, ns = c.ns, R = bp.R, Pb = N - R;
@@ -618,7 +622,7 @@ __global__ void __launch_bounds__(1024) k_basis_enum(DevModel dm, BuildParams bp
                     if (k < k1) {
                         sgm = (pw << R) | bp.patterns[k];
                         // quick reject: every block's Rep must be >= the top block
-                        uint32_t tie = 0;
+                        Tie tie = 0;
                         keep = true;
                         for (int X = 0; X < ns; ++X) {
                             const uint32_t sx = (uint32_t)(sgm >> (N - (X + 1) * m)) & c.mmask;
@@ -627,11 +631,11 @@ __global__ void __launch_bounds__(1024) k_basis_enum(DevModel dm, BuildParams bp
                                 keep = false;
                                 break;
                             }
-                            if (rv == t) tie |= 1u << X;
+                            if (rv == t) tie |= (Tie)1 << X;
                         }
                         bool compat = true;
                         while (tie && keep) {
-                            const int Y = __builtin_ctz(tie);
+                            const int Y = WIDE ? __builtin_ctzll(tie) : __builtin_ctz((uint32_t)tie);
                             tie &= tie - 1;
                             const uint32_t sy = (uint32_t)(sgm >> (N - (Y + 1) * m)) & c.mmask;
                             const uint32_t off = c.rep[Y * P + sy] >> 16;
@@ -1263,7 +1267,7 @@ int scan_counts(const uint32_t *counts, uint64_t *offsets, uint64_t n_counts, vo
 }
 
 
-template <typename AT>
+template <typename AT, bool WIDE>
 static int build_impl(ed_basis *b, hipStream_t st)
 {
     Tables &t = b->t;
@@ -1334,12 +1338,12 @@ static int build_impl(ed_basis *b, hipStream_t st)
     const size_t lds = dm.lds_total;
     const int threads = (int)lds * 2 > lds_limit() ? 1024 : 256;
     int per_cu = 1;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_basis_enum<AT, true>, threads, lds);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_basis_enum<AT, true, WIDE>, threads, lds);
     per_cu = std::max(per_cu, 1);
     const uint64_t need = (np + threads / kWave - 1) / (threads / kWave);
     const uint64_t grid = std::max<uint64_t>(std::min<uint64_t>(need, (uint64_t)per_cu * num_cus()), 1);
     if (np > 0)
-        hipLaunchKernelGGL((k_basis_enum<AT, false>), dim3((unsigned)grid), dim3(threads), lds, st, dm, bp, counts,
+        hipLaunchKernelGGL((k_basis_enum<AT, false, WIDE>), dim3((unsigned)grid), dim3(threads), lds, st, dm, bp, counts,
                            (const uint64_t *)nullptr, (uint64_t *)nullptr, ix);
     if (hipGetLastError() != hipSuccess) {
         cleanup();
@@ -1393,7 +1397,7 @@ static int build_impl(ed_basis *b, hipStream_t st)
         }
     }
     if (D > 0)
-        hipLaunchKernelGGL((k_basis_enum<AT, true>), dim3((unsigned)grid), dim3(threads), lds, st, dm, bp,
+        hipLaunchKernelGGL((k_basis_enum<AT, true, WIDE>), dim3((unsigned)grid), dim3(threads), lds, st, dm, bp,
                            (uint32_t *)nullptr, (const uint64_t *)offsets, (uint64_t *)states, ix);
     if (hipGetLastError() != hipSuccess) {
         cleanup();
@@ -1470,9 +1474,11 @@ int launch_basis_build(ed_basis *b, void *stream)
     b->db.index_mode = b->tuning.index_mode == 1 ? IDX_LIMITS : IDX_HASH;
     int rc = upload_tables(b, st);
     if (rc) return rc;
-    if (b->dm.act_bytes == 1) return build_impl<uint8_t>(b, st);
-    if (b->dm.act_bytes == 2) return b->fermion ? build_impl<FermiU16>(b, st) : build_impl<uint16_t>(b, st);
-    return build_impl<uint32_t>(b, st);
+    if (b->dm.ns > 32)   // 1- or 4-byte entries
+        return b->dm.act_bytes == 1 ? build_impl<uint8_t, true>(b, st) : build_impl<uint32_t, true>(b, st);
+    if (b->dm.act_bytes == 1) return build_impl<uint8_t, false>(b, st);
+    if (b->dm.act_bytes == 2) return b->fermion ? build_impl<FermiU16, false>(b, st) : build_impl<uint16_t, false>(b, st);
+    return build_impl<uint32_t, false>(b, st);
 }
 
 // ---- H.v -----------------------------------------------------------------

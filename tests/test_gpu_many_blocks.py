@@ -1,6 +1,7 @@
 """Many sublattices: a block's position takes more than the four bits of a 2-byte
-table entry above 16 blocks.  Bases, H.v, adjoint and batched H.v against the
-oracle."""
+table entry above 16 blocks, and a word of 32 tied blocks does not do above 32
+(blocks of one site, with which any permutation group is stable).  Bases, H.v,
+adjoint and batched H.v against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 # sites, blocks, up spins
 SHAPES = [(16, 16, 6), (32, 16, 3), (17, 17, 8), (34, 17, 3), (36, 18, 3), (20, 20, 7), (40, 20, 3), (24, 24, 4),
-          (32, 32, 3)]
+          (32, 32, 3), (33, 33, 3), (40, 40, 3), (56, 56, 3)]
 TUNINGS = [{}, {"table_entry_bytes": 1}, {"table_entry_bytes": 2}, {"stored_terms_mb": -1}, {"index_mode": 1}]
 
 
@@ -56,7 +57,7 @@ def test_many_blocks(n, blocks, n_up, k):
 
 
 @pytest.mark.parametrize("terms", [0, -1])
-@pytest.mark.parametrize("n,blocks,n_up", [(17, 17, 8), (36, 18, 3)], ids=["17_in_17", "36_in_18"])
+@pytest.mark.parametrize("n,blocks,n_up", [(17, 17, 8), (36, 18, 3), (40, 40, 3)], ids=["17_in_17", "36_in_18", "40_in_40"])
 def test_many_blocks_batched(n, blocks, n_up, terms):
     from paper_1804_05028_amd import ed
     ws = [_chain(n, blocks, k, n_up) for k in (0, 1, 4)]
@@ -76,7 +77,7 @@ def test_many_blocks_batched(n, blocks, n_up, terms):
         mb.close()
 
 
-@pytest.mark.parametrize("n,blocks,n_part", [(20, 20, 5), (34, 17, 3)], ids=["20_in_20", "34_in_17"])
+@pytest.mark.parametrize("n,blocks,n_part", [(20, 20, 5), (34, 17, 3), (36, 36, 3)], ids=["20_in_20", "34_in_17", "36_in_36"])
 def test_many_blocks_fermions(n, blocks, n_part):
     from paper_1804_05028_amd import ed
     c = lat.chain(n, superlattice_period=blocks)
