@@ -670,6 +670,19 @@ int ed_tridiag_eigh(int32_t m, const double *alpha, const double *beta, double *
     if (m < 0 || (m > 0 && (!alpha || !evals))) return set_error(ED_ERR_ARG, "bad arguments");
     if (m > 1 && !beta) return set_error(ED_ERR_ARG, "null beta");
     if (m == 0) return ED_OK;
+    // squares of entries far from 1 leave the range of a double: solve the
+    // matrix scaled by a power of two (others are solved as they are)
+    double most = 0.0;
+    for (int k = 0; k < m; ++k) most = std::max({most, std::fabs(alpha[k]), k < m - 1 ? std::fabs(beta[k]) : 0.0});
+    if (std::isfinite(most) && most > 0.0 && (most < 1e-100 || most > 1e100)) {
+        const int e = std::ilogb(most);
+        std::vector<double> a(m), b(std::max(m - 1, 1), 0.0);
+        for (int k = 0; k < m; ++k) a[k] = std::ldexp(alpha[k], -e);
+        for (int k = 0; k < m - 1; ++k) b[k] = std::ldexp(beta[k], -e);
+        const int rc = ed_tridiag_eigh(m, a.data(), b.data(), evals, evec0);
+        for (int k = 0; !rc && k < m; ++k) evals[k] = std::ldexp(evals[k], e);
+        return rc;
+    }
     std::vector<double> b2(std::max(m - 1, 1), 0.0);
     double lo = alpha[0], hi = alpha[0];
     for (int k = 0; k < m; ++k) {
@@ -709,7 +722,8 @@ int ed_tridiag_eigh(int32_t m, const double *alpha, const double *beta, double *
             seed = seed * 6364136223846793005ull + 1442695040888963407ull;
             v[k] = 0.5 + (double)(seed >> 11) * (1.0 / 9007199254740992.0);
         }
-        const double pert = DBL_EPSILON * span;
+        // the floor keeps 1 / pert and its square finite where T is zero
+        const double pert = std::max(DBL_EPSILON * span, 1e-150);
         for (int iter = 0; iter < 4; ++iter) {
             rhs = v;
             // Gaussian elimination with partial pivoting on the tridiagonal
