@@ -227,7 +227,7 @@ void ed_free_basis(ed_basis_t *b);
  * sums.  For a larger sector, a Lanczos call of 12 steps or more (counting both
  * passes where psi0 is asked for) stores terms while it lasts, in up to half
  * of the memory that is then free: all, or those of the first rows.  The
- * driver clears freed memory before it is used again, so that an allocation
+ * GPU driver clears freed memory before it is used again, so that an allocation
  * soon after such a call, of more than the other half, waits for it (29 ms per
  * GB freed).  Until the call returns, other threads and handles find that half
  * taken; stored_terms_mb bounds it or leaves it out.
